@@ -490,49 +490,7 @@ hl_status build_tables(hl_plan_s* pl, std::vector<double>& tab, WeightMode wm) {
   const std::vector<double> Wq = weight_operator(pl, P, 0, wm);   // sum_k w_k kappa^k Lap^k
   hl_status st;
   if (d == 3) {
-    // 3D: explicit x pass, y and z merged into the table:
-    //   M[a_y, a_z][o][b_x] = scale * sum_{b_y, b_z} W(o, b) gy(b_y, a_y) gz(b_z, a_z)
-    // with gy / gz the sigma/delta pass coefficients (derivative pass for the
-    // component along that dimension).
-    auto gdim = [&](int k, int b, int a, int dH) -> double {
-      if (!dH) return H[b * N2 + MP + a];
-      return (b + 1 < N2) ? (b + 1) * H[(b + 1) * N2 + MP + a] / pl->h[k] : 0.0;
-    };
-    int t_end = 0;
-    auto pack3 = [&](const std::vector<double>& W, const std::vector<std::vector<int>>& outs, int fy, int fz,
-                     double scale, int off) -> hl_status {
-      int t = off;
-      for (int az = 0; az < MP; ++az)
-        for (int ay = 0; ay < MP; ++ay)
-          for (size_t o = 0; o < outs.size(); ++o) {
-            const int ox = outs[o][0], oy = outs[o][1], oz = outs[o][2];
-            const int orow = ox + N2 * (oy + N2 * oz);
-            const int ky = (oy + ay + fy) & 1, kz = (oz + az + fz) & 1;
-            for (int bx = 0; bx < N2; ++bx) {
-              double v = 0.0;
-              for (int bz = 0; bz < N2; ++bz)
-                for (int by = 0; by < N2; ++by) {
-                  const double w = W[(size_t)orow * P.size + bx + N2 * (by + N2 * bz)];
-                  if (w == 0.0) continue;
-                  if (((by + ay + fy) & 1) != ky || ((bz + az + fz) & 1) != kz)
-                    return fail(HL_ERR_ARG, "internal: 3D merged table mixes sigma and delta terms");
-                  v += w * gdim(1, by, ay, fy) * gdim(2, bz, az, fz);
-                }
-              v *= scale;
-              if (bx >= ox && ((bx - ox) & 1) == 0)
-                tab[t++] = v;
-              else if (v != 0.0)
-                return fail(HL_ERR_ARG, "internal: 3D merged table has a nonzero outside its pattern");
-            }
-          }
-      t_end = t;
-      return HL_OK;
-    };
-    if ((st = pack3(Wp, out_p, 0, 0, 1.0 / pl->h[0], ks.p_off[0])) != HL_OK) return st;
-    if ((st = pack3(Wp, out_p, 1, 0, 1.0, ks.p_off[1])) != HL_OK) return st;
-    if ((st = pack3(Wp, out_p, 0, 1, 1.0, ks.p_off[2])) != HL_OK) return st;
-    if ((st = pack3(Wq, out_g, 0, 0, 1.0, ks.u_off)) != HL_OK) return st;
-    if (ks.f_off >= 0) {
+    {
       // fully merged pressure table F[i][a][o] = A[e = upper corner in every
       // dimension][o][i][a] (A: the per-corner operator of the transposed
       // half-steps' construction); every other corner's block must equal it
@@ -543,7 +501,12 @@ hl_status build_tables(hl_plan_s* pl, std::vector<double>& tab, WeightMode wm) {
       const int nc = pl->nc;
       // tu[e'][i][a][s] holds A[1 - e'][s][i][a]: e' = 0 is the all-upper corner
       auto Ablk = [&](int e, int i, int s, int a) { return tu[((((size_t)(7 ^ e)) * 3 + i) * nc + a) * nc + s]; };
-      int t = ks.f_off;
+      // outputs stored even x index first
+      std::vector<int> rank(nc);
+      int n = 0;
+      for (int par = 0; par < 2; ++par)
+        for (int o = 0; o < nc; ++o)
+          if (((o % MP) & 1) == par) rank[o] = n++;
       for (int i = 0; i < 3; ++i)
         for (int a = 0; a < nc; ++a)
           for (int o = 0; o < nc; ++o) {
@@ -557,15 +520,18 @@ hl_status build_tables(hl_plan_s* pl, std::vector<double>& tab, WeightMode wm) {
               if (std::fabs(got - want) > 1e-12 * (std::fabs(F) + 1e-300) + 1e-300)
                 return fail(HL_ERR_ARG, "internal: fully merged 3D table lacks the sigma/delta symmetry");
             }
-            tab[t++] = F;
+            tab[ks.f_off + (i * nc + a) * nc + rank[o]] = F;
           }
-      t_end = t;
     }
-    if (ks.fu_off >= 0) {
+    {
       // fully merged velocity table Fu[a][o] = sum_b W_q(o, b) H[b_x][R_ax] H[b_y][R_ay] H[b_z][R_az]
       // (the upper corner's coefficient; the kernel's butterfly gives the
       // others their sign): every contributing b must share the parity of o
-      int t = ks.fu_off;
+      std::vector<int> rank(out_g.size());
+      int n = 0;
+      for (int par = 0; par < 2; ++par)
+        for (size_t o = 0; o < out_g.size(); ++o)
+          if ((out_g[o][0] & 1) == par) rank[o] = n++;
       for (int a = 0; a < pl->nc; ++a) {
         const int ad[3] = {a % MP, (a / MP) % MP, a / (MP * MP)};
         for (size_t o = 0; o < out_g.size(); ++o) {
@@ -582,12 +548,12 @@ hl_status build_tables(hl_plan_s* pl, std::vector<double>& tab, WeightMode wm) {
                     return fail(HL_ERR_ARG, "internal: fully merged velocity table mixes sigma and delta terms");
                 v += w * H[bx * N2 + MP + ad[0]] * H[by * N2 + MP + ad[1]] * H[bz * N2 + MP + ad[2]];
               }
-          tab[t++] = v;
+          tab[ks.fu_off + a * (int)out_g.size() + rank[o]] = v;
         }
       }
-      t_end = t;
     }
-    if (t_end != ks.table_words) return fail(HL_ERR_ARG, "internal: 3D table size mismatch");
+    if (ks.fu_off + pl->nc * (int)out_g.size() != ks.table_words)
+      return fail(HL_ERR_ARG, "internal: 3D table size mismatch");
     return HL_OK;
   }
   // x-component (2D): the slice pass gives the x-derivative in units of 1/h_x
@@ -893,7 +859,10 @@ bool make_grid(const hl_plan_s* pl, const int32_t* tile, int32_t ygroup, const i
   g->soff = soff;
   g->tx = tile[0];
   g->ty = tile[1];
-  g->pad = 0;
+  // whole 128-byte lines per row (the narrowest word of a row: FP32_COMP's BF16 lo words), and a state past the
+  // 256 MB last-level cache
+  const int64_t state = (int64_t)pl->nc * (pl->pnodes + pl->d * pl->unodes) * pl->word_bytes * pl->words_per_coef;
+  g->stream = ooff == 0 && (int64_t)oext[0] * pl->word_bytes % 128 == 0 && state > (int64_t)256 << 20;
   g->onodes = onodes;
   g->snodes = snodes;
   return true;

@@ -50,42 +50,13 @@
 #ifndef HL_SCHED_MASK
 #define HL_SCHED_MASK 0
 #endif
-// 3D half-steps (fully merged tables): load the next datum's 8 corners before the current
-// datum's arithmetic (HL_PREFETCH3: 0 never, 1 for FP64 storage, 2 always).
-// With FP64 words the half-steps wait on memory at 3-5 resident waves per
-// SIMD, and a second datum in flight per wave pays (256^3 u half-step 7.57 ->
-// 7.05 ms, p half-step 7.70 -> 7.61); FP32 (VALU-bound p half-step 2.97 ->
-// 3.14 ms) and the split FP32+BF16 storage (16 loads per datum: u half-step
-// 7.01 -> 15.3 ms) run slower with it.
-#ifndef HL_PREFETCH3
-#define HL_PREFETCH3 1
-#endif
-// Cache policy of the 3D half-steps' read-modify-write of their outputs: 2,
-// the non-temporal bit.  Each output word is read and written once per
-// half-step, while the corner words are read by up to 8 neighbouring nodes;
-// streaming the outputs leaves the L2 to the corners (256^3 m = 2 step: FP64
-// 14.68 -> 14.27 ms, FP32 6.20 -> 6.06 ms).
-#ifndef HL_STREAM_AUX
-#define HL_STREAM_AUX 2
-#endif
-// 1D and 2D: the same streaming of the outputs for FP64 and FP32_COMP words
-// (2D m = 3 1024^2 step: FP64 0.295 -> 0.267 ms, FP32_COMP 0.220 -> 0.202 ms);
-// not for FP32, whose 1024^2 state (201 MB) stays in the 256 MB MALL between
-// half-steps when its outputs are cached (0.098 -> 0.125 ms streamed).
-#ifndef HL_STREAM2D
-#define HL_STREAM2D 1
-#endif
-template <class S>
-constexpr bool kPrefetch3 = HL_PREFETCH3 == 2 || (HL_PREFETCH3 == 1 && S::kBytes == 8);
+// Buffer-instruction cache policy of streamed outputs (Grid::stream): the
+// non-temporal bit.
+constexpr int kStreamAux = 2;
 
 // Minimum waves per SIMD requested from the register allocator (0 = none).
 #ifndef HL_WAVES_PER_EU
 #define HL_WAVES_PER_EU 0
-#endif
-// 3D velocity half-step through the fully merged table (1) or the explicit x
-// pass plus the (y, z) merged table (0).
-#ifndef HL_U3_FULL
-#define HL_U3_FULL 1
 #endif
 // 3D tile extent in x and y (x * y = 256 work-items).
 #ifndef HL_TILE3_X
@@ -116,7 +87,15 @@ struct Grid {
   int32_t soff;       // lower corner of node j at index j + soff (-1 or 0)
   int32_t sext[3];    // corner (source) array extents
   int32_t tx, ty;     // tile extents in x and y = the workgroup shape (tx * ty <= 256)
-  int32_t pad;
+  // Outputs are read and written with the non-temporal policy.  Each output
+  // word is touched once per half-step, so streaming it leaves the caches to
+  // the corner words.  It pays only where every access covers whole 128-byte
+  // lines (a line shared by two accesses is otherwise fetched twice) and the
+  // state does not fit the 256 MB last-level cache, where cached outputs
+  // are still found by the next half-step (make_grid).  Measured, velocity
+  // half-step, streamed / cached: 3D m = 2 FP64 256^3 5.04 / 5.33 ms, 64^3
+  // 98 / 83 us; FP32 161x150x143 1006 / 684 us.
+  int32_t stream;
   int64_t onodes;     // output array nodes (plane size)
   int64_t snodes;     // source array nodes (plane size)
 };
@@ -150,6 +129,22 @@ __device__ __forceinline__ void pass1d(const T* L, const T* R, T* out) {
   }
 }
 
+// Tile coordinates of tile number t.
+template <int D>
+__device__ __forceinline__ void tile_coords(const Grid& g, int t, int32_t* c) {
+  c[0] = t % g.nt[0];
+  c[1] = c[2] = 0;
+  if constexpr (D > 1) {
+    const int r = t / g.nt[0];
+    const int grp_rows = g.ygroup * g.nt[2];  // tile rows (y, z) per group
+    const int grp = r / grp_rows;
+    const int rem = r - grp * grp_rows;
+    const int gy = min(g.ygroup, g.nt[1] - grp * g.ygroup);  // rows of y in this (possibly ragged) group
+    c[1] = grp * g.ygroup + rem % gy;
+    c[2] = rem / gy;
+  }
+}
+
 // Node of this work-item in workgroup `blk` of the grid's launch; false when
 // outside the grid.
 template <int D>
@@ -157,19 +152,11 @@ __device__ __forceinline__ bool node_of_block(const Grid& g, int blk, int32_t* j
   const int i = blk;
   const int t = (i % kXcds) * g.per_xcd + i / kXcds;
   if (t >= g.tiles) return false;
-  int tx = t % g.nt[0], ty = 0, tz = 0;
-  if constexpr (D > 1) {
-    const int r = t / g.nt[0];
-    const int grp_rows = g.ygroup * g.nt[2];  // tile rows (y, z) per group
-    const int grp = r / grp_rows;
-    const int rem = r - grp * grp_rows;
-    const int gy = min(g.ygroup, g.nt[1] - grp * g.ygroup);  // rows of y in this (possibly ragged) group
-    ty = grp * g.ygroup + rem % gy;
-    tz = rem / gy;
-  }
-  j[0] = tx * g.tx + threadIdx.x;
-  j[1] = ty * g.ty + threadIdx.y;
-  j[2] = tz;
+  int32_t c[3];
+  tile_coords<D>(g, t, c);
+  j[0] = c[0] * g.tx + threadIdx.x;
+  j[1] = c[1] * g.ty + threadIdx.y;
+  j[2] = c[2];
   return j[0] < g.K[0] && j[1] < g.K[1] && j[2] < g.K[2];
 }
 
@@ -208,45 +195,96 @@ __device__ __forceinline__ void corner_nodes(const Grid& g, const int32_t* j, ui
     cn[e] = node_index<D>((e & 1) ? hi[0] : lo[0], (e & 2) ? hi[1] : lo[1], (e & 4) ? hi[2] : lo[2], g.sext);
 }
 
-// entry <- f(entry) at node n0 of plane pl.  3D kernels address their planes
-// through buffer descriptors (scalar plane base, 32-bit per-lane offset), the
-// others through plain pointers.
-template <int D, class S, class F>
-__device__ __forceinline__ void update_entry(const typename S::View& v, int pl, uint32_t n0, F f) {
-  if constexpr (D == 3) {
-    const typename S::Planes pr = S::planes(v, pl);
-    S::template bstore<HL_STREAM_AUX>(pr, n0, f(S::template bload<HL_STREAM_AUX>(pr, n0)));
-  } else if constexpr (HL_STREAM2D && S::kBytes >= 6) {
-    S::update_nt(v, pl, n0, f);
-  } else {
-    S::update(v, pl, n0, f);
+// Entry of plane pl at node n0 of a half-step's output.  3D kernels address
+// their planes through buffer descriptors (scalar plane base, 32-bit per-lane
+// offset), the others through plain pointers.
+template <int D, class S, bool NT>
+__device__ __forceinline__ typename S::C load_output(const typename S::View& v, int pl, uint32_t n0) {
+  if constexpr (D == 3)
+    return S::template bload<NT ? kStreamAux : 0>(S::planes(v, pl), n0);
+  else if constexpr (NT)
+    return S::load_nt(v, pl, n0);
+  else
+    return S::load(v, pl, n0);
+}
+template <int D, class S, bool NT>
+__device__ __forceinline__ void store_output(const typename S::View& v, int pl, uint32_t n0, typename S::C x) {
+  if constexpr (D == 3)
+    S::template bstore<NT ? kStreamAux : 0>(S::planes(v, pl), n0, x);
+  else if constexpr (NT)
+    S::store_nt(v, pl, n0, x);
+  else
+    S::store(v, pl, n0, x);
+}
+
+// entry <- f(i, entry) for the N output planes plane(0) .. plane(N - 1) at node
+// n0.  The planes may alias as far as the compiler knows, so that written
+// entry by entry each load waits for the store before it: one memory latency
+// per plane.  The loads are therefore issued in batches of B, the next batch
+// before the stores of the current one (B = 9 in 3D; 3 in 2D, where more of
+// them cost resident wavefronts).  Velocity half-step: 3D m = 2 FP64 256^3
+// 6.14 -> 5.06 ms, 2D m = 3 FP32_COMP 1024^2 129 -> 95 us, FP64 512^2 35.5 ->
+// 28.9 us.
+template <int D, class S, int N, bool NT, class P, class F>
+__device__ __forceinline__ void update_outputs_as(const typename S::View& v, uint32_t n0, P plane, F f) {
+  using T = typename S::C;
+  constexpr int B = D == 3 ? 9 : 3;
+  T x[2][B];
+#pragma unroll
+  for (int i = 0; i < B; ++i)
+    if (i < N) x[0][i] = load_output<D, S, NT>(v, plane(i), n0);
+#pragma unroll
+  for (int c = 0; c * B < N; ++c) {
+    int zero = 0;  // 3D: opaque, so that plane bases are formed here and not all held from the start
+    if constexpr (D == 3) asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+      if ((c + 1) * B + i < N) x[(c + 1) & 1][i] = load_output<D, S, NT>(v, plane((c + 1) * B + i) + zero, n0);
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+      if (c * B + i < N) store_output<D, S, NT>(v, plane(c * B + i) + zero, n0, f(c * B + i, x[c & 1][i]));
   }
+}
+
+template <int D, class S, int N, class P, class F>
+__device__ __forceinline__ void update_outputs(const Grid& g, const typename S::View& v, uint32_t n0, P plane, F f) {
+  if (g.stream)
+    update_outputs_as<D, S, N, true>(v, n0, plane, f);
+  else
+    update_outputs_as<D, S, N, false>(v, n0, plane, f);
 }
 
 // p -= acc at node n0.
 template <int D, int M, class S>
-__device__ __forceinline__ void finish_pressure(const typename S::View& p, uint32_t n0, const typename S::C* acc) {
+__device__ __forceinline__ void finish_pressure(const Grid& g, const typename S::View& p, uint32_t n0,
+                                                const typename S::C* acc) {
   using T = typename S::C;
+  if constexpr (D == 2) {
+    // streamed 2D pressures one by one: FP64 m = 3 1024^2 114 us against 131
+    // batched (at 512^2, not streamed, 31.6 against 25.9)
+    if (g.stream) {
 #pragma unroll
-  for (int s = 0; s < Dims<D, M>::NC; ++s) update_entry<D, S>(p, s, n0, [&](T x) { return x - acc[s]; });
+      for (int s = 0; s < Dims<D, M>::NC; ++s) S::store_nt(p, s, n0, S::load_nt(p, s, n0) - acc[s]);
+      return;
+    }
+  }
+  update_outputs<D, S, Dims<D, M>::NC>(g, p, n0, [](int s) { return s; }, [&](int s, T x) { return x - acc[s]; });
 }
 
 // u_i[s] -= wscale * (s_i + 1) / h_i * Q[s + e_i]   (Q on the set G)
 template <int D, int M, class S>
-__device__ __forceinline__ void finish_velocity(const typename S::View& u, uint32_t n0, const typename S::C* Q,
-                                                typename S::C wscale, const typename S::C* ih) {
+__device__ __forceinline__ void finish_velocity(const Grid& g, const typename S::View& u, uint32_t n0,
+                                                const typename S::C* Q, typename S::C wscale, const typename S::C* ih) {
   using T = typename S::C;
   constexpr int MP = M + 1, NC = Dims<D, M>::NC;
+  T f[D];
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const T f = wscale * ih[i];
-#pragma unroll
-    for (int s = 0; s < NC; ++s) {
-      const T a = -(T)(digit(s, MP, i) + 1) * f;
-      const T q = Q[kGIndex<D, M>.g[i][s]];
-      update_entry<D, S>(u, i * NC + s, n0, [&](T x) { return fma(a, q, x); });
-    }
-  }
+  for (int i = 0; i < D; ++i) f[i] = wscale * ih[i];
+  update_outputs<D, S, D * NC>(g, u, n0, [](int t) { return t; }, [&](int t, T x) {
+    const int i = t / NC, s = t % NC;
+    const T a = -(T)(digit(s, MP, i) + 1) * f[i];
+    return fma(a, Q[kGIndex<D, M>.g[i][s]], x);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -338,7 +376,7 @@ __device__ __forceinline__ void p_half_body(typename S::View p, typename S::View
     // last component: interpolation pass in x, derivative in the merged table
     slice_pair_merge<D, M, false, 0, 1, S>(u, D - 1, cn, l, tab + TL::P_B_OFF + l * NNZ, acc);
   }
-  finish_pressure<D, M, S>(p, out_index<D>(g, j), acc);
+  finish_pressure<D, M, S>(g, p, out_index<D>(g, j), acc);
 }
 
 template <int D, int M, class S>
@@ -370,7 +408,7 @@ __device__ __forceinline__ void u_half_body(typename S::View u, typename S::View
 #pragma unroll
   for (int l = 0; l < MP; ++l) slice_pair_merge<D, M, true, 0, 0, S>(p, 0, cn, l, tab + TL::U_OFF + l * NNZ, Q);
   const T ih[3] = {ih0, ih1, ih2};
-  finish_velocity<D, M, S>(u, out_index<D>(g, j), Q, wscale, ih);
+  finish_velocity<D, M, S>(g, u, out_index<D>(g, j), Q, wscale, ih);
 }
 
 template <int D, int M, class S>
@@ -383,313 +421,409 @@ __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_kernel(typename S
 }
 
 // ---------------------------------------------------------------------------
-// 3D kernels.  A work-item interpolates explicitly only along x: for every
-// y/z datum pair (a_y, a_z) it loads the 8 corners' x-lines, applies the x
-// pass (derivative pass for the x-component of the pressure half-step), and
-// combines the four (y, z) corners into sigma/delta in y and in z.  The y and
-// z interpolation, the Cauchy-Kowalevsky weights and (for the y- and
-// z-components) the divergence are all in the runtime table (Merge3Spec).
+// 3D kernels.  Interpolation in x, y and z, the Cauchy-Kowalevsky weights and
+// the divergence are all in one runtime table (hl_layout.hpp TableLayout<3, M>):
+// per datum (one coefficient plane of one source field) a node's 8 corner
+// values are combined into sigma / delta in x, y and z, and every output takes
+// the one combination whose parity in each dimension is that of
+// o_k + a_k (+ 1 in the divergence dimension), times its table entry.
+//
+// What bounds these kernels is HBM, and how many distinct lines they keep in
+// flight: per datum a node needs 8 corner words of which 7 are shared with its
+// neighbours.  So a workgroup stages each datum's tile of source words (its
+// nodes' corners: (tx + 1) x (ty + 1) x 2) through LDS: every word is loaded
+// once per workgroup instead of up to 8 times.  The data go in groups of
+// kStageGroup: a group's words are loaded into registers (NE per work-item and
+// datum) while the previous group is computed, then written to one of two LDS
+// buffers, so that one barrier per group separates the writes of a group from
+// the reads of the group two before.  256^3, m = 2, pressure / velocity half-
+// step, every work-item loading its own corners -> staged: FP64 7.5 / 6.7 ->
+// 4.3 / 5.1 ms (the pressure half-step then reads and writes 21.7 GB at 5.0
+// TB/s, a device copy's rate), FP32 2.9 / 3.1 -> 2.3 / 2.6 ms, FP32_COMP
+// 5.1 / 6.8 -> 3.6 / 4.0 ms (a staged word is widened once, not once per
+// corner).  A loop over the lines of data in place of the unrolled code (the
+// sigma / delta choice made by signs) is 5 times smaller but runs 4.5 / 2.5 /
+// 4.0 ms.
+//
 // Coefficient planes are read through buffer descriptors, one per plane, with
 // a 32-bit per-lane offset: the kernels touch 4 (m+1)^3 planes, too many for
 // a 64-bit scalar base each.
 // ---------------------------------------------------------------------------
+constexpr int kStageGroup = 3;
 
-// X[k_y][k_z][b_x] for datum pair (a_y, a_z), whose m+1 coefficient planes
-// (a_x = 0..m) start at plane pl0; cn[e], e = e_x + 2 e_y + 4 e_z, are the
-// corners' node indices.
-template <int M, int FLIPX, class S>
-__device__ __forceinline__ void xlines(const typename S::View& f, int pl0, const uint32_t* cn,
-                                       typename S::C (&X)[2][2][2 * M + 2]) {
-  using T = typename S::C;
-  constexpr int MP = M + 1, N2 = 2 * M + 2;
-  // for large m keep the loads of different (a_y, a_z) blocks apart, or the
-  // scheduler clusters them and runs out of registers
-  if constexpr (M >= 3) __builtin_amdgcn_sched_barrier(0);
-  typename S::Planes pr[MP];
-#pragma unroll
-  for (int ax = 0; ax < MP; ++ax) pr[ax] = S::planes(f, pl0 + ax);
-  T Y[2][2][N2];  // [e_y][e_z][b_x]
-#pragma unroll
-  for (int ez = 0; ez < 2; ++ez)
-#pragma unroll
-    for (int ey = 0; ey < 2; ++ey) {
-      T Lv[MP], Rv[MP];
-#pragma unroll
-      for (int ax = 0; ax < MP; ++ax) {
-        Lv[ax] = S::bload(pr[ax], cn[0 + 2 * ey + 4 * ez]);
-        Rv[ax] = S::bload(pr[ax], cn[1 + 2 * ey + 4 * ez]);
-      }
-      pass1d<M, FLIPX>(Lv, Rv, Y[ey][ez]);
-    }
-#pragma unroll
-  for (int b = 0; b < N2; ++b) {
-    const T s0 = Y[1][0][b] + Y[0][0][b], d0 = Y[1][0][b] - Y[0][0][b];  // z = lower
-    const T s1 = Y[1][1][b] + Y[0][1][b], d1 = Y[1][1][b] - Y[0][1][b];  // z = upper
-    X[0][0][b] = s1 + s0;
-    X[0][1][b] = s1 - s0;
-    X[1][0][b] = d1 + d0;
-    X[1][1][b] = d1 - d0;
-  }
-}
-
-template <int M, bool VEL, int FY, int FZ, typename T, typename TP>
-__device__ __forceinline__ void merge3(TP Mt, int ay, int az, const T (&X)[2][2][2 * M + 2], T* acc) {
-  constexpr int NNZ = Merge3Spec<M, VEL, FY, FZ>::NNZ;
-  constexpr int kChunk = sizeof(T) == 8 ? 16 : 32;
-#pragma unroll
-  for (int t = 0; t < NNZ; ++t) {
-    if (t % kChunk == 0) __builtin_amdgcn_sched_barrier(HL_SCHED_MASK);
-    const int o = kMerge3<M, VEL, FY, FZ>.o[t];
-    const int bx = kMerge3<M, VEL, FY, FZ>.bx[t];
-    const int ky = kMerge3<M, VEL, FY, FZ>.ky[t][ay];
-    const int kz = kMerge3<M, VEL, FY, FZ>.kz[t][az];
-    acc[o] = fma(Mt[t], X[ky][kz][bx], acc[o]);
-  }
-}
-
-// Pressure half-step, 3D: the x interpolation is merged into the
-// table as well.  Per component i and datum a the 8 corners are combined into
-// sigma/delta in x, y and z (X[k], k = k_x + 2 k_y + 4 k_z, 0 = sigma); output
-// o takes the combination whose parity in each dimension is that of
-// o_k + a_k (+1 in the divergence dimension k = i), times F[i][a][o].  Per
-// node and component: 8 loads, 24 add/sub and 27 FMA per datum, against the
-// explicit x pass's 72 VALU per datum (at m = 2 the x pass costs more than
-// the table it saves).
-template <int M, class S, typename TP>
-__device__ __forceinline__ void p_half_3d_full_body(typename S::View p, typename S::View u, TP tab, Grid g,
-                                                    int blk) {
-  using T = typename S::C;
-  using TL = TableLayout<3, M>;
-  constexpr int MP = M + 1, NC = Dims<3, M>::NC;
-  int32_t j[3];
-  if (!node_of_block<3>(g, blk, j)) return;
-  uint32_t cn[8];
-  corner_nodes<3>(g, j, cn);  // dual q = j - 1 + e
-  T acc[NC];
-#pragma unroll
-  for (int s = 0; s < NC; ++s) acc[s] = T(0);
-  T vn[8];  // the next datum's corners, loaded one datum ahead
-  if constexpr (kPrefetch3<S>) {
-    const typename S::Planes pr = S::planes(u, 0);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) vn[e] = S::bload(pr, cn[e]);
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int a = 0; a < NC; ++a) {
-      // keep the scalar table loads of one datum together (SGPR pressure)
-      __builtin_amdgcn_sched_barrier(0);
-      T v[8];
-      if constexpr (kPrefetch3<S>) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = vn[e];
-        if (i * NC + a + 1 < 3 * NC) {
-          int zero;  // opaque: the plane base is formed here, not hoisted to the kernel start
-          asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
-          const typename S::Planes pn = S::planes(u, i * NC + a + 1 + zero);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) vn[e] = S::bload(pn, cn[e]);
-        }
-      } else {
-        const typename S::Planes pr = S::planes(u, i * NC + a);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = S::bload(pr, cn[e]);
-      }
-      T X[8];  // [k_x + 2 k_y + 4 k_z]
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {  // x: corners (2q, 2q+1)
-        X[2 * q] = v[2 * q + 1] + v[2 * q];
-        X[2 * q + 1] = v[2 * q + 1] - v[2 * q];
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = X[q];
-#pragma unroll
-      for (int kz = 0; kz < 2; ++kz)  // y: pairs (kx + 4 kz, kx + 2 + 4 kz)
-#pragma unroll
-        for (int kx = 0; kx < 2; ++kx) {
-          const T lo = v[kx + 4 * kz], hi = v[kx + 2 + 4 * kz];
-          X[kx + 4 * kz] = hi + lo;
-          X[kx + 2 + 4 * kz] = hi - lo;
-        }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {  // z: pairs (q, q + 4)
-        const T lo = X[q], hi = X[q + 4];
-        v[q] = hi + lo;
-        v[q + 4] = hi - lo;
-      }
-      const int ax = a % MP, ay = (a / MP) % MP, az = a / (MP * MP);
-#pragma unroll
-      for (int o = 0; o < NC; ++o) {
-        const int ox = o % MP, oy = (o / MP) % MP, oz = o / (MP * MP);
-        const int k = ((ox + ax + (i == 0)) & 1) + 2 * ((oy + ay + (i == 1)) & 1) + 4 * ((oz + az + (i == 2)) & 1);
-        acc[o] = fma(tab[TL::F_OFF + (i * NC + a) * NC + o], v[k], acc[o]);
-      }
-    }
-  finish_pressure<3, M, S>(p, out_index<3>(g, j), acc);
-}
-
-template <int M, class S, typename TP>
-__device__ __forceinline__ void p_half_3d_body(typename S::View p, typename S::View u,
-                                               TP tab, Grid g, int blk) {
-  using T = typename S::C;
-  using TL = TableLayout<3, M>;
-  constexpr int MP = M + 1, NC = Dims<3, M>::NC, N2 = 2 * M + 2;
-  constexpr int NNZ = Merge3Spec<M, false, 0, 0>::NNZ;
-  int32_t j[3];
-  if (!node_of_block<3>(g, blk, j)) return;
-  uint32_t cn[8];
-  corner_nodes<3>(g, j, cn);  // dual q = j - 1 + e (p) or primal j = q + e (u)
-  T acc[NC];
-#pragma unroll
-  for (int s = 0; s < NC; ++s) acc[s] = T(0);
-#pragma unroll
-  for (int az = 0; az < MP; ++az)
-#pragma unroll
-    for (int ay = 0; ay < MP; ++ay) {
-      const int blk = ay + MP * az;
-      {
-        T X[2][2][N2];
-        xlines<M, 1, S>(u, MP * blk, cn, X);
-        merge3<M, false, 0, 0>(tab + TL::p_off(0) + blk * NNZ, ay, az, X, acc);
-      }
-      {
-        T X[2][2][N2];
-        xlines<M, 0, S>(u, NC + MP * blk, cn, X);
-        merge3<M, false, 1, 0>(tab + TL::p_off(1) + blk * NNZ, ay, az, X, acc);
-      }
-      {
-        T X[2][2][N2];
-        xlines<M, 0, S>(u, 2 * NC + MP * blk, cn, X);
-        merge3<M, false, 0, 1>(tab + TL::p_off(2) + blk * NNZ, ay, az, X, acc);
-      }
-    }
-  finish_pressure<3, M, S>(p, out_index<3>(g, j), acc);
-}
-
+// Wavefront classes of a workgroup: the outputs are split over NS = 1 or 2
+// classes of wavefronts by the parity of their x index, all reading the same
+// staged words.  A class forms only the sigma or the delta in x that its
+// outputs take, so no arithmetic is repeated.  Split where the accumulators
+// of all outputs would leave too few resident wavefronts.
 template <int M, class S>
-__global__ void __launch_bounds__(256, HL_WAVES_PER_EU) p_half_3d(typename S::View p, typename S::View u,
-                                                                   const typename S::C* __restrict__ tab, Grid g) {
-  if constexpr (TableLayout<3, M>::FULL_P)
-    p_half_3d_full_body<M, S, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
-  else
-    p_half_3d_body<M, S, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
+constexpr int kPSplit = M >= 3 ? 2 : 1;
+template <int M, class S>
+constexpr int kUSplit = M >= 2 ? 2 : 1;
+// Node layers in z of a workgroup's tile: TZ layers stage TZ + 1 planes, so
+// two layers fetch 1.5 planes per layer instead of 2 (FP64 256^3 pressure
+// half-step: 19.8 -> 18.1 GB read, 4.73 -> 4.43 ms).  Its workgroups are
+// twice as large: only where at least kLayeredTiles of them remain (two per
+// CU); 40^3 FP32 runs 39 us with one layer, 51 us with two.
+template <int M, class S>
+constexpr int kPLayers = M >= 3 ? 1 : 2;
+constexpr int kLayeredTiles = 512;
+
+// Work-items of one class: the tile rounded up to whole wavefronts.
+__host__ __device__ constexpr int class_items(int tx, int ty, int tz) { return (tx * ty * tz + 63) / 64 * 64; }
+// Staged words of a tile, and whether NE words per work-item cover them.
+__host__ __device__ constexpr int stage_words(int tx, int ty, int tz) { return (tz + 1) * (tx + 1) * (ty + 1); }
+__host__ __device__ constexpr bool stage_fits(int tx, int ty, int tz, int ns, int ne) {
+  return stage_words(tx, ty, tz) <= ne * ns * class_items(tx, ty, tz);
+}
+// Words per work-item and datum for the default 64 x 4 tile, and for any tile
+// hl_set_tile takes.
+constexpr int stage_few(int ns, int tz) {
+  int ne = 1;
+  while (!stage_fits(64, 4, tz, ns, ne)) ++ne;
+  return ne;
+}
+constexpr int stage_any(int ns, int tz) {
+  int ne = 1;
+  for (int tx = 32; tx <= 256; tx += 32)
+    for (int ty = 1; tx * ty <= 256; ++ty)
+      while (tx * ty >= 64 && !stage_fits(tx, ty, tz, ns, ne)) ++ne;
+  return ne;
+}
+// One half-step's workgroup shape: NS classes, TZ layers, NE staged words per
+// work-item and datum; CAP LDS words per buffer (NE words of the most
+// work-items a workgroup has).
+// ANY: tiles that need fewer than NE words skip the rest.
+template <int NS_, int TZ_, int NE_, bool ANY_>
+struct StageShape {
+  static constexpr bool ANY = ANY_;
+  static constexpr int NS = NS_, TZ = TZ_, NE = NE_, CAP = NE_ * NS_ * 256 * TZ_;
+};
+// The default tile with its layers, with one layer, and any tile.
+enum StageForm { kLayered, kOneLayer, kAnyTile };
+template <int NS, int TZ, int FORM>
+using ShapeOf = StageShape<NS, FORM == kLayered ? TZ : 1,
+                           FORM == kAnyTile ? stage_any(NS, 1) : stage_few(NS, FORM == kLayered ? TZ : 1),
+                           FORM == kAnyTile>;
+template <int M, class S, int FORM>
+using PShape = ShapeOf<kPSplit<M, S>, kPLayers<M, S>, FORM>;
+template <int M, class S, int FORM>
+using UShape = ShapeOf<kUSplit<M, S>, 1, FORM>;
+
+// One workgroup's tile: this work-item's node and the source nodes of the
+// words it stages.
+template <class SH>
+struct Stage3 {
+  static constexpr int NE = SH::NE;
+  int32_t j[3];        // this work-item's output node
+  bool active;         // inside the grid (all work-items stage and meet the barriers)
+  int cls;             // class of this wavefront, 0 .. NS - 1
+  int item, items;     // this work-item's first staged word, and the stride to its next
+  int total;           // staged words
+  int base, sx, sxy;   // LDS index of corner 0 and the strides in y and z
+  uint32_t src[NE];    // source node of each staged word
+
+  // false: this workgroup has no tile (uniform)
+  __device__ __forceinline__ bool init(const Grid& g, int blk) {
+    const int t = (blk % kXcds) * g.per_xcd + blk / kXcds;
+    if (t >= g.tiles) return false;
+    int32_t o[3];
+    tile_coords<3>(g, t, o);
+    const int per = class_items(g.tx, g.ty, SH::TZ);
+    item = threadIdx.x;
+    items = SH::NS * per;
+    cls = __builtin_amdgcn_readfirstlane(item / per);
+    const int l = item - cls * per;
+    const int ix = l % g.tx, iyz = l / g.tx;
+    const int iy = SH::TZ == 1 ? iyz : iyz % g.ty, iz = SH::TZ == 1 ? 0 : iyz / g.ty;
+    o[0] *= g.tx;
+    o[1] *= g.ty;
+    o[2] *= SH::TZ;
+    j[0] = o[0] + ix;
+    j[1] = o[1] + iy;
+    j[2] = o[2] + iz;
+    active = iy < g.ty && iz < SH::TZ && j[0] < g.K[0] && j[1] < g.K[1] && j[2] < g.K[2];
+    sx = g.tx + 1;
+    sxy = sx * (g.ty + 1);
+    total = (SH::TZ + 1) * sxy;
+    base = ix + sx * min(iy, g.ty - 1) + sxy * min(iz, SH::TZ - 1);
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int e = min(item + k * items, total - 1);
+      const int c[3] = {e % sx, (e / sx) % (g.ty + 1), e / sxy};
+      int32_t n[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        // the corners of the grid's nodes wrap at most once; words of nodes
+        // outside the grid are clamped into the array and never used
+        int32_t i = o[q] + g.soff + c[q];
+        if (i < 0) i += g.sext[q];
+        if (i >= g.sext[q]) i -= g.sext[q];
+        n[q] = min(i, g.sext[q] - 1);
+      }
+      src[k] = node_index<3>(n[0], n[1], n[2], g.sext);
+    }
+    return true;
+  }
+  // Output node; outside the grid the first index past the plane, whose
+  // loads the buffer descriptor answers with zero and whose stores it drops.
+  __device__ __forceinline__ uint32_t out(const Grid& g) const {
+    return active ? out_index<3>(g, j) : (uint32_t)g.onodes;
+  }
+};
+
+// Issue the loads of plane pl's staged words.
+template <class S, class SH>
+__device__ __forceinline__ void stage_load(const typename S::View& f, int pl, const Stage3<SH>& st,
+                                           typename S::Raw* r) {
+  int zero;  // opaque: the plane base is formed here, not hoisted to the kernel start
+  asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+  const typename S::Planes pr = S::planes(f, pl + zero);
+#pragma unroll
+  for (int k = 0; k < SH::NE; ++k)
+    if (!SH::ANY || k * st.items < st.total) r[k] = S::raw_load(pr, st.src[k]);
 }
 
-// Velocity half-step, 3D: the x interpolation merged into the table
-// as well (as for the pressure half-step).  Per datum a of the primal corners
-// the 8 corner values are combined into the sigma/delta products X[k] (x, y
-// and z, k = k_x + 2 k_y + 4 k_z); member o of G takes the product whose
-// parity in each dimension is that of o_k + a_k, times Fu[a][o].  Per node:
-// 8 loads, 24 add/sub and |G| FMA per datum (27 x 77 VALU at m = 2) against
-// the explicit x pass plus the (y, z) merged table (about 2700 VALU).
-template <int M, class S, typename TP>
-__device__ __forceinline__ void u3_full_Q(const typename S::View& p, const uint32_t* cn, TP tab,
-                                          typename S::C* Q) {
-  using T = typename S::C;
-  using TL = TableLayout<3, M>;
-  constexpr int MP = M + 1, NC = Dims<3, M>::NC, NG = GSet<3, M>::NG;
+template <class S, class SH>
+__device__ __forceinline__ void stage_store(typename S::C* buf, const Stage3<SH>& st, const typename S::Raw* r) {
 #pragma unroll
-  for (int o = 0; o < NG; ++o) Q[o] = T(0);
-  T vn[8];  // the next datum's corners, loaded one datum ahead
-  if constexpr (kPrefetch3<S>) {
-    const typename S::Planes pr = S::planes(p, 0);
+  for (int k = 0; k < SH::NE; ++k)
+    if (!SH::ANY || k * st.items < st.total) buf[st.item + k * st.items] = S::value(r[k]);
+}
+
+// Corner combinations of the staged datum in X[k_x + 2 k_y + 4 k_z] (0 = sigma,
+// 1 = delta); only those with k_x = KX when KX >= 0.
+template <int KX, typename T>
+__device__ __forceinline__ void butterfly3(const T* c, int sx, int sxy, T* X) {
+  T x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) vn[e] = S::bload(pr, cn[e]);
+  for (int q = 0; q < 4; ++q) {
+    const T* row = c + (q & 1) * sx + (q >> 1) * sxy;
+    const T lo = row[0], hi = row[1];
+    if (KX != 1) x[2 * q] = hi + lo;
+    if (KX != 0) x[2 * q + 1] = hi - lo;
   }
 #pragma unroll
-  for (int a = 0; a < NC; ++a) {
-    // keep the scalar table loads of one datum together (SGPR pressure)
-    __builtin_amdgcn_sched_barrier(0);
-    T v[8];
-    if constexpr (kPrefetch3<S>) {
+  for (int kx = 0; kx < 2; ++kx) {
+    if (KX >= 0 && kx != KX) continue;
+    T y[4];  // [k_y + 2 e_z]
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = vn[e];
-      if (a + 1 < NC) {
-        int zero;  // opaque: the plane base is formed here, not hoisted to the kernel start
-        asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
-        const typename S::Planes pn = S::planes(p, a + 1 + zero);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vn[e] = S::bload(pn, cn[e]);
-      }
-    } else {
-      const typename S::Planes pr = S::planes(p, a);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = S::bload(pr, cn[e]);
-    }
-    T X[8];  // [k_x + 2 k_y + 4 k_z]
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {  // x: corners (2q, 2q+1)
-      X[2 * q] = v[2 * q + 1] + v[2 * q];
-      X[2 * q + 1] = v[2 * q + 1] - v[2 * q];
+    for (int ez = 0; ez < 2; ++ez) {
+      const T lo = x[kx + 4 * ez], hi = x[kx + 2 + 4 * ez];
+      y[2 * ez] = hi + lo;
+      y[1 + 2 * ez] = hi - lo;
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = X[q];
-#pragma unroll
-    for (int kz = 0; kz < 2; ++kz)  // y: pairs (kx + 4 kz, kx + 2 + 4 kz)
-#pragma unroll
-      for (int kx = 0; kx < 2; ++kx) {
-        const T lo = v[kx + 4 * kz], hi = v[kx + 2 + 4 * kz];
-        X[kx + 4 * kz] = hi + lo;
-        X[kx + 2 + 4 * kz] = hi - lo;
-      }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {  // z: pairs (q, q + 4)
-      const T lo = X[q], hi = X[q + 4];
-      v[q] = hi + lo;
-      v[q + 4] = hi - lo;
+    for (int ky = 0; ky < 2; ++ky) {
+      X[kx + 2 * ky] = y[ky + 2] + y[ky];
+      X[kx + 2 * ky + 4] = y[ky + 2] - y[ky];
     }
-    const int ax = a % MP, ay = (a / MP) % MP, az = a / (MP * MP);
+  }
+}
+
+// Keeps an accumulator's arithmetic where it is written (no instruction):
+// otherwise the compiler moves every datum's products past the last barrier,
+// to where the sums are used, and holds all table entries in registers.
+template <typename T>
+__device__ __forceinline__ void pin(T& x) {
+  asm volatile("" : "+v"(x));
+}
+
+// The data loop of one wavefront class: per datum q = 0 .. NQ - 1 (plane q of
+// f) its staged corners' combinations X are handed to apply.  F::kx(q) is the
+// combination in x that the class's outputs take (NS = 2).
+template <class S, class SH, int Q, class F>
+__device__ __forceinline__ void stage_datum(const Stage3<SH>& st, const typename S::C* buf, F& apply) {
+  // keep the scalar table loads of one datum together (SGPR pressure)
+  __builtin_amdgcn_sched_barrier(0);
+  typename S::C X[8];
+  butterfly3<SH::NS == 2 ? F::kx(Q) : -1>(buf + (Q % kStageGroup) * SH::CAP + st.base, st.sx, st.sxy, X);
+  apply.template operator()<Q>(X);
+}
+
+template <int NQ, class S, class SH, int GR, class F, int... I>
+__device__ __forceinline__ void stage_group(const typename S::View& f, const Stage3<SH>& st, typename S::C* lds,
+                                            typename S::Raw (*r)[SH::NE], F& apply, std::integer_sequence<int, I...>) {
+  constexpr int G = kStageGroup;
+  __builtin_amdgcn_sched_barrier(0);
+  typename S::C* buf = lds + (GR & 1) * G * SH::CAP;
+#pragma unroll
+  for (int i = 0; i < (int)sizeof...(I); ++i) stage_store<S, SH>(buf + i * SH::CAP, st, r[i]);
+#pragma unroll
+  for (int i = 0; i < G; ++i)
+    if ((GR + 1) * G + i < NQ) stage_load<S, SH>(f, (GR + 1) * G + i, st, r[i]);
+  __syncthreads();
+  (stage_datum<S, SH, GR * G + I>(st, buf, apply), ...);
+}
+
+template <int NQ, class S, class SH, class F, int... GR>
+__device__ __forceinline__ void stage_loop(const typename S::View& f, const Stage3<SH>& st, typename S::C* lds, F& apply,
+                                           std::integer_sequence<int, GR...>) {
+  constexpr int G = kStageGroup;
+  typename S::Raw r[G][SH::NE];
+#pragma unroll
+  for (int i = 0; i < G && i < NQ; ++i) stage_load<S, SH>(f, i, st, r[i]);
+  (stage_group<NQ, S, SH, GR>(f, st, lds, r, apply,
+                              std::make_integer_sequence<int, ((GR + 1) * G <= NQ ? G : NQ - GR * G)>{}),
+   ...);
+}
+template <int NQ>
+using StageGroups = std::make_integer_sequence<int, (NQ + kStageGroup - 1) / kStageGroup>;
+
+template <int N>
+struct IndexList {
+  int n;
+  short v[N];
+};
+
+// Pressure half-step, 3D.  Table F[i][a][rank(o)]: component i, datum a, output
+// o.  Per node and datum at m = 2: 24 add/sub and 27 multiply-adds.
+template <int M, class S, int CLS, int NS, typename TP>
+struct PApply3 {
+  using T = typename S::C;
+  static constexpr int MP = M + 1, NC = Dims<3, M>::NC;
+  TP tab;
+  T acc[NC];
+  static constexpr int kx(int q) { return (CLS + q % NC % MP + (q / NC == 0)) & 1; }
+  static constexpr bool mine(int o) { return NS == 1 || ((o % MP) & 1) == CLS; }
+  // the planes this class writes
+  static constexpr IndexList<NC> outputs() {
+    IndexList<NC> l{};
+    for (int o = 0; o < NC; ++o)
+      if (mine(o)) l.v[l.n++] = (short)o;
+    return l;
+  }
+  static constexpr IndexList<NC> kOut = outputs();
+  template <int Q>
+  __device__ __forceinline__ void operator()(const T* X) {
+    constexpr int i = Q / NC, a = Q % NC, ax = a % MP, ay = (a / MP) % MP, az = a / (MP * MP);
+#pragma unroll
+    for (int o = 0; o < NC; ++o) {
+      if (!mine(o)) continue;
+      const int ox = o % MP, oy = (o / MP) % MP, oz = o / (MP * MP);
+      const int k = ((ox + ax + (i == 0)) & 1) + 2 * ((oy + ay + (i == 1)) & 1) + 4 * ((oz + az + (i == 2)) & 1);
+      acc[o] = fma(tab[TableLayout<3, M>::F_OFF + Q * NC + kPRank<M>.r[o]], X[k], acc[o]);
+    }
+#pragma unroll
+    for (int o = 0; o < NC; ++o)
+      if (mine(o)) pin(acc[o]);
+  }
+};
+
+template <int M, class S, class SH, int CLS, typename TP>
+__device__ __forceinline__ void p_half_3d_class(const typename S::View& p, const typename S::View& u, TP tab,
+                                                const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
+  using T = typename S::C;
+  constexpr int NC = Dims<3, M>::NC;
+  using A = PApply3<M, S, CLS, SH::NS, TP>;
+  A f;
+  f.tab = tab;
+#pragma unroll
+  for (int s = 0; s < NC; ++s) f.acc[s] = T(0);
+  stage_loop<3 * NC, S, SH>(u, st, lds, f, StageGroups<3 * NC>{});
+  const uint32_t n0 = st.out(g);
+  update_outputs<3, S, A::kOut.n>(g, p, n0, [](int k) { return A::kOut.v[k]; },
+                                  [&](int k, T x) { return x - f.acc[A::kOut.v[k]]; });
+}
+
+template <int M, class S, class SH, typename TP>
+__device__ __forceinline__ void p_half_3d_body(typename S::View p, typename S::View u, TP tab, Grid g, int blk) {
+  __shared__ typename S::C lds[2 * kStageGroup * SH::CAP];
+  Stage3<SH> st;
+  if (!st.init(g, blk)) return;  // dual q = j - 1 + e
+  if (SH::NS == 1 || st.cls == 0)
+    p_half_3d_class<M, S, SH, 0>(p, u, tab, g, st, lds);
+  else if constexpr (SH::NS > 1)
+    p_half_3d_class<M, S, SH, 1>(p, u, tab, g, st, lds);
+}
+
+template <int M, class S, int FORM>
+__global__ void __launch_bounds__((256 * kPSplit<M, S> * PShape<M, S, FORM>::TZ), HL_WAVES_PER_EU)
+    p_half_3d(typename S::View p, typename S::View u, const typename S::C* __restrict__ tab, Grid g) {
+  p_half_3d_body<M, S, PShape<M, S, FORM>, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
+}
+
+// Velocity half-step, 3D.  Table Fu[a][rank(o)]: datum a, member o of G.  Per
+// node and datum at m = 2: 24 add/sub and 53 multiply-adds, split
+// over two wavefront classes by the parity of the member's x index (29 and 24
+// members): 12 add/sub each.
+template <int M, class S, int CLS, int NS, typename TP>
+struct UApply3 {
+  using T = typename S::C;
+  static constexpr int MP = M + 1, NG = GSet<3, M>::NG;
+  TP tab;
+  T Q[NG];
+  static constexpr int kx(int a) { return (CLS + a % MP) & 1; }
+  static constexpr bool mine(int o) { return NS == 1 || (kGSet<3, M>.dig[o][0] & 1) == CLS; }
+  // the planes i NC + s this class writes: those whose member is its own
+  static constexpr int NC = Dims<3, M>::NC;
+  static constexpr IndexList<3 * NC> outputs() {
+    IndexList<3 * NC> l{};
+    for (int t = 0; t < 3 * NC; ++t)
+      if (mine(kGIndex<3, M>.g[t / NC][t % NC])) l.v[l.n++] = (short)t;
+    return l;
+  }
+  static constexpr IndexList<3 * NC> kOut = outputs();
+  template <int A>
+  __device__ __forceinline__ void operator()(const T* X) {
+    constexpr int ax = A % MP, ay = (A / MP) % MP, az = A / (MP * MP);
 #pragma unroll
     for (int o = 0; o < NG; ++o) {
-      if (o == NG / 2) __builtin_amdgcn_sched_barrier(0);  // two halves of the datum's table loads
+      if (NS == 1 && o == NG / 2) __builtin_amdgcn_sched_barrier(0);  // two halves of the datum's table loads
+      if (!mine(o)) continue;
       const int k = ((kGSet<3, M>.dig[o][0] + ax) & 1) + 2 * ((kGSet<3, M>.dig[o][1] + ay) & 1) +
                     4 * ((kGSet<3, M>.dig[o][2] + az) & 1);
-      Q[o] = fma(tab[TL::FU_OFF + a * NG + o], v[k], Q[o]);
+      Q[o] = fma(tab[TableLayout<3, M>::FU_OFF + A * NG + kURank<M>.r[o]], X[k], Q[o]);
     }
+#pragma unroll
+    for (int o = 0; o < NG; ++o)
+      if (mine(o)) pin(Q[o]);
   }
-}
+};
 
-template <int M, class S, typename TP>
-__device__ __forceinline__ void u_half_3d_body(typename S::View u, typename S::View p,
-                                               TP tab, Grid g,
-                                               typename S::C wscale, typename S::C ih0,
-                                               typename S::C ih1, typename S::C ih2, int blk) {
+template <int M, class S, class SH, int CLS, typename TP>
+__device__ __forceinline__ void u_half_3d_class(const typename S::View& u, const typename S::View& p, TP tab,
+                                                const Grid& g, typename S::C wscale, const typename S::C* ih,
+                                                const Stage3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
-  using TL = TableLayout<3, M>;
-  constexpr int MP = M + 1, N2 = 2 * M + 2;
-  constexpr int NG = GSet<3, M>::NG;
-  constexpr int NNZ = Merge3Spec<M, true, 0, 0>::NNZ;
-  int32_t j[3];
-  if (!node_of_block<3>(g, blk, j)) return;
-  uint32_t cn[8];
-  corner_nodes<3>(g, j, cn);  // dual q = j - 1 + e (p) or primal j = q + e (u)
-  T Q[NG];
-  if constexpr (TL::FULL_U && HL_U3_FULL) {
-    u3_full_Q<M, S>(p, cn, tab, Q);
-  } else {
+  constexpr int NC = Dims<3, M>::NC, MP = M + 1, NG = GSet<3, M>::NG;
+  using A = UApply3<M, S, CLS, SH::NS, TP>;
+  A f;
+  f.tab = tab;
 #pragma unroll
-    for (int o = 0; o < NG; ++o) Q[o] = T(0);
-#pragma unroll
-    for (int az = 0; az < MP; ++az)
-#pragma unroll
-      for (int ay = 0; ay < MP; ++ay) {
-        const int blk = ay + MP * az;
-        T X[2][2][N2];
-        xlines<M, 0, S>(p, MP * blk, cn, X);
-        merge3<M, true, 0, 0>(tab + TL::U_OFF + blk * NNZ, ay, az, X, Q);
-      }
-  }
-  const T ih[3] = {ih0, ih1, ih2};
-  finish_velocity<3, M, S>(u, out_index<3>(g, j), Q, wscale, ih);
+  for (int o = 0; o < NG; ++o) f.Q[o] = T(0);
+  stage_loop<NC, S, SH>(p, st, lds, f, StageGroups<NC>{});
+  const uint32_t n0 = st.out(g);
+  // u_i[s] -= wscale * (s_i + 1) / h_i * Q[s + e_i]
+  const T w[3] = {wscale * ih[0], wscale * ih[1], wscale * ih[2]};
+  update_outputs<3, S, A::kOut.n>(g, u, n0, [](int k) { return A::kOut.v[k]; }, [&](int k, T x) {
+    const int i = A::kOut.v[k] / NC, s = A::kOut.v[k] % NC;
+    const T a = -(T)(digit(s, MP, i) + 1) * w[i];
+    return fma(a, f.Q[kGIndex<3, M>.g[i][s]], x);
+  });
 }
 
-template <int M, class S>
-__global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_3d(typename S::View u, typename S::View p,
-                                                                   const typename S::C* __restrict__ tab, Grid g,
-                                                                   typename S::C wscale, typename S::C ih0,
-                                                                   typename S::C ih1, typename S::C ih2) {
-  u_half_3d_body<M, S, const typename S::C* __restrict__>(u, p, tab, g, wscale, ih0, ih1, ih2, blockIdx.x);
+template <int M, class S, class SH, typename TP>
+__device__ __forceinline__ void u_half_3d_body(typename S::View u, typename S::View p, TP tab, Grid g,
+                                               typename S::C wscale, typename S::C ih0, typename S::C ih1,
+                                               typename S::C ih2, int blk) {
+  using T = typename S::C;
+  __shared__ T lds[2 * kStageGroup * SH::CAP];
+  Stage3<SH> st;
+  if (!st.init(g, blk)) return;  // primal j = q + e
+  const T ih[3] = {ih0, ih1, ih2};
+  if (SH::NS == 1 || st.cls == 0)
+    u_half_3d_class<M, S, SH, 0>(u, p, tab, g, wscale, ih, st, lds);
+  else if constexpr (SH::NS > 1)
+    u_half_3d_class<M, S, SH, 1>(u, p, tab, g, wscale, ih, st, lds);
+}
+
+template <int M, class S, int FORM>
+__global__ void __launch_bounds__((256 * kUSplit<M, S>), HL_WAVES_PER_EU)
+    u_half_3d(typename S::View u, typename S::View p, const typename S::C* __restrict__ tab, Grid g,
+              typename S::C wscale, typename S::C ih0, typename S::C ih1, typename S::C ih2) {
+  u_half_3d_body<M, S, UShape<M, S, FORM>, const typename S::C* __restrict__>(u, p, tab, g, wscale, ih0, ih1, ih2,
+                                                                             blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------

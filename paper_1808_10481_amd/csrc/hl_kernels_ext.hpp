@@ -559,7 +559,7 @@ __device__ __forceinline__ void p_half_var_body(typename S::View p, typename S::
 #pragma unroll
     for (int s = 0; s < NC; ++s) acc[s] += t[poly_index<D, M>(s, 0, 0, 0)];
   }
-  finish_pressure<D, M, S>(p, n0, acc);
+  finish_pressure<D, M, S>(g, p, n0, acc);
 }
 
 template <int D, int M, class S>
@@ -1567,7 +1567,8 @@ __device__ __forceinline__ ShotHalf<S> shot_desc(const ShotHalf<S>* __restrict__
 }
 
 template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__(256, HL_WAVES_PER_EU) p_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kPSplit<M, S> : 256), HL_WAVES_PER_EU)
+    p_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;
   const ConstPtr<typename S::C> tab = const_ptr(sh.tab);
@@ -1575,16 +1576,15 @@ __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) p_half_batch(const ShotH
   const typename G::View out = S::global(sh.out), in = S::global(sh.in), kap = S::global(sh.kap);
   if constexpr (VAR)
     p_half_var_body<D, M, G>(out, in, kap, sh.g, sh.va, blk);
-  else if constexpr (D == 3 && TableLayout<3, M>::FULL_P)
-    p_half_3d_full_body<M, G>(out, in, tab, sh.g, blk);
   else if constexpr (D == 3)
-    p_half_3d_body<M, G>(out, in, tab, sh.g, blk);
+    p_half_3d_body<M, G, PShape<M, S, kAnyTile>>(out, in, tab, sh.g, blk);
   else
     p_half_body<D, M, G>(out, in, tab, sh.g, blk);
 }
 
 template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kUSplit<M, S> : 256), HL_WAVES_PER_EU)
+    u_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;
   const ConstPtr<typename S::C> tab = const_ptr(sh.tab);
@@ -1593,7 +1593,7 @@ __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_batch(const ShotH
   if constexpr (VAR)
     u_half_var_body<D, M, G>(out, in, kap, sh.g, sh.va, sh.wscale, blk);
   else if constexpr (D == 3)
-    u_half_3d_body<M, G>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
+    u_half_3d_body<M, G, UShape<M, S, kAnyTile>>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
   else
     u_half_body<D, M, G>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
 }

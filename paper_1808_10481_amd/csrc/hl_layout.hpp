@@ -6,8 +6,8 @@
 // Per cell the method interpolates 2^d corner blocks of (m+1)^d scaled data
 // into a polynomial of degree 2m+1 per variable (Sec. 2, eq. (interp); Sec. 5)
 // and applies the Cauchy-Kowalevsky leapfrog weights (Sec. 2, eq. (final1);
-// Sec. 3.1.2, eqs. (pdup), (vdup)).  The kernels interpolate all but the last
-// dimension explicitly ("slice passes", compile-time constants) and fuse the
+// Sec. 3.1.2, eqs. (pdup), (vdup)).  In 1D and 2D the kernels interpolate all
+// but the last dimension explicitly ("slice passes", compile-time constants) and fuse the
 // last dimension's interpolation with the weight operator into one runtime
 // "merged" table, so the (2m+2)^d interpolant never exists as a whole.
 #pragma once
@@ -284,64 +284,34 @@ template <int D, int M>
 inline constexpr GIndex<D, M> kGIndex{};
 
 // ---------------------------------------------------------------------------
-// 3D: interpolation is explicit only along x; y and z are merged into the
-// table.  For y/z data a' = (a_y, a_z) and output o:
-//   M[a'][o][b_x] = scale * sum_{b_y, b_z} W(o, b) Gy[b_y][a_y] Gz[b_z][a_z]
-// acting on the combination of the four (y, z) corners' x-interpolants
-//   X[k_y][k_z] = sum_{e_y, e_z} (+-1) Y_{e_y e_z},  k = sigma (R + L) or delta (R - L),
-// with k_y = sigma iff o_y + a_y + flip_y is even (likewise z).  Structural
-// nonzeros: b_x - o_x even and >= 0.  Walk order: a' block, then o, then b_x.
+// 3D: the outputs of a datum's table row are stored even x index first, so
+// that a kernel that takes one parity reads consecutive entries: rank of
+// pressure output o, and of member o of G.
 // ---------------------------------------------------------------------------
 template <int M>
-constexpr int count_bx(int ox) {
-  int n = 0;
-  for (int bx = ox; bx < 2 * M + 2; bx += 2) ++n;
-  return n;
-}
-
-template <int M, bool VEL>
-constexpr int merge3_block_nnz() {
-  int n = 0;
-  for (int o = 0; o < n_out<3, M>(VEL); ++o) {
-    int od[3] = {0, 0, 0};
-    out_digits<3, M>(VEL, o, od);
-    n += count_bx<M>(od[0]);
-  }
-  return n;
-}
-
-template <int M, bool VEL>
-constexpr int merge3_size() {
-  return (M + 1) * (M + 1) * merge3_block_nnz<M, VEL>();
-}
-
-template <int M, bool VEL, int FY, int FZ>
-struct Merge3Spec {
-  static constexpr int NNZ = merge3_block_nnz<M, VEL>();  // per a' block
-  short o[NNZ];
-  short bx[NNZ];
-  unsigned char ky[NNZ][M + 1];  // 1 = delta in y, for a_y
-  unsigned char kz[NNZ][M + 1];  // 1 = delta in z, for a_z
-  constexpr Merge3Spec() : o(), bx(), ky(), kz() {
-    int t = 0;
-    for (int oo = 0; oo < n_out<3, M>(VEL); ++oo) {
-      int od[3] = {0, 0, 0};
-      out_digits<3, M>(VEL, oo, od);
-      for (int b = od[0]; b < 2 * M + 2; b += 2) {
-        o[t] = (short)oo;
-        bx[t] = (short)b;
-        for (int a = 0; a <= M; ++a) {
-          ky[t][a] = (unsigned char)((od[1] + a + FY) & 1);
-          kz[t][a] = (unsigned char)((od[2] + a + FZ) & 1);
-        }
-        ++t;
-      }
-    }
+struct PRank {
+  short r[Dims<3, M>::NC];
+  constexpr PRank() : r() {
+    int n = 0;
+    for (int par = 0; par < 2; ++par)
+      for (int o = 0; o < Dims<3, M>::NC; ++o)
+        if (((o % (M + 1)) & 1) == par) r[o] = (short)n++;
   }
 };
-
-template <int M, bool VEL, int FY, int FZ>
-inline constexpr Merge3Spec<M, VEL, FY, FZ> kMerge3{};
+template <int M>
+struct URank {
+  short r[GSet<3, M>::NG];
+  constexpr URank() : r() {
+    int n = 0;
+    for (int par = 0; par < 2; ++par)
+      for (int o = 0; o < GSet<3, M>::NG; ++o)
+        if ((kGSet<3, M>.dig[o][0] & 1) == par) r[o] = (short)n++;
+  }
+};
+template <int M>
+inline constexpr PRank<M> kPRank{};
+template <int M>
+inline constexpr URank<M> kURank{};
 
 template <int D, int M>
 struct TableLayout;
@@ -358,36 +328,16 @@ struct TableLayout {
   static constexpr int p_off(int i) { return (D > 1 && i == 0) ? P_A_OFF : P_B_OFF; }
 };
 
-// 3D: one pressure table per component (derivative dimension), then Q (the
-// (y, z) merged tables of the explicit x-pass path); then the fully merged
-// pressure table (x merged too): F[i][a][o], component i, datum a, output o,
-// (m+1)^3 x (m+1)^3 per component, and the fully merged velocity table
-// Fu[a][o] over the members o of G.  The kernels use the fully merged tables
-// (one FMA per entry after the corner butterfly) for every m;
-// HL_FULLP_MAXM / HL_FULLU_MAXM below 3 select the explicit x pass plus the
-// (y, z) tables for the larger m instead (at m = 3 that path needs 512 VGPRs
-// and spills 1.8-2.6 KB per lane).
-#ifndef HL_FULLP_MAXM
-#define HL_FULLP_MAXM 3
-#endif
-#ifndef HL_FULLU_MAXM
-#define HL_FULLU_MAXM 3
-#endif
-
+// 3D: every dimension's interpolation is in the table.  F[i][a][rank(o)]:
+// component i, datum a, pressure output o, (m+1)^3 x (m+1)^3 per component;
+// then Fu[a][rank(o)] over the members o of G.  One multiply-add per entry
+// after the corner combinations.
 template <int M>
 struct TableLayout<3, M> {
-  static constexpr int PG = merge3_size<M, false>();
-  static constexpr int p_off(int i) { return i * PG; }
-  static constexpr int P_A_OFF = 0;
-  static constexpr int P_B_OFF = 2 * PG;
-  static constexpr int U_OFF = 3 * PG;
-  static constexpr bool FULL_P = M <= HL_FULLP_MAXM;
   static constexpr int NC = (M + 1) * (M + 1) * (M + 1);
-  static constexpr int F_OFF = U_OFF + merge3_size<M, true>();
-  // the fully merged velocity table Fu[a][o], datum a, member o of G
-  static constexpr bool FULL_U = M <= HL_FULLU_MAXM;
-  static constexpr int FU_OFF = F_OFF + (FULL_P ? 3 * NC * NC : 0);
-  static constexpr int TOTAL = FU_OFF + (FULL_U ? NC * GSet<3, M>::NG : 0);
+  static constexpr int F_OFF = 0;
+  static constexpr int FU_OFF = 3 * NC * NC;
+  static constexpr int TOTAL = FU_OFF + NC * GSet<3, M>::NG;
 };
 
 }  // namespace hl

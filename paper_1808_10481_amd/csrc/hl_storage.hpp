@@ -74,11 +74,12 @@ struct PlainStore {
     WP q = reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W));
     *q = f(*q);
   }
-  // the same with non-temporal accesses
-  template <class F>
-  __device__ static __forceinline__ void update_nt(const View& v, int pl, uint32_t node, F f) {
-    WP q = reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W));
-    __builtin_nontemporal_store(f(__builtin_nontemporal_load(q)), q);
+  // the same accesses, non-temporal
+  __device__ static __forceinline__ C load_nt(const View& v, int pl, uint32_t node) {
+    return __builtin_nontemporal_load(reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W)));
+  }
+  __device__ static __forceinline__ void store_nt(const View& v, int pl, uint32_t node, C x) {
+    __builtin_nontemporal_store(x, reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W)));
   }
   __device__ static __forceinline__ void store(const View& v, int pl, uint32_t node, C x) {
     *reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W)) = x;
@@ -91,6 +92,10 @@ struct PlainStore {
   __device__ static __forceinline__ Planes planes(const View& v, int pl) {
     return Planes{raw_rsrc((const void*)(uintptr_t)plane(v, pl), (uint32_t)(v.nodes * (int64_t)sizeof(W)))};
   }
+  // A stored entry as loaded, before it is widened to the arithmetic type.
+  using Raw = W;
+  __device__ static __forceinline__ Raw raw_load(const Planes& p, uint32_t node) { return bload(p, node); }
+  __device__ static __forceinline__ C value(Raw x) { return x; }
   // AUX: the cache-policy operand of the buffer instruction (0: default).
   template <int AUX = 0>
   __device__ static __forceinline__ C bload(const Planes& p, uint32_t node) {
@@ -150,26 +155,24 @@ struct SplitStoreT {
     const uint16_t lo = *reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u);
     return widen(hi, lo);
   }
+  __device__ static __forceinline__ void store(const View& v, int pl, uint32_t node, C x) {
+    const float hi = (float)x;
+    *reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u) = hi;
+    *reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u) = to_bf16((float)(x - (double)hi));
+  }
   template <class F>
   __device__ static __forceinline__ void update(const View& v, int pl, uint32_t node, F f) {
-    FP qh = reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u);
-    HP ql = reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u);
-    const double val = f(widen(*qh, *ql));
-    const float hi = (float)val;
-    *qh = hi;
-    *ql = to_bf16((float)(val - (double)hi));
+    store(v, pl, node, f(load(v, pl, node)));
   }
-  __device__ static __forceinline__ void store(const View& v, int pl, uint32_t node, C x) {
-    update(v, pl, node, [&](C) { return x; });
+  __device__ static __forceinline__ C load_nt(const View& v, int pl, uint32_t node) {
+    return widen(__builtin_nontemporal_load(reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u)),
+                 __builtin_nontemporal_load(reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u)));
   }
-  template <class F>
-  __device__ static __forceinline__ void update_nt(const View& v, int pl, uint32_t node, F f) {
-    FP qh = reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u);
-    HP ql = reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u);
-    const double val = f(widen(__builtin_nontemporal_load(qh), __builtin_nontemporal_load(ql)));
-    const float hi = (float)val;
-    __builtin_nontemporal_store(hi, qh);
-    __builtin_nontemporal_store(to_bf16((float)(val - (double)hi)), ql);
+  __device__ static __forceinline__ void store_nt(const View& v, int pl, uint32_t node, C x) {
+    const float hi = (float)x;
+    __builtin_nontemporal_store(hi, reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u));
+    __builtin_nontemporal_store(to_bf16((float)(x - (double)hi)),
+                                reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u));
   }
 
   struct Planes {
@@ -180,6 +183,15 @@ struct SplitStoreT {
     return Planes{raw_rsrc((const void*)(uintptr_t)hi_plane(v, pl), 4u * n),
                   raw_rsrc((const void*)(uintptr_t)lo_plane(v, pl), 2u * n)};
   }
+  struct Raw {
+    float hi;
+    uint16_t lo;
+  };
+  __device__ static __forceinline__ Raw raw_load(const Planes& p, uint32_t node) {
+    return Raw{__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(p.hi, node * 4u, 0u, 0)),
+               (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(p.lo, node * 2u, 0u, 0)};
+  }
+  __device__ static __forceinline__ C value(Raw x) { return widen(x.hi, x.lo); }
   template <int AUX = 0>
   __device__ static __forceinline__ C bload(const Planes& p, uint32_t node) {
     const float hi = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(p.hi, node * 4u, 0u, AUX));
