@@ -272,6 +272,48 @@ struct VarArgs {
   T ih[3];     // 1 / h_k
 };
 
+// Coefficients a half-step's result depends on.  t_k = T[kappa Lap t_{k-1}]
+// feeds the result directly on the output set (pressure: {0..m}^D; velocity,
+// VEL: s + e_i with s in {0..m}^D) and through the remaining J = kmax - k
+// Laplacians, each of which reads two orders up in one variable; a product's
+// coefficient b reads its operands at all orders <= b.  So t_k and the operand
+// Lap t_{k-1} are formed only on the coefficients b of need(b) <= J, need(b)
+// the least number of Laplacians from b down into the output set; every kept
+// coefficient is the same sum in the same order.  Multiply-adds of the products
+// of one half-step against full products: 2D m = 3 6120 of 9072 (pressure),
+// 3D m = 2 37044 of 64827.
+template <int D, int M, bool VEL>
+struct Need {
+  static constexpr int N2 = 2 * M + 2, NP = ipow(N2, D);
+  static constexpr int over(int b, int top) { return b > top ? (b - top + 1) / 2 : 0; }
+  // per-variable orders (b_x, b_y, b_z), 0 beyond D
+  static constexpr int of(int bx, int by, int bz) {
+    const int dg[3] = {bx, by, bz};
+    int best = 99;
+    for (int i = 0; i < (VEL ? D : 1); ++i) {
+      int n = 0;
+      for (int k = 0; k < D; ++k) n += over(dg[k], VEL && k == i ? M + 1 : M);
+      best = n < best ? n : best;
+    }
+    return best;
+  }
+  static constexpr int at(int b) { return of(b % N2, D > 1 ? (b / N2) % N2 : 0, D > 2 ? b / (N2 * N2) : 0); }
+  static constexpr int top() {
+    int t = 0;
+    for (int b = 0; b < NP; ++b) t = at(b) > t ? at(b) : t;
+    return t;
+  }
+  signed char n[NP];
+  constexpr Need() : n() {
+    for (int b = 0; b < NP; ++b) n[b] = (signed char)at(b);
+  }
+};
+template <int D, int M, bool VEL>
+inline constexpr Need<D, M, VEL> kNeed{};
+// Products from J = kNeedTop on are full.
+template <int D, int M, bool VEL>
+constexpr int kNeedTop = Need<D, M, VEL>::top();
+
 // The truncated products of the adjoint kernels load their kappa terms in
 // groups of kKappaGroup, each group issued while the previous one is applied.
 // The plane base of every load is formed from an opaque scalar zero taken
@@ -283,7 +325,8 @@ constexpr int kKappaGroup = 4;
 
 // out_b += kappa_A f_{b-A} (TR = false: T[kappa f]) or out_b += kappa_A f_{A+b}
 // (TR = true: T^T[kappa] f), for one term A.
-template <int D, int M, bool TR, int A, typename T>
+// Only coefficients of need <= J (J >= kNeedTop: all).
+template <int D, int M, bool VEL, int J, bool TR, int A, typename T>
 __device__ __forceinline__ void kterm_apply(T ka, const T* f, T* out) {
   constexpr int N2 = 2 * M + 2, AX = A % N2, AY = (A / N2) % N2, AZ = A / (N2 * N2);
   constexpr int NY = D > 1 ? N2 : 1, NZ = D > 2 ? N2 : 1;
@@ -294,6 +337,7 @@ __device__ __forceinline__ void kterm_apply(T ka, const T* f, T* out) {
 #pragma unroll
       for (int bx = 0; bx + AX < N2; ++bx) {
         const int lo = bx + N2 * (by + N2 * bz), hi = (bx + AX) + N2 * ((by + AY) + N2 * (bz + AZ));
+        if (kNeed<D, M, VEL>.n[hi] > J) continue;
         if constexpr (TR)
           out[lo] = fma(ka, f[hi], out[lo]);
         else
@@ -301,63 +345,65 @@ __device__ __forceinline__ void kterm_apply(T ka, const T* f, T* out) {
       }
 }
 
-template <int D, int M, bool TR, int BASE, typename T, int... I>
+template <int D, int M, bool VEL, int J, bool TR, int BASE, typename T, int... I>
 __device__ __forceinline__ void kgroup_apply(const T* kc, const T* f, T* out, std::integer_sequence<int, I...>) {
-  (kterm_apply<D, M, TR, BASE + I>(kc[I], f, out), ...);
+  (kterm_apply<D, M, VEL, J, TR, BASE + I>(kc[I], f, out), ...);
 }
 
-// kb[i] = kappa_{BASE + i} for the terms BASE + i < NP.
-template <class S, int BASE, int NP>
+// kb[i] = kappa_{BASE + i} for the terms BASE + i < NP of need <= J.
+template <class S, int D, int M, bool VEL, int J, int BASE, int NP>
 __device__ __forceinline__ void kgroup_load(const typename S::View& kv, uint32_t n0, typename S::C* kb) {
   int zero;
   asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
 #pragma unroll
   for (int i = 0; i < kKappaGroup; ++i)
-    if (BASE + i < NP) kb[i] = S::load(kv, BASE + i + zero, n0);
+    if (BASE + i < NP && kNeed<D, M, VEL>.n[BASE + i < NP ? BASE + i : 0] <= J)
+      kb[i] = S::load(kv, BASE + i + zero, n0);
 }
 
-template <int D, int M, bool TR, class S, int GRP>
+template <int D, int M, bool VEL, int J, bool TR, class S, int GRP>
 __device__ __forceinline__ void kgroup_step(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                             typename S::C* out, typename S::C (*kb)[kKappaGroup]) {
   constexpr int G = kKappaGroup, NP = VK<D, M>::NP, NG = (NP + G - 1) / G;
   constexpr int CNT = NP - GRP * G < G ? NP - GRP * G : G;
-  if constexpr (GRP + 1 < NG) kgroup_load<S, (GRP + 1) * G, NP>(kv, n0, kb[(GRP + 1) & 1]);
-  kgroup_apply<D, M, TR, GRP * G>(kb[GRP & 1], f, out, std::make_integer_sequence<int, CNT>{});
+  if constexpr (GRP + 1 < NG) kgroup_load<S, D, M, VEL, J, (GRP + 1) * G, NP>(kv, n0, kb[(GRP + 1) & 1]);
+  kgroup_apply<D, M, VEL, J, TR, GRP * G>(kb[GRP & 1], f, out, std::make_integer_sequence<int, CNT>{});
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int D, int M, bool TR, class S, int... GRP>
+template <int D, int M, bool VEL, int J, bool TR, class S, int... GRP>
 __device__ __forceinline__ void kgroup_steps(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                              typename S::C* out, std::integer_sequence<int, GRP...>) {
   typename S::C kb[2][kKappaGroup];
-  kgroup_load<S, 0, VK<D, M>::NP>(kv, n0, kb[0]);
-  (kgroup_step<D, M, TR, S, GRP>(kv, n0, f, out, kb), ...);
+  kgroup_load<S, D, M, VEL, J, 0, VK<D, M>::NP>(kv, n0, kb[0]);
+  (kgroup_step<D, M, VEL, J, TR, S, GRP>(kv, n0, f, out, kb), ...);
 }
 
-// out = T[kappa f] (TR = false) or T^T[kappa] f (TR = true), kappa_a read
-// from plane a of the kappa array at node n0.  The same terms in the same
-// order as tprod.
-template <int D, int M, bool TR, class S>
+// out = T[kappa f] (TR = false) or T^T[kappa] f (TR = true) on the coefficients
+// of need <= J, kappa_a read from plane a of the kappa array at node n0.  The
+// same terms in the same order as tprod.  (TR: f is zero off that set, and so
+// is the result.)
+template <int D, int M, bool VEL, int J, bool TR, class S>
 __device__ __forceinline__ void tprod_grouped(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                               typename S::C* out) {
   using T = typename S::C;
   constexpr int NP = VK<D, M>::NP, NG = (NP + kKappaGroup - 1) / kKappaGroup;
 #pragma unroll
   for (int b = 0; b < NP; ++b) out[b] = T(0);
-  kgroup_steps<D, M, TR, S>(kv, n0, f, out, std::make_integer_sequence<int, NG>{});
+  kgroup_steps<D, M, VEL, J, TR, S>(kv, n0, f, out, std::make_integer_sequence<int, NG>{});
 }
 
 // The forward variable-kappa half-steps take the grouped kappa loads from
 // m = 4 on, where the per-term loads' addresses spill (2D m = 4 FP64: 788 ->
 // 124 bytes of scratch per lane, m = 5 FP32: 507 -> 359 VGPRs); below, the
 // per-term loads measured faster (2D m = 3 1024^2 FP32 0.86 against 0.91 ms).
-template <int D, int M, class S>
+template <int D, int M, bool VEL, int J, class S>
 __device__ __forceinline__ void tprod_fwd(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                           typename S::C* out) {
   if constexpr (M >= 4)
-    tprod_grouped<D, M, false, S>(kv, n0, f, out);
+    tprod_grouped<D, M, VEL, J, false, S>(kv, n0, f, out);
   else
-    tprod<D, M, S>(kv, n0, f, out);
+    tprod<D, M, VEL, J, S>(kv, n0, f, out);
 }
 
 // Full interpolant c[b_x + N2 (b_y + N2 b_z)] of one component from its 2^D
@@ -461,11 +507,12 @@ __device__ __forceinline__ void interp_full(const typename S::View& f, int comp,
 // template argument so that every register index is a compile-time constant:
 // as one 64 x 64 loop nest the compiler stopped unrolling and indexed f
 // through scratch memory).
-template <int D, int M, int A, class S>
+template <int D, int M, bool VEL, int J, int A, class S>
 __device__ __forceinline__ void tprod_term(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                            typename S::C* out) {
   constexpr int N2 = 2 * M + 2, AX = A % N2, AY = (A / N2) % N2, AZ = A / (N2 * N2);
   constexpr int NY = D > 1 ? N2 : 1, NZ = D > 2 ? N2 : 1;
+  if constexpr (kNeed<D, M, VEL>.n[A] > J) return;
   const typename S::C ka = S::load(kv, A, n0);
 #pragma unroll
   for (int bz = AZ; bz < NZ; ++bz)
@@ -474,36 +521,40 @@ __device__ __forceinline__ void tprod_term(const typename S::View& kv, uint32_t 
 #pragma unroll
       for (int bx = AX; bx < N2; ++bx) {
         const int o = bx + N2 * (by + N2 * bz);
+        if (kNeed<D, M, VEL>.n[o] > J) continue;
         out[o] = fma(ka, f[(bx - AX) + N2 * ((by - AY) + N2 * (bz - AZ))], out[o]);
       }
 }
 
-template <int D, int M, class S, int... A>
+template <int D, int M, bool VEL, int J, class S, int... A>
 __device__ __forceinline__ void tprod_terms(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                             typename S::C* out, std::integer_sequence<int, A...>) {
-  (tprod_term<D, M, A, S>(kv, n0, f, out), ...);
+  (tprod_term<D, M, VEL, J, A, S>(kv, n0, f, out), ...);
 }
 
-// out = T[kappa f]: out_b = sum_{a <= b} kappa_a f_{b-a} (per variable),
-// kappa_a read from plane a of the kappa array at node n0.
-template <int D, int M, class S>
+// out = T[kappa f]: out_b = sum_{a <= b} kappa_a f_{b-a} (per variable) on the
+// coefficients of need <= J, kappa_a read from plane a of the kappa array at
+// node n0.
+template <int D, int M, bool VEL, int J, class S>
 __device__ __forceinline__ void tprod(const typename S::View& kv, uint32_t n0, const typename S::C* f,
                                       typename S::C* out) {
   using T = typename S::C;
   constexpr int NP = VK<D, M>::NP;
 #pragma unroll
   for (int b = 0; b < NP; ++b) out[b] = T(0);
-  tprod_terms<D, M, S>(kv, n0, f, out, std::make_integer_sequence<int, NP>{});
+  tprod_terms<D, M, VEL, J, S>(kv, n0, f, out, std::make_integer_sequence<int, NP>{});
 }
 
 // out = sc Lap f in coefficient space: sc sum_i (b_i + 1)(b_i + 2) / h_i^2 f_{b + 2 e_i}.
-template <int D, int M, typename T>
+// On the coefficients of need <= J.
+template <int D, int M, bool VEL, int J, typename T>
 __device__ __forceinline__ void lap_coef(const T* f, T* out, const T* ih, T sc) {
   constexpr int N2 = 2 * M + 2, NP = VK<D, M>::NP;
   const T ix2 = sc * ih[0] * ih[0], iy2 = sc * ih[1] * ih[1], iz2 = sc * ih[2] * ih[2];
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     const int bx = b % N2, by = (b / N2) % N2, bz = b / (N2 * N2);
+    if (kNeed<D, M, VEL>.n[b] > J) continue;
     T v = T(0);
     if (bx + 2 < N2) v = fma(T((bx + 1) * (bx + 2)) * ix2, f[b + 2], v);
     if (D > 1 && by + 2 < N2) v = fma(T((by + 1) * (by + 2)) * iy2, f[b + 2 * N2], v);
@@ -519,6 +570,37 @@ __host__ __device__ constexpr int poly_index(int s, int dx, int dy, int dz) {
   constexpr int MP = M + 1, N2 = 2 * M + 2;
   const int sx = s % MP, sy = D > 1 ? (s / MP) % MP : 0, sz = D > 2 ? s / (MP * MP) : 0;
   return (sx + dx) + N2 * ((sy + dy) + N2 * (sz + dz));
+}
+
+// t_k = T[kappa (w_k / w_{k-1}) Lap t_{k-1}] for k = 1 .. kmax, each handed to
+// add: a loop while the products are full, then one unrolled step per J.
+template <int D, int M, bool VEL, int J, class S, class F>
+__device__ __forceinline__ void var_series_tail(const typename S::View& kv, uint32_t n0, typename S::C* t,
+                                                const VarArgs<typename S::C>& va, F& add) {
+  if constexpr (J >= 0) {
+    using T = typename S::C;
+    T l[VK<D, M>::NP];
+    lap_coef<D, M, VEL, J>(t, l, va.ih, va.ratio[VK<D, M>::KMAX - J]);
+    tprod_fwd<D, M, VEL, J, S>(kv, n0, l, t);
+    add(t);
+    var_series_tail<D, M, VEL, J - 1, S>(kv, n0, t, va, add);
+  }
+}
+template <int D, int M, bool VEL, class S, class F>
+__device__ __forceinline__ void var_series(const typename S::View& kv, uint32_t n0, typename S::C* t,
+                                           const VarArgs<typename S::C>& va, F& add) {
+  using T = typename S::C;
+  // m >= 4: full products throughout (one copy of an already long product; the
+  // last steps' own copies spill)
+  constexpr int KMAX = VK<D, M>::KMAX, TOP = M >= 4 ? 0 : kNeedTop<D, M, VEL>;
+#pragma unroll 1
+  for (int k = 1; k <= KMAX - TOP; ++k) {
+    T l[VK<D, M>::NP];
+    lap_coef<D, M, VEL, KMAX>(t, l, va.ih, va.ratio[k]);
+    tprod_fwd<D, M, VEL, KMAX, S>(kv, n0, l, t);
+    add(t);
+  }
+  var_series_tail<D, M, VEL, (TOP - 1 < KMAX - 1 ? TOP - 1 : KMAX - 1), S>(kv, n0, t, va, add);
 }
 
 template <int D, int M, class S>
@@ -548,17 +630,14 @@ __device__ __forceinline__ void p_half_var_body(typename S::View p, typename S::
     }
   }
   T t[NP], acc[NC];
-  tprod_fwd<D, M, S>(kp, n0, div, t);  // t_0 = w_0 r_0
+  tprod_fwd<D, M, false, VK<D, M>::KMAX, S>(kp, n0, div, t);  // t_0 = w_0 r_0
 #pragma unroll
   for (int s = 0; s < NC; ++s) acc[s] = t[poly_index<D, M>(s, 0, 0, 0)];
-#pragma unroll 1
-  for (int k = 1; k <= VK<D, M>::KMAX; ++k) {
-    T l[NP];
-    lap_coef<D, M>(t, l, va.ih, va.ratio[k]);
-    tprod_fwd<D, M, S>(kp, n0, l, t);  // t_k = w_k r_k
+  auto add = [&](const T* x) {
 #pragma unroll
-    for (int s = 0; s < NC; ++s) acc[s] += t[poly_index<D, M>(s, 0, 0, 0)];
-  }
+    for (int s = 0; s < NC; ++s) acc[s] += x[poly_index<D, M>(s, 0, 0, 0)];
+  };
+  var_series<D, M, false, S>(kp, n0, t, va, add);
   finish_pressure<D, M, S>(g, p, n0, acc);
 }
 
@@ -578,33 +657,28 @@ __device__ __forceinline__ void u_half_var_body(typename S::View u, typename S::
   uint32_t cn[1 << D];
   corner_nodes<D>(g, j, cn);  // primal j = q + e
   const uint32_t n0 = out_index<D>(g, j);
-  T gk[NP], q[NP];  // gk: t_k = w_k g_k
+  T gk[NP], q[NP];  // gk: t_k = w_k g_k; q: their sum on the output set (need 0)
   interp_full<D, M, S>(p, 0, cn, gk);
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     gk[b] *= va.w0;
     q[b] = gk[b];
   }
-#pragma unroll 1
-  for (int k = 1; k <= VK<D, M>::KMAX; ++k) {
-    T l[NP];
-    lap_coef<D, M>(gk, l, va.ih, va.ratio[k]);
-    tprod_fwd<D, M, S>(ku, n0, l, gk);
+  auto add = [&](const T* x) {
 #pragma unroll
-    for (int b = 0; b < NP; ++b) q[b] += gk[b];
-  }
+    for (int b = 0; b < NP; ++b)
+      if (kNeed<D, M, true>.n[b] == 0) q[b] += x[b];
+  };
+  var_series<D, M, true, S>(ku, n0, gk, va, add);
   // u_i[s] -= wscale (s_i + 1) / h_i q[s + e_i]
+  T f[D];
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const T f = wscale * va.ih[i];
-#pragma unroll
-    for (int s = 0; s < NC; ++s) {
-      const int si = digit(s, MP, i);
-      const T qv = q[poly_index<D, M>(s, i == 0, i == 1, i == 2)];
-      const T a = -(T)(si + 1) * f;
-      S::update(u, i * NC + s, n0, [&](T x) { return fma(a, qv, x); });
-    }
-  }
+  for (int i = 0; i < D; ++i) f[i] = wscale * va.ih[i];
+  update_outputs_as<D, S, D * NC, false>(u, n0, [](int t) { return t; }, [&](int t, T x) {
+    const int i = t / NC, s = t % NC;
+    const T a = -(T)(digit(s, MP, i) + 1) * f[i];
+    return fma(a, q[poly_index<D, M>(s, i == 0, i == 1, i == 2)], x);
+  });
 }
 
 template <int D, int M, class S>
@@ -622,8 +696,8 @@ __global__ void __launch_bounds__(256) u_half_var(typename S::View u, typename S
 // lane l < (2m+2)^2 owns the x-pencil b_y = l mod (2m+2), b_z = l div (2m+2)
 // (2m+2 coefficients along x, held in registers).  The arithmetic is that of
 // the per-node kernels above (the same tensor-product passes, and the same
-// products kappa_a f_{b-a}), except that at m = 2 a pencil's sum is formed
-// from partial sums over chunks of its terms (below).
+// products kappa_a f_{b-a}), except that a pencil's sum is formed from partial
+// sums over chunks of its terms (below).
 // ---------------------------------------------------------------------------
 template <int M>
 struct VW {
@@ -709,91 +783,93 @@ __device__ __forceinline__ void interp_wave(const typename S::View& f, int comp,
   __syncthreads();
 }
 
-// Work split of one truncated product over the 64 lanes.  Pencil (by, bz)
-// sums over the (by+1)(bz+1) pairs (a_y, a_z) <= (by, bz) (a_z outer), 2m+2
-// to 36 of them at m = 2; one lane per pencil would leave 28 lanes idle and
-// wait on the longest pencil.  Instead every pencil's pairs are cut into
-// chunks of at most C consecutive pairs, one chunk per lane, C the smallest
-// length that needs at most 64 chunks (m = 2: C = 10, 60 chunks; m = 3: no
-// cut, the 64 pencils take the 64 lanes), and each pencil then adds its
-// chunks' partial sums in chunk order.
-template <int M>
+// Work split of one truncated product over the 64 lanes.  The product is
+// formed on the pencils with a coefficient of need <= J (above), on the first
+// XL coefficients of each (the most any of them needs).  Pencil (by, bz) sums
+// over the (by+1)(bz+1) pairs (a_y, a_z) <= (by, bz) (a_z outer), 1 to
+// (2m+2)^2 of them; one lane per pencil would wait on the longest.  Instead
+// every pencil's pairs are cut into chunks of at most C consecutive pairs, one
+// chunk per lane, C the smallest length that needs at most 64 chunks (m = 2:
+// C = 10 for a full product, 1 for the last), and each pencil then adds its
+// chunks' partial sums in chunk order.  Pairs the longest lane walks in one
+// half-step: m = 2 pressure 70 with full products, 49 so; m = 3 640 with
+// full products, 453 so.
+template <int M, bool VEL, int J>
 struct WaveSched {
-  int C, n;
-  int8_t by[64], bz[64], i0[64], cnt[64];  // chunk (lane) -> pencil, first pair, pairs
-  int8_t first[64], nch[64];               // pencil -> its first chunk, chunks
+  static constexpr int N2 = 2 * M + 2;
+  using ND = Need<3, M, VEL>;
+  int C, n, xl, pairs;
+  uint32_t chunk[64];  // lane -> by, bz, first pair, pairs (a byte each)
+  uint32_t pen[64];    // pencil -> its first chunk, chunks
+  static constexpr bool needed(int q) { return ND::of(0, q % N2, q / N2) <= J; }
+  static constexpr int weight(int q) { return (q % N2 + 1) * (q / N2 + 1); }
+  constexpr WaveSched() : C(1), n(0), xl(0), pairs(0), chunk(), pen() {
+    for (int b = 0; b < N2; ++b)
+      if (ND::of(b, 0, 0) <= J) xl = b + 1;
+    for (;; ++C) {
+      int k = 0;
+      for (int q = 0; q < N2 * N2; ++q)
+        if (needed(q)) k += (weight(q) + C - 1) / C;
+      if (k <= 64) break;
+    }
+    for (int q = 0; q < N2 * N2; ++q) {
+      if (!needed(q)) continue;
+      const int w = weight(q);
+      pen[q] = (uint32_t)(n | ((w + C - 1) / C) << 8);
+      for (int i = 0; i < w; i += C, ++n) {
+        const int cnt = w - i < C ? w - i : C;
+        chunk[n] = (uint32_t)(q % N2 | (q / N2) << 8 | i << 16 | cnt << 24);
+        pairs += cnt;
+      }
+    }
+  }
+  // every needed pencil's pairs covered once, in order, by its chunks
+  constexpr bool ok() const {
+    if (n > 64) return false;
+    int total = 0;
+    for (int q = 0; q < N2 * N2; ++q) {
+      if (!needed(q)) continue;
+      int next = 0;
+      const int first = pen[q] & 255, nch = pen[q] >> 8;
+      for (int c = first; c < first + nch; ++c) {
+        if ((int)(chunk[c] & 255) != q % N2 || (int)((chunk[c] >> 8) & 255) != q / N2) return false;
+        if ((int)((chunk[c] >> 16) & 255) != next) return false;
+        const int cnt = chunk[c] >> 24;
+        if (cnt < 1 || cnt > C) return false;
+        next += cnt;
+      }
+      if (next != weight(q)) return false;
+      total += next;
+    }
+    return total == pairs;
+  }
 };
-
-template <int M>
-constexpr WaveSched<M> wave_sched() {
-  constexpr int N2 = 2 * M + 2;
-  WaveSched<M> s{};
-  int C = 1;
-  for (;; ++C) {
-    int n = 0;
-    for (int q = 0; q < N2 * N2; ++q) n += ((q % N2 + 1) * (q / N2 + 1) + C - 1) / C;
-    if (n <= 64) break;
-  }
-  s.C = C;
-  int c = 0;
-  for (int q = 0; q < N2 * N2; ++q) {
-    const int w = (q % N2 + 1) * (q / N2 + 1);
-    s.first[q] = (int8_t)c;
-    s.nch[q] = (int8_t)((w + C - 1) / C);
-    for (int i = 0; i < w; i += C, ++c) {
-      s.by[c] = (int8_t)(q % N2);
-      s.bz[c] = (int8_t)(q / N2);
-      s.i0[c] = (int8_t)i;
-      s.cnt[c] = (int8_t)(w - i < C ? w - i : C);
-    }
-  }
-  s.n = c;
-  return s;
-}
-
-// Every pencil's pairs covered once, in order, by its chunks.
-template <int M>
-constexpr bool wave_sched_ok(const WaveSched<M>& s) {
-  constexpr int N2 = 2 * M + 2;
-  if (s.n > 64) return false;
-  for (int q = 0; q < N2 * N2; ++q) {
-    int next = 0;
-    for (int c = s.first[q]; c < s.first[q] + s.nch[q]; ++c) {
-      if (s.by[c] != q % N2 || s.bz[c] != q / N2 || s.i0[c] != next || s.cnt[c] < 1 || s.cnt[c] > s.C) return false;
-      next += s.cnt[c];
-    }
-    if (next != (q % N2 + 1) * (q / N2 + 1)) return false;
-  }
-  return true;
-}
-
-template <int M>
-constexpr WaveSched<M> kWaveSched = wave_sched<M>();
-static_assert(wave_sched_ok<2>(kWaveSched<2>) && kWaveSched<2>.C == 10 && kWaveSched<2>.n == 60, "m = 2 split");
-static_assert(wave_sched_ok<3>(kWaveSched<3>) && kWaveSched<3>.n == 64, "m = 3: one chunk per pencil");
-// LDS words for the chunks' partial sums (1 when no pencil is cut)
-template <int M>
-constexpr int kWaveRed = kWaveSched<M>.n > VW<M>::NPEN ? 64 * VW<M>::N2 : 1;
+template <int M, bool VEL, int J>
+__device__ constexpr WaveSched<M, VEL, J> kWaveSched{};
+static_assert(kWaveSched<2, false, 6>.ok() && kWaveSched<2, false, 6>.C == 10 && kWaveSched<2, false, 6>.n == 60, "");
+static_assert(kWaveSched<2, false, 0>.ok() && kWaveSched<2, false, 0>.C == 1 && kWaveSched<2, false, 0>.xl == 3, "");
+static_assert(kWaveSched<2, true, 1>.ok() && kWaveSched<3, false, 6>.ok() && kWaveSched<3, true, 2>.ok(), "");
 
 // Partial sum of pencil (by, bz) of T[kappa f] over the pairs i0 .. i0+cnt-1:
-// out[b_x] = sum of kappa_a f_{b-a}, a_x <= b_x, K and F in LDS.
-template <int M, typename T>
-__device__ __forceinline__ void tprod_chunk(const T* KA, const T* F, int by, int bz, int i0, int cnt, T* out) {
+// out[b_x] = sum of kappa_a f_{b-a}, a_x <= b_x < XL, K and F in LDS.
+template <int M, int XL, typename T>
+__device__ __forceinline__ void tprod_chunk(const T* KA, const T* F, uint32_t chunk, T* out) {
   constexpr int N2 = VW<M>::N2;
+  const int by = chunk & 255, bz = (chunk >> 8) & 255, i0 = (chunk >> 16) & 255, cnt = chunk >> 24;
 #pragma unroll
-  for (int b = 0; b < N2; ++b) out[b] = T(0);
+  for (int b = 0; b < XL; ++b) out[b] = T(0);
   int ay = i0 % (by + 1), az = i0 / (by + 1);
   for (int i = 0; i < cnt; ++i) {
-    T kp[N2], fp[N2];
+    T kp[XL], fp[XL];
     const T* kr = KA + N2 * (ay + N2 * az);
     const T* fr = F + N2 * ((by - ay) + N2 * (bz - az));
 #pragma unroll
-    for (int b = 0; b < N2; ++b) {
+    for (int b = 0; b < XL; ++b) {
       kp[b] = kr[b];
       fp[b] = fr[b];
     }
 #pragma unroll
-    for (int bx = 0; bx < N2; ++bx)
+    for (int bx = 0; bx < XL; ++bx)
 #pragma unroll
       for (int ax = 0; ax <= bx; ++ax) out[bx] = fma(kp[ax], fp[bx - ax], out[bx]);
     if (++ay > by) {
@@ -803,87 +879,56 @@ __device__ __forceinline__ void tprod_chunk(const T* KA, const T* F, int by, int
   }
 }
 
-// Pencil (by, bz) of T[kappa f] in one lane (no cut): a_z outer, a_y inner.
-template <int M, typename T>
-__device__ __forceinline__ void tprod_pencil(const T* KA, const T* F, int by, int bz, T* out) {
-  constexpr int N2 = VW<M>::N2;
-#pragma unroll
-  for (int b = 0; b < N2; ++b) out[b] = T(0);
-  for (int az = 0; az <= bz; ++az)
-    for (int ay = 0; ay <= by; ++ay) {
-      T kp[N2], fp[N2];
-      const T* kr = KA + N2 * (ay + N2 * az);
-      const T* fr = F + N2 * ((by - ay) + N2 * (bz - az));
-#pragma unroll
-      for (int b = 0; b < N2; ++b) {
-        kp[b] = kr[b];
-        fp[b] = fr[b];
-      }
-#pragma unroll
-      for (int bx = 0; bx < N2; ++bx)
-#pragma unroll
-        for (int ax = 0; ax <= bx; ++ax) out[bx] = fma(kp[ax], fp[bx - ax], out[bx]);
-    }
-}
-
-// This lane's chunk of a truncated product, and the pencil totals.
-template <int M>
+// This lane's pencil, and its chunk of every product (one schedule per J up to
+// the first full product).
+template <int M, bool VEL>
 struct WaveLane {
-  int lane, cby, cbz, ci0, ccnt;  // the lane's chunk
-  bool pen;                       // lane < (2m+2)^2 owns pencil (by, bz) = (lane mod N2, lane div N2)
-  int by, bz, first, nch;
+  static constexpr int TOP = kNeedTop<3, M, VEL>, N2 = VW<M>::N2;
+  int lane;
+  bool pen;  // lane < (2m+2)^2 owns pencil (by, bz) = (lane mod N2, lane div N2)
+  int by, bz;
+  uint32_t chunk[TOP + 1], tot[TOP + 1];
+  template <int... J>
+  __device__ __forceinline__ void load(std::integer_sequence<int, J...>) {
+    ((chunk[J] = kWaveSched<M, VEL, J>.chunk[lane], tot[J] = kWaveSched<M, VEL, J>.pen[lane]), ...);
+  }
   __device__ __forceinline__ explicit WaveLane(int l) : lane(l) {
-    constexpr int N2 = VW<M>::N2;
-    const WaveSched<M>& s = kWaveSched<M>;
-    const bool has = l < s.n;
-    cby = has ? s.by[l] : 0;
-    cbz = has ? s.bz[l] : 0;
-    ci0 = has ? s.i0[l] : 0;
-    ccnt = has ? s.cnt[l] : 0;
     pen = l < VW<M>::NPEN;
     by = pen ? l % N2 : 0;
     bz = pen ? l / N2 : 0;
-    first = pen ? s.first[l] : 0;
-    nch = pen ? s.nch[l] : 0;
+    load(std::make_integer_sequence<int, TOP + 1>{});
   }
 };
 
-// t = pencil (by, bz) of T[kappa F] on the owning lanes; RED: 64 (2m+2)
-// partial sums.  Begins and ends with LDS reads only; callers separate it
-// from the next writes of F and RED by a barrier.
-template <int M, typename T>
-__device__ __forceinline__ void tprod_wave(const T* KA, const T* F, T* RED, const WaveLane<M>& w, T* t) {
-  constexpr int N2 = VW<M>::N2;
-  constexpr bool kSplit = kWaveSched<M>.n > VW<M>::NPEN;
-  T part[N2];
-  if constexpr (kSplit)
-    tprod_chunk<M>(KA, F, w.cby, w.cbz, w.ci0, w.ccnt, part);
-  else
-    tprod_pencil<M>(KA, F, w.cby, w.cbz, part);
-  if constexpr (kSplit) {
+// t = pencil (by, bz) of T[kappa F] on the owning lanes, its first XL
+// coefficients; RED: 64 (2m+2) partial sums.  Begins and ends with LDS reads
+// only; callers separate it from the next writes of F and RED by a barrier.
+template <int M, bool VEL, int J, typename T>
+__device__ __forceinline__ void tprod_wave(const T* KA, const T* F, T* RED, const WaveLane<M, VEL>& w, T* t) {
+  constexpr int N2 = VW<M>::N2, JJ = J < kNeedTop<3, M, VEL> ? J : kNeedTop<3, M, VEL>;
+  constexpr int XL = kWaveSched<M, VEL, JJ>.xl;
+  T part[XL];
+  tprod_chunk<M, XL>(KA, F, w.chunk[JJ], part);
 #pragma unroll
-    for (int b = 0; b < N2; ++b) RED[w.lane * N2 + b] = part[b];
-    __syncthreads();
+  for (int b = 0; b < XL; ++b) RED[w.lane * N2 + b] = part[b];
+  __syncthreads();
 #pragma unroll
-    for (int b = 0; b < N2; ++b) t[b] = T(0);
-    for (int q = 0; q < w.nch; ++q) {
+  for (int b = 0; b < XL; ++b) t[b] = T(0);
+  const int first = w.tot[JJ] & 255, nch = w.tot[JJ] >> 8;
+  for (int q = 0; q < nch; ++q) {
 #pragma unroll
-      for (int b = 0; b < N2; ++b) t[b] += RED[(w.first + q) * N2 + b];
-    }
-  } else {  // chunk c is pencil c
-#pragma unroll
-    for (int b = 0; b < N2; ++b) t[b] = part[b];
+    for (int b = 0; b < XL; ++b) t[b] += RED[(first + q) * N2 + b];
   }
 }
 
 // Pencil (by, bz) of sc Lap t (coefficient space), t in LDS.
-template <int M, typename T>
+template <int M, int XL, typename T>
 __device__ __forceinline__ void lap_pencil(const T* t, int by, int bz, const T* ih, T sc, T* out) {
   constexpr int N2 = VW<M>::N2;
   const T ix2 = sc * ih[0] * ih[0], iy2 = sc * ih[1] * ih[1], iz2 = sc * ih[2] * ih[2];
   const T* r0 = t + N2 * (by + N2 * bz);
 #pragma unroll
-  for (int bx = 0; bx < N2; ++bx) {
+  for (int bx = 0; bx < XL; ++bx) {
     T v = T(0);
     if (bx + 2 < N2) v = fma(T((bx + 1) * (bx + 2)) * ix2, r0[bx + 2], v);
     if (by + 2 < N2) v = fma(T((by + 1) * (by + 2)) * iy2, r0[bx + 2 * N2], v);
@@ -892,17 +937,61 @@ __device__ __forceinline__ void lap_pencil(const T* t, int by, int bz, const T* 
   }
 }
 
+// One step of the series at J: t <- T[kappa r Lap t] on the lane's pencil, for
+// the pencils and coefficients of need <= J.  Coefficients beyond hold no
+// defined value and reach none that is needed.
+template <int M, bool VEL, int J, typename T>
+__device__ __forceinline__ void wave_step(const T* KA, T* F, T* Tc, T* RED, const WaveLane<M, VEL>& w, const T* ih,
+                                          T ratio, T* t) {
+  constexpr int N2 = VW<M>::N2, TOP = kNeedTop<3, M, VEL>;
+  constexpr int XL = kWaveSched<M, VEL, (J < TOP ? J : TOP)>.xl;
+  constexpr int XT = kWaveSched<M, VEL, (J + 1 < TOP ? J + 1 : TOP)>.xl;
+  if (w.pen) {
+#pragma unroll
+    for (int b = 0; b < XT; ++b) Tc[N2 * (w.by + N2 * w.bz) + b] = t[b];
+  }
+  __syncthreads();
+  if (w.pen) {
+    T l[XL];
+    lap_pencil<M, XL>(Tc, w.by, w.bz, ih, ratio, l);
+#pragma unroll
+    for (int b = 0; b < XL; ++b) F[N2 * (w.by + N2 * w.bz) + b] = l[b];
+  }
+  __syncthreads();
+  tprod_wave<M, VEL, J>(KA, F, RED, w, t);
+}
+template <int M, bool VEL, int J, typename T, class FA>
+__device__ __forceinline__ void wave_series_tail(const T* KA, T* F, T* Tc, T* RED, const WaveLane<M, VEL>& w,
+                                                 const VarArgs<T>& va, T* t, FA& add) {
+  if constexpr (J >= 0) {
+    wave_step<M, VEL, J>(KA, F, Tc, RED, w, va.ih, va.ratio[VK<3, M>::KMAX - J], t);
+    add(t);
+    wave_series_tail<M, VEL, J - 1>(KA, F, Tc, RED, w, va, t, add);
+  }
+}
+template <int M, bool VEL, typename T, class FA>
+__device__ __forceinline__ void wave_series(const T* KA, T* F, T* Tc, T* RED, const WaveLane<M, VEL>& w,
+                                            const VarArgs<T>& va, T* t, FA& add) {
+  constexpr int KMAX = VK<3, M>::KMAX, TOP = kNeedTop<3, M, VEL>;
+#pragma unroll 1
+  for (int k = 1; k <= KMAX - TOP; ++k) {
+    wave_step<M, VEL, KMAX>(KA, F, Tc, RED, w, va.ih, va.ratio[k], t);
+    add(t);
+  }
+  wave_series_tail<M, VEL, (TOP < KMAX ? TOP : KMAX) - 1>(KA, F, Tc, RED, w, va, t, add);
+}
+
 template <int M, class S>
 __device__ __forceinline__ void p_half_var_wave_body(typename S::View p, typename S::View u, typename S::View kp,
                                                      Grid g, VarArgs<typename S::C> va, int32_t per_xcd, int blk) {
   using T = typename S::C;
   constexpr int MP = VW<M>::MP, N2 = VW<M>::N2, NP = VW<M>::NP;
   static_assert(VK<3, M>::KMAX <= kVarMaxK, "series longer than the ratio table");
-  __shared__ T A[NP], B[NP], KA[NP], RED[kWaveRed<M>];
+  __shared__ T A[NP], B[NP], KA[NP], RED[64 * N2];
   int32_t j[3];
   if (!wave_node(g, blk, per_xcd, j)) return;  // uniform over the workgroup
   const int lane = threadIdx.x;
-  const WaveLane<M> w(lane);
+  const WaveLane<M, false> w(lane);
   const uint32_t n0 = out_index<3>(g, j);
   const uint32_t cnl = corner_node_of(g, j, lane & 7);  // dual q = j - 1 + e
   for (int a = lane; a < NP; a += 64) KA[a] = S::load(kp, a, n0);
@@ -937,27 +1026,14 @@ __device__ __forceinline__ void p_half_var_wave_body(typename S::View p, typenam
   T acc[MP], t[N2];
 #pragma unroll
   for (int b = 0; b < N2; ++b) t[b] = T(0);
-  tprod_wave<M>(KA, F, RED, w, t);  // t_0 = w_0 r_0
+  tprod_wave<M, false, VK<3, M>::KMAX>(KA, F, RED, w, t);  // t_0 = w_0 r_0
 #pragma unroll
   for (int b = 0; b < MP; ++b) acc[b] = t[b];
-#pragma unroll 1
-  for (int k = 1; k <= VK<3, M>::KMAX; ++k) {
-    if (pen) {
+  auto add = [&](const T* x) {
 #pragma unroll
-      for (int b = 0; b < N2; ++b) Tc[N2 * (by + N2 * bz) + b] = t[b];
-    }
-    __syncthreads();
-    if (pen) {
-      T l[N2];
-      lap_pencil<M>(Tc, by, bz, va.ih, va.ratio[k], l);
-#pragma unroll
-      for (int b = 0; b < N2; ++b) F[N2 * (by + N2 * bz) + b] = l[b];
-    }
-    __syncthreads();
-    tprod_wave<M>(KA, F, RED, w, t);  // t_k = w_k r_k
-#pragma unroll
-    for (int b = 0; b < MP; ++b) acc[b] += t[b];
-  }
+    for (int b = 0; b < MP; ++b) acc[b] += x[b];
+  };
+  wave_series<M, false>(KA, F, Tc, RED, w, va, t, add);
   if (own) {
 #pragma unroll
     for (int bx = 0; bx < MP; ++bx)
@@ -971,11 +1047,11 @@ __device__ __forceinline__ void u_half_var_wave_body(typename S::View u, typenam
                                                      int32_t per_xcd, int blk) {
   using T = typename S::C;
   constexpr int MP = VW<M>::MP, N2 = VW<M>::N2, NP = VW<M>::NP, NC = VW<M>::NC;
-  __shared__ T A[NP], B[NP], KA[NP], RED[kWaveRed<M>];
+  __shared__ T A[NP], B[NP], KA[NP], RED[64 * N2];
   int32_t j[3];
   if (!wave_node(g, blk, per_xcd, j)) return;  // uniform over the workgroup
   const int lane = threadIdx.x;
-  const WaveLane<M> w(lane);
+  const WaveLane<M, true> w(lane);
   const uint32_t n0 = out_index<3>(g, j);
   const uint32_t cnl = corner_node_of(g, j, lane & 7);  // primal j = q + e
   for (int a = lane; a < NP; a += 64) KA[a] = S::load(ku, a, n0);
@@ -994,24 +1070,11 @@ __device__ __forceinline__ void u_half_var_wave_body(typename S::View u, typenam
 #pragma unroll
   for (int b = 0; b < N2; ++b) q[b] = gk[b];
   __syncthreads();
-#pragma unroll 1
-  for (int k = 1; k <= VK<3, M>::KMAX; ++k) {
-    if (pen) {
+  auto add = [&](const T* x) {  // q[0 .. m + 1] is what the outputs take
 #pragma unroll
-      for (int b = 0; b < N2; ++b) Tc[N2 * (by + N2 * bz) + b] = gk[b];
-    }
-    __syncthreads();
-    if (pen) {
-      T l[N2];
-      lap_pencil<M>(Tc, by, bz, va.ih, va.ratio[k], l);
-#pragma unroll
-      for (int b = 0; b < N2; ++b) F[N2 * (by + N2 * bz) + b] = l[b];
-    }
-    __syncthreads();
-    tprod_wave<M>(KA, F, RED, w, gk);
-#pragma unroll
-    for (int b = 0; b < N2; ++b) q[b] += gk[b];
-  }
+    for (int b = 0; b <= MP; ++b) q[b] += x[b];
+  };
+  wave_series<M, true>(KA, F, Tc, RED, w, va, gk, add);
   // u_i[s] -= wscale (s_i + 1) / h_i q[s + e_i]: the pencil holding q[s + e_i]
   // updates u_i[s]
   if (pen) {
@@ -1186,12 +1249,12 @@ __device__ __forceinline__ void adjoint_series(const typename S::View& kv, uint3
     for (int b = 0; b < NP; ++b) t[b] = STAGE ? L(t0s, b, NP) : t0r[b];
 #pragma unroll 1
     for (int q = 1; q < k; ++q) {  // t = t_{k-1}
-      lap_coef<D, M>(t, l, va.ih, va.ratio[q]);
-      tprod_grouped<D, M, false, S>(kv, n0, l, t);
+      lap_coef<D, M, !PSIDE, VK<D, M>::KMAX>(t, l, va.ih, va.ratio[q]);
+      tprod_grouped<D, M, !PSIDE, VK<D, M>::KMAX, false, S>(kv, n0, l, t);
     }
-    lap_coef<D, M>(t, l, va.ih, va.ratio[k]);  // g_k
+    lap_coef<D, M, !PSIDE, VK<D, M>::KMAX>(t, l, va.ih, va.ratio[k]);  // g_k
     corr<D, M>(lam, l, L, gs);
-    tprod_grouped<D, M, true, S>(kv, n0, lam, t);
+    tprod_grouped<D, M, !PSIDE, VK<D, M>::KMAX, true, S>(kv, n0, lam, t);
     lapT_coef<D, M>(t, l, va.ih, va.ratio[k]);
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
@@ -1237,7 +1300,7 @@ __global__ void __launch_bounds__(64) grad_p_var(typename S::View pb, typename S
       if (bi + 1 < N2) f[b] = fma(T(bi + 1) * w, c[b + st], f[b]);
     }
   }
-  tprod_grouped<D, M, false, S>(kp, n0, f, t0);
+  tprod_grouped<D, M, false, VK<D, M>::KMAX, false, S>(kp, n0, f, t0);
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     if (STAGE) {
@@ -1259,7 +1322,7 @@ __global__ void __launch_bounds__(64) grad_p_var(typename S::View pb, typename S
 #pragma unroll
   for (int b = 0; b < NP; ++b) gk[(size_t)b * g.onodes + n0] -= (double)L(GS, b, NP);
   T phi[NP];  // dS/df
-  tprod_grouped<D, M, true, S>(kp, n0, lam, phi);
+  tprod_grouped<D, M, false, VK<D, M>::KMAX, true, S>(kp, n0, lam, phi);
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     const T w = va.w0 * va.ih[i];
