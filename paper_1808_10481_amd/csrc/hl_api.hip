@@ -193,6 +193,8 @@ struct hl_plan_s {
   void* sp = nullptr;
   void* su = nullptr;
   double* gpart = nullptr;
+  void* stage = nullptr;       // staging of host-layout data (convert_component), at most kStageKeep
+  size_t stage_bytes = 0;
   double* dpartial = nullptr;  // norms scratch, kNormBlocks per plane
   int device = 0;
   // hl_step replays a captured graph of kGraphChunk steps for the last
@@ -573,46 +575,229 @@ LayoutMap layout_of(const hl_plan_s* pl, int field) {
   return hl_host::field_layout(pl->d, pl->m, pl->K, pl->walls, field);
 }
 
+// ---------------------------------------------------------------------------
+// Host layout <-> device planes on the device.  Host arrays cross the bus as
+// they are (FP64, nodes then coefficients) through a device staging buffer and
+// a kernel transposes them; on host threads the conversion took 2.5 ms for
+// 192 x 160 nodes of 16 + 32 coefficients (thread start-up, strided writes),
+// against 0.4 ms for the copies.  A workgroup takes 32 nodes along j_1 and up
+// to 64 coefficients through LDS, so that both sides move whole lines: runs of
+// coefficients on the host side, runs of i_1 on the plane side.
+// ---------------------------------------------------------------------------
+constexpr int kConvNodes = 32, kConvCoefs = 64;
+
+// One slab j_1 in [j0, j0 + jn) of a field component.
+struct ConvMap {
+  int32_t d, MP, nc;    // dimension, data per dimension, coefficients per node
+  int32_t K2, K3;       // host nodes in j_2, j_3 (1 beyond d)
+  int32_t E0, E1;       // device extents
+  int32_t off, o2, o3;  // device index of host node j: j + off per dimension
+  int32_t j0, jn, tiles;
+  int32_t plane0;       // first plane of the component
+};
+
+template <class S, bool TO_PLANES>
+__global__ void __launch_bounds__(256) convert_layout(typename S::View v, double* __restrict__ host, ConvMap m) {
+  __shared__ double tile[kConvNodes * (kConvCoefs + 1)];
+  const int t1 = blockIdx.x % m.tiles, r = blockIdx.x / m.tiles;  // tile along j_1, host node j_2 K3 + j_3
+  const int j2 = r / m.K3, j3 = r % m.K3;
+  const int c0 = blockIdx.y * kConvCoefs, cw = min(kConvCoefs, m.nc - c0);
+  const int base = t1 * kConvNodes, cnt = min(kConvNodes, m.jn - base);
+  const int64_t rows = (int64_t)m.K2 * m.K3;
+  const uint32_t row = (uint32_t)(m.j0 + base + m.off) +
+                       (uint32_t)m.E0 * ((uint32_t)(j2 + m.o2) + (uint32_t)m.E1 * (uint32_t)(j3 + m.o3));
+  auto plane = [&](int h) {  // host coefficient index (a_1 slowest) -> plane (a_1 fastest)
+    int a[3] = {0, 0, 0};
+    for (int k = m.d - 1; k >= 0; --k) {
+      a[k] = h % m.MP;
+      h /= m.MP;
+    }
+    return m.plane0 + a[0] + m.MP * (a[1] + m.MP * a[2]);
+  };
+  auto host_at = [&](int i, int c) -> double& { return host[((int64_t)(base + i) * rows + r) * m.nc + c0 + c]; };
+  if (TO_PLANES) {
+    for (int x = threadIdx.x; x < cnt * cw; x += 256) tile[x / cw * (kConvCoefs + 1) + x % cw] = host_at(x / cw, x % cw);
+    __syncthreads();
+    for (int x = threadIdx.x; x < kConvNodes * cw; x += 256) {
+      const int i = x % kConvNodes, c = x / kConvNodes;
+      if (i < cnt) S::store(v, plane(c0 + c), row + i, (typename S::C)tile[i * (kConvCoefs + 1) + c]);
+    }
+  } else {
+    for (int x = threadIdx.x; x < kConvNodes * cw; x += 256) {
+      const int i = x % kConvNodes, c = x / kConvNodes;
+      if (i < cnt) tile[i * (kConvCoefs + 1) + c] = (double)S::load(v, plane(c0 + c), row + i);
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < cnt * cw; x += 256) host_at(x / cw, x % cw) = tile[x / cw * (kConvCoefs + 1) + x % cw];
+  }
+}
+
+// *bad = 1 if any of n words is not finite.
+__global__ void check_finite(const double* __restrict__ x, int64_t n, int* __restrict__ bad) {
+  bool b = false;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    b = b || !(fabs(x[i]) <= 1.7976931348623157e308);
+  if (b) *bad = 1;
+}
+
+// A staging buffer of at least `bytes`: the plan's own up to kStageKeep (kept
+// until the plan is destroyed), a temporary one beyond.  NULL: no memory.
+constexpr size_t kStageKeep = (size_t)64 << 20;   // kept with the plan
+constexpr size_t kStageMost = (size_t)256 << 20;  // per call; larger components go slab by slab
+struct Staging {
+  void* ptr = nullptr;
+  bool own = false;
+  Staging(hl_plan_s* pl, size_t bytes) {
+    if (bytes > kStageKeep) {
+      own = hipMalloc(&ptr, bytes) == hipSuccess;
+      if (!own) ptr = nullptr;
+    } else {
+      if (pl->stage_bytes < bytes) {
+        if (pl->stage) (void)hipFree(pl->stage);
+        pl->stage = nullptr;
+        pl->stage_bytes = 0;
+        if (hipMalloc(&pl->stage, bytes) == hipSuccess)
+          pl->stage_bytes = bytes;
+        else
+          pl->stage = nullptr;
+      }
+      ptr = pl->stage;
+    }
+    if (!ptr) (void)hipGetLastError();
+  }
+  ~Staging() {
+    if (own) (void)hipFree(ptr);
+  }
+  Staging(const Staging&) = delete;
+  Staging& operator=(const Staging&) = delete;
+};
+
+template <bool TO_PLANES>
+hipError_t launch_convert(int precision, void* dev, int ncomp, const LayoutMap& L, ConvMap m, double* stage,
+                          hipStream_t s) {
+  m.tiles = (m.jn + kConvNodes - 1) / kConvNodes;
+  const dim3 grid((unsigned)((int64_t)m.tiles * m.K2 * m.K3), (unsigned)((m.nc + kConvCoefs - 1) / kConvCoefs));
+  const auto go = [&](auto tag) {
+    using S = decltype(tag);
+    hipLaunchKernelGGL((convert_layout<S, TO_PLANES>), grid, dim3(256), 0, s, S::make(dev, ncomp, L.nc, L.nodes), stage,
+                       m);
+  };
+  if (precision == HL_FP64)
+    go(hl::PlainStore<double>{});
+  else if (precision == HL_FP32)
+    go(hl::PlainStore<float>{});
+  else
+    go(hl::SplitStore{});
+  return hipGetLastError();
+}
+
+// The slabs of one component: words per j_1 and j_1 per staged slab (0: even
+// one j_1 is too large for the staging buffer or the launch).
+struct Slabs {
+  int64_t per, jn;
+};
+Slabs slabs_of(const LayoutMap& L) {
+  const int64_t rows = (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
+  Slabs q{rows * L.nc, std::min<int64_t>(L.K[0], (int64_t)(kStageMost / 8) / (rows * L.nc))};
+  if (rows > (int64_t)INT32_MAX / 64) q.jn = 0;
+  while (q.jn > 0 && (q.jn + kConvNodes - 1) / kConvNodes * rows > (int64_t)INT32_MAX) q.jn /= 2;
+  return q;
+}
+ConvMap conv_map(const LayoutMap& L, int comp) {
+  ConvMap m{};
+  m.d = L.d;
+  m.MP = L.MP;
+  m.nc = L.nc;
+  m.K2 = (int32_t)(L.d > 1 ? L.K[1] : 1);
+  m.K3 = (int32_t)(L.d > 2 ? L.K[2] : 1);
+  m.E0 = (int32_t)L.E[0];
+  m.E1 = (int32_t)(L.d > 1 ? L.E[1] : 1);
+  m.off = (int32_t)L.off;
+  m.o2 = (int32_t)(L.d > 1 ? L.off : 0);
+  m.o3 = (int32_t)(L.d > 2 ? L.off : 0);
+  m.plane0 = comp * L.nc;
+  return m;
+}
+
+// Component `comp` of `ncomp` between host (host layout) and the planes at
+// dev, through the staging buffer; hipErrorOutOfMemory when there is none (the
+// caller converts on the host instead).
+template <bool TO_PLANES>
+hipError_t convert_component(hl_plan_s* pl, int precision, void* dev, int ncomp, int comp, const LayoutMap& L,
+                             double* host, hipStream_t s) {
+  const Slabs q = slabs_of(L);
+  if (q.jn < 1) return hipErrorOutOfMemory;
+  Staging st(pl, (size_t)(q.per * q.jn) * 8);
+  if (!st.ptr) return hipErrorOutOfMemory;
+  ConvMap m = conv_map(L, comp);
+  hipError_t e = hipSuccess;
+  for (int64_t j0 = 0; j0 < L.K[0] && e == hipSuccess; j0 += q.jn) {
+    m.j0 = (int32_t)j0;
+    m.jn = (int32_t)std::min<int64_t>(q.jn, L.K[0] - j0);
+    const size_t bytes = (size_t)(q.per * m.jn) * 8;
+    if (TO_PLANES) e = hipMemcpyAsync(st.ptr, host + j0 * q.per, bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_convert<TO_PLANES>(precision, dev, ncomp, L, m, (double*)st.ptr, s);
+    if (!TO_PLANES && e == hipSuccess) e = hipMemcpyAsync(host + j0 * q.per, st.ptr, bytes, hipMemcpyDeviceToHost, s);
+  }
+  const hipError_t e2 = hipStreamSynchronize(s);  // also before the staging buffer is given back
+  return e == hipSuccess ? e2 : e;
+}
+
 // field 0: p (one component), field 1: u (d components).
-hl_status upload_field(const hl_plan_s* pl, const double* host, int field, void* dev, hipStream_t s) {
+hl_status upload_field(hl_plan_s* pl, const double* host, int field, void* dev, hipStream_t s) {
   const int ncomp = field == 0 ? 1 : pl->d;
   const LayoutMap L = layout_of(pl, field);
   const int64_t hw = (int64_t)pl->nc * L.K[0] * L.K[1] * L.K[2];  // host words per component
   FieldImage im{pl->precision, (int64_t)pl->nc * L.nodes, {}, {}};
-  if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_init: host staging allocation failed");
   unsigned char* d = static_cast<unsigned char*>(dev);
+  hipError_t e = hipSuccess;
+  // ghost nodes (walls) start at zero; the library refreshes them before use
+  if (!host || (pl->walls && field == 1)) {
+    e = hipMemsetAsync(dev, 0, ncomp * (im.hi_bytes() + im.lo_bytes()), s);
+    if (e != hipSuccess) return hip_fail(e, "hl_init: clear");
+    if (!host) {
+      e = hipStreamSynchronize(s);
+      return e == hipSuccess ? HL_OK : hip_fail(e, "hl_init: clear");
+    }
+  }
   for (int i = 0; i < ncomp; ++i) {
-    const double* src = host ? host + (size_t)i * hw : nullptr;
-    // ghost nodes (walls) start at zero; the library refreshes them before use
-    std::fill(im.hi.begin(), im.hi.end(), (unsigned char)0);
-    std::fill(im.lo.begin(), im.lo.end(), (unsigned char)0);
-    if (src) L.for_each([&](int64_t h, int64_t dv) { im.put(dv, src[h]); });
-    hipError_t e = hipMemcpyAsync(d + i * im.hi_bytes(), im.hi.data(), im.hi_bytes(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && im.lo_bytes())
-      e = hipMemcpyAsync(d + ncomp * im.hi_bytes() + i * im.lo_bytes(), im.lo.data(), im.lo_bytes(),
-                         hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const double* src = host + (size_t)i * hw;
+    e = convert_component<true>(pl, pl->precision, dev, ncomp, i, L, const_cast<double*>(src), s);
+    if (e == hipErrorOutOfMemory) {  // no staging memory: on host threads
+      if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_init: host staging allocation failed");
+      std::fill(im.hi.begin(), im.hi.end(), (unsigned char)0);
+      std::fill(im.lo.begin(), im.lo.end(), (unsigned char)0);
+      L.for_each([&](int64_t h, int64_t dv) { im.put(dv, src[h]); });
+      e = hipMemcpyAsync(d + i * im.hi_bytes(), im.hi.data(), im.hi_bytes(), hipMemcpyHostToDevice, s);
+      if (e == hipSuccess && im.lo_bytes())
+        e = hipMemcpyAsync(d + ncomp * im.hi_bytes() + i * im.lo_bytes(), im.lo.data(), im.lo_bytes(),
+                           hipMemcpyHostToDevice, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
     if (e != hipSuccess) return hip_fail(e, "hl_init: copy to device");
   }
   return HL_OK;
 }
 
-hl_status download_field(const hl_plan_s* pl, const void* dev, int field, double* host, hipStream_t s) {
+hl_status download_field(hl_plan_s* pl, const void* dev, int field, double* host, hipStream_t s) {
   const int ncomp = field == 0 ? 1 : pl->d;
   const LayoutMap L = layout_of(pl, field);
   const int64_t hw = (int64_t)pl->nc * L.K[0] * L.K[1] * L.K[2];
   FieldImage im{pl->precision, (int64_t)pl->nc * L.nodes, {}, {}};
-  if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_export: host staging allocation failed");
   const unsigned char* d = static_cast<const unsigned char*>(dev);
   for (int i = 0; i < ncomp; ++i) {
-    hipError_t e = hipMemcpyAsync(im.hi.data(), d + i * im.hi_bytes(), im.hi_bytes(), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && im.lo_bytes())
-      e = hipMemcpyAsync(im.lo.data(), d + ncomp * im.hi_bytes() + i * im.lo_bytes(), im.lo_bytes(),
-                         hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "hl_export: copy to host");
     double* dst = host + (size_t)i * hw;
-    L.for_each([&](int64_t h, int64_t dv) { dst[h] = im.get(dv); });
+    hipError_t e = convert_component<false>(pl, pl->precision, const_cast<void*>(dev), ncomp, i, L, dst, s);
+    if (e == hipErrorOutOfMemory) {  // no staging memory: on host threads
+      if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_export: host staging allocation failed");
+      e = hipMemcpyAsync(im.hi.data(), d + i * im.hi_bytes(), im.hi_bytes(), hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess && im.lo_bytes())
+        e = hipMemcpyAsync(im.lo.data(), d + ncomp * im.hi_bytes() + i * im.lo_bytes(), im.lo_bytes(),
+                           hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      if (e == hipSuccess) L.for_each([&](int64_t h, int64_t dv) { dst[h] = im.get(dv); });
+    }
+    if (e != hipSuccess) return hip_fail(e, "hl_export: copy to host");
   }
   return HL_OK;
 }
@@ -1116,7 +1301,7 @@ hl_status hl_plan_destroy(hl_plan_t plan) {
   if (plan->dadj) (void)hipFree(plan->dadj);
   for (void* q : {plan->dkap_p, plan->dkap_u, plan->tab_dk, plan->tab_rev, plan->fp, plan->fu, plan->sp, plan->su,
                   (void*)plan->gpart, (void*)plan->gkp, (void*)plan->gku, plan->vscr, plan->wscr, plan->vzw,
-                  plan->ucw})
+                  plan->ucw, plan->stage})
     if (q) (void)hipFree(q);
   if (plan->dpartial) (void)hipFree(plan->dpartial);
   delete plan;
@@ -1279,25 +1464,68 @@ hl_status hl_set_kappa(hl_plan_t plan, const double* kappa_p, const double* kapp
   // entries the kernels never read)
   const double* srcs[2] = {kappa_p, kappa_u};
   void** dsts[2] = {&plan->dkap_p, &plan->dkap_u};
+  LayoutMap Ls[2];
+  size_t words[2];
   for (int f = 0; f < 2; ++f) {
-    const LayoutMap L = hl_host::field_layout(plan->d, 2 * plan->m + 1, plan->K, plan->walls, f);
-    const int64_t hw = (int64_t)L.nc * L.K[0] * L.K[1] * L.K[2];
-    for (int64_t i = 0; i < hw; ++i)
-      if (!std::isfinite(srcs[f][i])) return fail(HL_ERR_ARG, "hl_set_kappa: kappa data must be finite");
+    Ls[f] = hl_host::field_layout(plan->d, 2 * plan->m + 1, plan->K, plan->walls, f);
+    words[f] = (size_t)Ls[f].nc * Ls[f].K[0] * Ls[f].K[1] * Ls[f].K[2];
+  }
+  // Both arrays are checked before either is converted: on the device where
+  // the staging buffer holds both, else on the host.
+  const bool both = (words[0] + words[1]) * 8 + 8 <= kStageMost && slabs_of(Ls[0]).jn == Ls[0].K[0] &&
+                    slabs_of(Ls[1]).jn == Ls[1].K[0];
+  Staging buf(plan, both ? (words[0] + words[1]) * 8 + 8 : 0);
+  double* staged = static_cast<double*>(buf.ptr);
+  if (!both) staged = nullptr;
+  if (staged) {
+    int* flag = reinterpret_cast<int*>(staged + words[0] + words[1]);
+    int bad = 0;
+    e = hipMemcpy(staged, kappa_p, words[0] * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(staged + words[0], kappa_u, words[1] * 8, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(flag, &bad, sizeof bad, hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+      const int64_t n = (int64_t)(words[0] + words[1]);
+      hipLaunchKernelGGL(check_finite, dim3((unsigned)std::min<int64_t>(1024, (n + 255) / 256)), dim3(256), 0, 0,
+                         (const double*)staged, n, flag);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpy(&bad, flag, sizeof bad, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "hl_set_kappa: copy to device");
+    if (bad) return fail(HL_ERR_ARG, "hl_set_kappa: kappa data must be finite");
+  } else {
+    for (int f = 0; f < 2; ++f)
+      for (size_t i = 0; i < words[f]; ++i)
+        if (!std::isfinite(srcs[f][i])) return fail(HL_ERR_ARG, "hl_set_kappa: kappa data must be finite");
   }
   for (int f = 0; f < 2; ++f) {
-    const LayoutMap L = hl_host::field_layout(plan->d, 2 * plan->m + 1, plan->K, plan->walls, f);
+    const LayoutMap& L = Ls[f];
     FieldImage im{plan->precision, (int64_t)L.nc * L.nodes, {}, {}};
-    if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_set_kappa: host staging allocation failed");
     // the kappa data in the plan's storage (FP32_COMP: hi planes, then lo planes)
-    if (!*dsts[f] && (e = hipMalloc(dsts[f], im.hi_bytes() + im.lo_bytes())) != hipSuccess)
-      return fail(HL_ERR_NOMEM, std::string("hl_set_kappa: device allocation: ") + hipGetErrorString(e));
-    L.for_each([&](int64_t h, int64_t dv) { im.put(dv, srcs[f][h]); });
-    e = hipMemcpy(*dsts[f], im.hi.data(), im.hi_bytes(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && im.lo_bytes())
-      e = hipMemcpy(static_cast<char*>(*dsts[f]) + im.hi_bytes(), im.lo.data(), im.lo_bytes(), hipMemcpyHostToDevice);
+    if (!*dsts[f]) {
+      if ((e = hipMalloc(dsts[f], im.hi_bytes() + im.lo_bytes())) != hipSuccess)
+        return fail(HL_ERR_NOMEM, std::string("hl_set_kappa: device allocation: ") + hipGetErrorString(e));
+      if (plan->walls && f == 1) e = hipMemset(*dsts[f], 0, im.hi_bytes() + im.lo_bytes());  // ghost entries, never read
+    }
+    if (e == hipSuccess && staged) {
+      ConvMap m = conv_map(L, 0);
+      m.j0 = 0;
+      m.jn = (int32_t)L.K[0];
+      e = launch_convert<true>(plan->precision, *dsts[f], 1, L, m, staged + (f ? words[0] : 0), 0);
+    } else if (e == hipSuccess) {
+      e = convert_component<true>(plan, plan->precision, *dsts[f], 1, 0, L, const_cast<double*>(srcs[f]), 0);
+      if (e == hipErrorOutOfMemory) {  // no staging memory: on host threads
+        if (!im.alloc()) return fail(HL_ERR_NOMEM, "hl_set_kappa: host staging allocation failed");
+        L.for_each([&](int64_t h, int64_t dv) { im.put(dv, srcs[f][h]); });
+        e = hipMemcpy(*dsts[f], im.hi.data(), im.hi_bytes(), hipMemcpyHostToDevice);
+        if (e == hipSuccess && im.lo_bytes())
+          e = hipMemcpy(static_cast<char*>(*dsts[f]) + im.hi_bytes(), im.lo.data(), im.lo_bytes(),
+                        hipMemcpyHostToDevice);
+      }
+    }
     if (e != hipSuccess) return hip_fail(e, "hl_set_kappa: copy to device");
   }
+  e = hipDeviceSynchronize();  // the staging buffer is read until here
+  if (e != hipSuccess) return hip_fail(e, "hl_set_kappa: copy to device");
   plan->var_kappa = true;
   return HL_OK;
 }
@@ -1611,10 +1839,13 @@ hl_status hl_kappa_grad(hl_plan_t plan, double* grad_p, double* grad_u, int rese
     // hl_set_kappa's layout (with walls: K+1 primal nodes, dual nodes in the padded array)
     const LayoutMap L = hl_host::field_layout(plan->d, 2 * plan->m + 1, plan->K, plan->walls, f);
     if (host[f]) {
-      std::vector<double> img((size_t)(np * nodes[f]));
-      e = hipMemcpy(img.data(), dev[f], img.size() * sizeof(double), hipMemcpyDeviceToHost);
+      e = convert_component<false>(plan, HL_FP64, dev[f], 1, 0, L, host[f], 0);
+      if (e == hipErrorOutOfMemory) {  // no staging memory: on host threads
+        std::vector<double> img((size_t)(np * nodes[f]));
+        e = hipMemcpy(img.data(), dev[f], img.size() * sizeof(double), hipMemcpyDeviceToHost);
+        if (e == hipSuccess) L.for_each([&](int64_t h, int64_t dv) { host[f][h] = img[(size_t)dv]; });
+      }
       if (e != hipSuccess) return hip_fail(e, "hl_kappa_grad: copy to host");
-      L.for_each([&](int64_t h, int64_t dv) { host[f][h] = img[(size_t)dv]; });
     }
     if (reset && (e = hipMemset(dev[f], 0, (size_t)(np * nodes[f]) * sizeof(double))) != hipSuccess)
       return hip_fail(e, "hl_kappa_grad: reset");
