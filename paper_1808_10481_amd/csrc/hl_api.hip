@@ -202,6 +202,14 @@ struct hl_plan_s {
   // is launched on the caller's stream.
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
+  // 1D: the other buffers of multi-step launches over several workgroups, the
+  // stream that used them last and its event (a call on another stream waits
+  // for it)
+  void* alt_p = nullptr;
+  void* alt_u = nullptr;
+  hipEvent_t alt_done = nullptr;
+  hipStream_t alt_stream = nullptr;
+  bool alt_used = false;
   const void* graph_p = nullptr;  // buffers the graph was captured for
   const void* graph_u = nullptr;
   // bumped by every call that changes what a batch descriptor bakes in
@@ -238,6 +246,9 @@ struct hl_batch_s {
 };
 
 namespace {
+
+// Bytes per stored coefficient (FP32_COMP: an FP32 hi word and a BF16 lo word).
+size_t state_bytes(const hl_plan_s* pl) { return (size_t)pl->word_bytes * pl->words_per_coef; }
 
 constexpr int kNormBlocks = 256;
 constexpr int64_t kGraphChunk = 16;   // steps per captured graph (32 kernel nodes)
@@ -296,6 +307,35 @@ hipError_t capture_steps(hl_plan_s* pl, const hl::PlanView& v, void* p, void* u)
     pl->gexec = nullptr;
   }
   return e;
+}
+
+// 1D, constant kappa: all steps in a few launches; *done = false where the
+// steps have to be launched one by one (several workgroups and few steps, no
+// second buffers, or a stream under capture, whose replays the plan could not
+// order against other uses of those buffers).
+hl_status steps_1d(hl_plan_s* pl, const hl::PlanView& v, void* p, void* u, int64_t nsteps, hipStream_t s, bool* done) {
+  *done = false;
+  const bool whole = pl->pnodes <= pl->ks.whole;
+  hipError_t e = hipSuccess;
+  if (!whole) {
+    if (nsteps < 4 || !pl->alt_done) return HL_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return HL_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return HL_OK;
+    if (pl->alt_used && pl->alt_stream != s) e = hipStreamWaitEvent(s, pl->alt_done, 0);
+  }
+  if (e == hipSuccess) e = pl->ks.steps(v, pl->K[0], pl->walls, p, u, pl->alt_p, pl->alt_u, nsteps, s);
+  if (!whole && e == hipSuccess) {
+    e = hipEventRecord(pl->alt_done, s);
+    pl->alt_stream = s;
+    pl->alt_used = true;
+  }
+  if (e != hipSuccess) return hip_fail(e, "hl_step: launch");
+  *done = true;
+  return HL_OK;
 }
 
 int max_m(int d) { return d == 1 ? 7 : (d == 2 ? 5 : 3); }
@@ -922,9 +962,6 @@ __global__ void add_partials(const double* __restrict__ partial, int n, double* 
 }
 
 // *acc += <a, b> for two p-shaped (field 0) or u-shaped (field 1) buffers.
-// Bytes per stored coefficient (FP32_COMP: an FP32 hi word and a BF16 lo word).
-size_t state_bytes(const hl_plan_s* pl) { return (size_t)pl->word_bytes * pl->words_per_coef; }
-
 hipError_t dot_into(const hl_plan_s* pl, const void* a, const void* b, int field, double* acc, hipStream_t s) {
   const int planes = (field == 0 ? 1 : pl->d) * pl->nc;
   const int64_t nodes = field == 0 ? pl->pnodes : pl->unodes;
@@ -1288,6 +1325,22 @@ hl_status hl_plan(const hl_problem* prob, hl_plan_t* out) {
       return hip_fail(e, "hl_plan: adjoint table upload");
     }
   }
+  // 1D grids of several workgroups: the multi-step launches' other buffers, for
+  // states up to 64 MB (larger ones are not launch-bound); without them every
+  // step is two launches
+  const size_t state = (size_t)pl->nc * (pl->pnodes + pl->unodes) * state_bytes(pl);
+  if (pl->ks.steps && pl->pnodes > pl->ks.whole && state <= (size_t)64 << 20) {
+    e = hipMalloc(&pl->alt_p, (size_t)pl->nc * pl->pnodes * state_bytes(pl));
+    if (e == hipSuccess) e = hipMalloc(&pl->alt_u, (size_t)pl->nc * pl->unodes * state_bytes(pl));
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->alt_done, hipEventDisableTiming);
+    if (e != hipSuccess) {
+      for (void** q : {&pl->alt_p, &pl->alt_u}) {
+        if (*q) (void)hipFree(*q);
+        *q = nullptr;
+      }
+      (void)hipGetLastError();
+    }
+  }
   *out = pl;
   return HL_OK;
 }
@@ -1301,8 +1354,9 @@ hl_status hl_plan_destroy(hl_plan_t plan) {
   if (plan->dadj) (void)hipFree(plan->dadj);
   for (void* q : {plan->dkap_p, plan->dkap_u, plan->tab_dk, plan->tab_rev, plan->fp, plan->fu, plan->sp, plan->su,
                   (void*)plan->gpart, (void*)plan->gkp, (void*)plan->gku, plan->vscr, plan->wscr, plan->vzw,
-                  plan->ucw, plan->stage})
+                  plan->ucw, plan->stage, plan->alt_p, plan->alt_u})
     if (q) (void)hipFree(q);
+  if (plan->alt_done) (void)hipEventDestroy(plan->alt_done);
   if (plan->dpartial) (void)hipFree(plan->dpartial);
   delete plan;
   return HL_OK;
@@ -1388,6 +1442,11 @@ hl_status hl_step(hl_plan_t plan, void* p, void* u, int64_t nsteps, void* stream
   const hl::PlanView v = view(plan);
   hipStream_t s = (hipStream_t)stream;
   int64_t n = 0;
+  if (plan->ks.steps && !plan->var_kappa && nsteps > 0) {
+    bool done = false;
+    st = steps_1d(plan, v, p, u, nsteps, s, &done);
+    if (st != HL_OK || done) return st;
+  }
   if (nsteps >= kGraphChunk) {
     if (!plan->gexec || plan->graph_p != p || plan->graph_u != u) {
       hipError_t e = capture_steps(plan, v, p, u);

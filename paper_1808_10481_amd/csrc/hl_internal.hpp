@@ -28,6 +28,11 @@ struct PlanView {
 
 typedef hipError_t (*PHalfFn)(const PlanView&, void* p, const void* u, hipStream_t);
 typedef hipError_t (*UHalfFn)(const PlanView&, void* u, const void* p, double wscale, hipStream_t);
+// 1D, constant kappa: n steps on (p, u) with a few launches; sp, su: scratch
+// shaped like p and u, not used where one workgroup holds the grid
+// (KernelSet::whole nodes at most).
+typedef hipError_t (*StepsFn)(const PlanView&, int32_t K, bool walls, void* p, void* u, void* sp, void* su, int64_t n,
+                              hipStream_t);
 typedef hipError_t (*GhostFn)(const PlanView&, void* u, hipStream_t);
 // Transposed half-steps: pb -= B^T ub (AdjFn p), ub -= A^T pb (AdjFn u).
 typedef hipError_t (*AdjFn)(const PlanView&, void* out, const void* in, hipStream_t);
@@ -61,6 +66,8 @@ typedef hipError_t (*BatchSrcFn)(const void* pbase, const void* ent, const void*
 struct KernelSet {
   PHalfFn p_half;
   UHalfFn u_half;
+  StepsFn steps;         // 1D FP64 and FP32, NULL otherwise
+  int whole;             // 1D: nodes one workgroup holds
   GhostFn ghost;         // ghost-shell refresh of a wall-bounded velocity array
   AdjFn adj_p, adj_u;    // transposed half-steps, NULL where not built
   AdjWallFn adj_u_walls; // walls: ub -= G^T A^T pb, NULL where not built
@@ -195,6 +202,53 @@ hipError_t launch_u(const PlanView& pv, void* u, const void* p, double wscale, h
   } else
     hipLaunchKernelGGL((u_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vu, vp, (const T*)pv.tab,
                        g, (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
+  return hipGetLastError();
+}
+
+// Nodes one workgroup holds: a node each, in 64 KB of LDS.
+template <int M, class S>
+constexpr int kWhole1 = kSteps1Whole < 65536 / (int)(2 * (M + 1) * sizeof(typename S::C))
+                            ? kSteps1Whole
+                            : 65536 / (int)(2 * (M + 1) * sizeof(typename S::C));
+
+// The grid in one workgroup: one launch in place.  Otherwise an even number of
+// launches, (p, u) -> scratch -> (p, u) -> .., of nearly equal step counts.
+template <int M, class S>
+hipError_t launch_steps_1d(const PlanView& pv, int32_t K, bool walls, void* p, void* u, void* sp, void* su, int64_t n,
+                           hipStream_t s) {
+  using T = typename S::C;
+  constexpr int MP = M + 1;
+  const int64_t np = pv.gp.onodes, nu = pv.gu.onodes;
+  const int nodes = walls ? K + 1 : K;
+  const typename S::View vp = S::make(p, 1, MP, np), vu = S::make(u, 1, MP, nu);
+  Steps1 a{};
+  a.K = K;
+  a.walls = walls;
+  a.whole = nodes <= kWhole1<M, S>;
+  if (a.whole) {
+    a.own = a.n = nodes;
+    a.last = 1;
+    for (int64_t done = 0; done < n; done += a.steps) {
+      a.steps = (int32_t)(n - done < (1 << 16) ? n - done : 1 << 16);
+      hipLaunchKernelGGL((steps_1d<M, S>), dim3(1), dim3((unsigned)((a.n + 63) / 64 * 64)),
+                         (size_t)2 * MP * a.n * sizeof(T), s, vp, vu, vp, vu, (const T*)pv.tab, a, (T)pv.ih[0]);
+    }
+    return hipGetLastError();
+  }
+  const typename S::View wp = S::make(sp, 1, MP, np), wu = S::make(su, 1, MP, nu);
+  const int64_t launches = 2 * ((n + 2 * kSteps1Halo - 1) / (2 * kSteps1Halo));
+  a.own = kSteps1Own;
+  const unsigned blocks = (unsigned)((nodes + a.own - 1) / a.own);
+  for (int64_t k = 0; k < launches; ++k) {
+    a.steps = (int32_t)(n * (k + 1) / launches - n * k / launches);
+    a.halo = a.steps;
+    a.n = a.own + 2 * a.halo;
+    a.last = k + 1 == launches;
+    const bool back = k & 1;
+    hipLaunchKernelGGL((steps_1d<M, S>), dim3(blocks), dim3((unsigned)((a.n + 63) / 64 * 64)),
+                       (size_t)2 * MP * a.n * sizeof(T), s, back ? wp : vp, back ? wu : vu, back ? vp : wp,
+                       back ? vu : wu, (const T*)pv.tab, a, (T)pv.ih[0]);
+  }
   return hipGetLastError();
 }
 
@@ -508,6 +562,12 @@ inline bool make_set(KernelSet* out) {
   fill_layout<D, M>(out);
   out->p_half = &launch_p<D, M, S>;
   out->u_half = &launch_u<D, M, S>;
+  out->steps = nullptr;
+  out->whole = 0;
+  if constexpr (D == 1 && kPlain<S>) {
+    out->steps = &launch_steps_1d<M, S>;
+    out->whole = kWhole1<M, S>;
+  }
   out->ghost = &launch_ghost<D, M, S>;
   out->adj_p = nullptr;
   out->adj_u = nullptr;

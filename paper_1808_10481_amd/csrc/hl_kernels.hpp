@@ -421,6 +421,135 @@ __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_kernel(typename S
 }
 
 // ---------------------------------------------------------------------------
+// 1D: several steps per launch.  A 1D half-step is a few multiply-adds per
+// node, so stepping by two launches is launch latency (1.8 us each, whatever
+// the grid below about 10^5 nodes).  Here a workgroup holds a stretch of nodes
+// of both fields in LDS and runs all of a launch's steps on it: the whole grid
+// in one workgroup (whole), or B owned nodes plus a halo of `steps` nodes on
+// either side, of which each step makes one more node per side invalid (the
+// pressure half-step reads the dual node to the left, the velocity half-step
+// the primal node to the right).  Halo nodes are computed by the same
+// arithmetic from the same data as their owner computes them, so every result
+// equals stepping launch by launch bit for bit (FP64 and FP32 words; an
+// FP32_COMP value may have two hi + lo encodings, and LDS would not keep which).
+// With a halo, neighbours still read the
+// old state while a workgroup writes, so the result goes to other buffers than
+// the source.  200 cells, m = 1, FP64: 3.7 -> 0.25 us per step.
+// ---------------------------------------------------------------------------
+constexpr int kSteps1Whole = 768;  // one workgroup up to this many nodes
+constexpr int kSteps1Own = 256;    // nodes owned by a workgroup otherwise ..
+constexpr int kSteps1Halo = 32;    // .. and the most steps of such a launch
+struct Steps1 {
+  int32_t K;      // cells
+  int32_t walls;  // reflecting walls: primal 0 .. K, dual 0 .. K - 1 at index q + 1 of a padded array
+  int32_t whole;  // the grid in one workgroup
+  int32_t own, halo, n;  // owned nodes, halo, local nodes (own + 2 halo)
+  int32_t steps;
+  int32_t last;   // the launch that leaves the final state: ghosts as the last step's refresh left them
+};
+
+template <int M, class S>
+__global__ void __launch_bounds__(1024) steps_1d(typename S::View ps, typename S::View us, typename S::View pd,
+                                                 typename S::View ud, const typename S::C* __restrict__ tab, Steps1 a,
+                                                 typename S::C ih0) {
+  using T = typename S::C;
+  using TL = TableLayout<1, M>;
+  constexpr int MP = M + 1, NG = GSet<1, M>::NG;
+  extern __shared__ __align__(16) char steps1_lds[];
+  T* P = reinterpret_cast<T*>(steps1_lds);  // [c][local node]
+  T* U = P + MP * a.n;
+  const int np = a.walls ? a.K + 1 : a.K, off = a.walls ? 1 : 0;  // primal nodes; dual node q at index q + off
+  const int first = (int)blockIdx.x * a.own;                      // first owned node
+  // global node of local node i on the primal / dual grid, -1 where there is none
+  auto node = [&](int i, int count) -> int {
+    int g = first - a.halo + i;
+    if (!a.walls) {
+      g %= a.K;
+      return g < 0 ? g + a.K : g;
+    }
+    return g >= 0 && g < count ? g : -1;
+  };
+  for (int i = threadIdx.x; i < a.n; i += blockDim.x) {
+    const int j = node(i, np), q = node(i, a.K);
+#pragma unroll
+    for (int c = 0; c < MP; ++c) {
+      P[c * a.n + i] = j < 0 ? T(0) : S::load(ps, c, (uint32_t)j);
+      U[c * a.n + i] = q < 0 ? T(0) : S::load(us, c, (uint32_t)(q + off));
+    }
+  }
+  __syncthreads();
+  // a dual node beyond a wall is the mirror of the node inside (normal
+  // component even: (-1)^c)
+  auto mirrored = [](int c, T x) { return (c & 1) ? -x : x; };
+  for (int t = 0; t < a.steps; ++t) {
+    if (a.walls && a.last && t + 1 == a.steps) {  // the ghosts of the last refresh
+      for (int i = threadIdx.x; i < a.n; i += blockDim.x) {
+        const int q = first - a.halo + i;
+        if (i < a.halo || i >= a.halo + a.own) continue;
+#pragma unroll
+        for (int c = 0; c < MP; ++c) {
+          if (q == 0) S::store(ud, c, 0u, mirrored(c, U[c * a.n + i]));
+          if (q == a.K - 1) S::store(ud, c, (uint32_t)(a.K + 1), mirrored(c, U[c * a.n + i]));
+        }
+      }
+    }
+    for (int i = threadIdx.x; i < a.n; i += blockDim.x) {
+      const int g = first - a.halo + i;
+      int lo = i - 1, hi = i;
+      bool mlo = false, mhi = false;
+      if (a.walls) {
+        if (g == 0) lo = i, mlo = true;         // ghost dual -1 mirrors dual 0
+        if (g == a.K) hi = i - 1, mhi = true;   // ghost dual K mirrors dual K - 1
+      } else if (a.whole && i == 0) {
+        lo = a.n - 1;
+      }
+      lo = max(lo, 0);
+      hi = max(hi, 0);
+      T acc[MP];
+#pragma unroll
+      for (int s = 0; s < MP; ++s) acc[s] = T(0);
+#pragma unroll
+      for (int l = 0; l < MP; ++l) {
+        const T ul = U[l * a.n + lo], ur = U[l * a.n + hi];
+        const T YL = mlo ? mirrored(l, ul) : ul, YR = mhi ? mirrored(l, ur) : ur;
+        const T Sg[1] = {YR + YL}, Df[1] = {YR - YL};
+        merge<1, M, false, 1>(tab + TL::P_B_OFF + l * merged_nnz<1, M>(false), l, Sg, Df, acc);
+      }
+#pragma unroll
+      for (int s = 0; s < MP; ++s) P[s * a.n + i] = P[s * a.n + i] - acc[s];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < a.n; i += blockDim.x) {
+      const int hi = i + 1 < a.n ? i + 1 : (a.whole && !a.walls ? 0 : i);
+      T Q[NG];
+#pragma unroll
+      for (int o = 0; o < NG; ++o) Q[o] = T(0);
+#pragma unroll
+      for (int l = 0; l < MP; ++l) {
+        const T YL = P[l * a.n + i], YR = P[l * a.n + hi];
+        const T Sg[1] = {YR + YL}, Df[1] = {YR - YL};
+        merge<1, M, true, 0>(tab + TL::U_OFF + l * merged_nnz<1, M>(true), l, Sg, Df, Q);
+      }
+      const T f = T(1) * ih0;
+#pragma unroll
+      for (int s = 0; s < MP; ++s) {
+        const T w = -(T)(s + 1) * f;
+        U[s * a.n + i] = fma(w, Q[kGIndex<1, M>.g[0][s]], U[s * a.n + i]);
+      }
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < a.own; i += blockDim.x) {
+    const int g = first + i, k = a.halo + i;
+#pragma unroll
+    for (int c = 0; c < MP; ++c) {
+      if (g < np) S::store(pd, c, (uint32_t)g, P[c * a.n + k]);
+      if (g < a.K) S::store(ud, c, (uint32_t)(g + off), U[c * a.n + k]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // 3D kernels.  Interpolation in x, y and z, the Cauchy-Kowalevsky weights and
 // the divergence are all in one runtime table (hl_layout.hpp TableLayout<3, M>):
 // per datum (one coefficient plane of one source field) a node's 8 corner
