@@ -74,6 +74,9 @@ struct PlainStore {
     WP q = reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W));
     *q = f(*q);
   }
+  // Entry i of all planes in a row.
+  __device__ static __forceinline__ C load_at(const View& v, int64_t i) { return v.base[i]; }
+  __device__ static __forceinline__ void store_at(const View& v, int64_t i, C x) { v.base[i] = x; }
   // the same accesses, non-temporal
   __device__ static __forceinline__ C load_nt(const View& v, int pl, uint32_t node) {
     return __builtin_nontemporal_load(reinterpret_cast<WP>(plane(v, pl) + node * (uint32_t)sizeof(W)));
@@ -159,6 +162,12 @@ struct SplitStoreT {
     const float hi = (float)x;
     *reinterpret_cast<FP>(reinterpret_cast<CP>(hi_plane(v, pl)) + node * 4u) = hi;
     *reinterpret_cast<HP>(reinterpret_cast<CP>(lo_plane(v, pl)) + node * 2u) = to_bf16((float)(x - (double)hi));
+  }
+  __device__ static __forceinline__ C load_at(const View& v, int64_t i) { return widen(v.hi[i], v.lo[i]); }
+  __device__ static __forceinline__ void store_at(const View& v, int64_t i, C x) {
+    const float hi = (float)x;
+    v.hi[i] = hi;
+    v.lo[i] = to_bf16((float)(x - (double)hi));
   }
   template <class F>
   __device__ static __forceinline__ void update(const View& v, int pl, uint32_t node, F f) {
