@@ -252,6 +252,9 @@ hipError_t launch_steps_1d(const PlanView& pv, int32_t K, bool walls, void* p, v
   return hipGetLastError();
 }
 
+template <int D, int M>
+constexpr unsigned ghost_groups = (D * Dims<D, M>::NC + kGhostPlanes - 1) / kGhostPlanes;
+
 template <int D, int M, class S>
 hipError_t launch_ghost(const PlanView& pv, void* u, hipStream_t s) {
   constexpr int NC = Dims<D, M>::NC;
@@ -264,7 +267,7 @@ hipError_t launch_ghost(const PlanView& pv, void* u, hipStream_t s) {
     face = f > face ? f : face;
   }
   const typename S::View vu = S::make(u, D, NC, nodes);
-  hipLaunchKernelGGL((ghost_fill<D, M, S>), dim3((unsigned)((face + 255) / 256), D, 1), dim3(256, 1, 1), 0, s, vu,
+  hipLaunchKernelGGL((ghost_fill<D, M, S>), dim3((unsigned)((face + 255) / 256), D, ghost_groups<D, M>), dim3(256, 1, 1), 0, s, vu,
                      pv.uext[0], pv.uext[1], pv.uext[2]);
   return hipGetLastError();
 }
