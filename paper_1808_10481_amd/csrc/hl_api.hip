@@ -168,11 +168,11 @@ struct hl_plan_s {
   int32_t ygroup_req = 0; // 3D tile rows per group asked for (the grids clamp it to their extent)
   hl::KernelSet ks;
   void* dtab = nullptr;
-  void* dadj = nullptr;        // adjoint blocks (B^T then A^T), or NULL
-  size_t adj_u_off = 0;        // element offset of the A^T blocks in dadj
+  void* dadj = nullptr;        // transposed half-steps' tables (B^T then A^T), or NULL
+  size_t adj_u_off = 0;        // element offset of the A^T table in dadj
   // kappa gradient, allocated on first use: tables with kappa-derivative
   // weights and with -dt (one step reversed), copies of the forward state
-  // walked back step by step, scratch fields and reduction partials
+  // walked back step by step, and the partial sums
   // variable kappa (hl_set_kappa): Taylor data on the primal / dual nodes
   bool var_kappa = false;
   void* dkap_p = nullptr;
@@ -190,9 +190,8 @@ struct hl_plan_s {
   void* tab_rev = nullptr;
   void* fp = nullptr;
   void* fu = nullptr;
-  void* sp = nullptr;
-  void* su = nullptr;
   double* gpart = nullptr;
+  int gpart_n = 0;
   void* stage = nullptr;       // staging of host-layout data (convert_component), at most kStageKeep
   size_t stage_bytes = 0;
   double* dpartial = nullptr;  // norms scratch, kNormBlocks per plane
@@ -435,6 +434,53 @@ void build_adjoint_tables(const hl_plan_s* pl, std::vector<double>& tp, std::vec
         }
       }
     }
+}
+
+// The transposed half-steps' tables as their kernels read them: the all-upper
+// corner's entries (t, o), datum t, output o, first Pb -= B^T Ub (t = component
+// and coefficient of Ub), then Ub -= A^T Pb (t = coefficient of Pb).  Every
+// other corner's block must equal them up to the sigma / delta sign.  3D rows
+// hold the outputs of even r_x (Ub: even r_x + [i = 0]) first.
+hl_status pack_adjoint_tables(const hl_plan_s* pl, std::vector<double>& out, size_t* u_off) {
+  std::vector<double> tp, tu;
+  build_adjoint_tables(pl, tp, tu, WeightMode{pl->dt, false});
+  const int d = pl->d, MP = pl->m + 1, nc = pl->nc, ne = 1 << d;
+  auto dig = [&](int x, int k) {
+    for (int q = 0; q < k; ++q) x /= MP;
+    return x % MP;
+  };
+  for (int side = 0; side < 2; ++side) {
+    const bool ptype = side == 0;
+    const int no = ptype ? nc : d * nc, nt = ptype ? d * nc : nc;
+    std::vector<int> rank(no);
+    int n = 0;
+    for (int par = 0; par < 2; ++par)
+      for (int o = 0; o < no; ++o) {
+        const int x = d < 3 ? 0 : (o % MP + (!ptype && o / nc == 0)) & 1;
+        if (x == par) rank[o] = n++;
+      }
+    if (!ptype) *u_off = out.size();
+    const size_t base = out.size();
+    out.resize(base + (size_t)nt * no);
+    // tp[e'][ii][r][c], tu[e'][io][r][c]
+    auto blk = [&](int e, int i, int r, int c) {
+      return (ptype ? tp : tu)[(((size_t)e * d + i) * nc + r) * nc + c];
+    };
+    for (int t = 0; t < nt; ++t)
+      for (int o = 0; o < no; ++o) {
+        const int i = ptype ? t / nc : o / nc, r = o % nc, c = t % nc;
+        const double up = blk(ne - 1, i, r, c);
+        for (int e = 0; e < ne; ++e) {
+          double sgn = 1.0;
+          for (int k = 0; k < d; ++k)
+            if (!((e >> k) & 1) && ((dig(r, k) + dig(c, k) + (k == i)) & 1)) sgn = -sgn;
+          if (std::fabs(blk(e, i, r, c) - sgn * up) > 1e-12 * std::fabs(up) + 1e-300)
+            return fail(HL_ERR_ARG, "internal: transposed table lacks the sigma/delta symmetry");
+        }
+        out[base + (size_t)t * no + rank[o]] = up;
+      }
+  }
+  return HL_OK;
 }
 
 // Build every table of the plan into host FP64 memory (packed as the kernels
@@ -929,59 +975,53 @@ hl_status sumsq(const hl_plan_s* pl, const void* x, int field, double* out) {
   }
 }
 
-// <a, b> over `planes` coefficient planes of `nodes` entries (periodic state
-// buffers: every entry counts), FP64 accumulation; one partial per block.
-template <class S>
-__global__ void dot_kernel(typename S::View a, typename S::View b, int planes, double* __restrict__ partial) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  for (int pl = 0; pl < planes; ++pl)
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < a.nodes; n += (int64_t)gridDim.x * blockDim.x)
-      acc = fma((double)S::load(a, pl, (uint32_t)n), (double)S::load(b, pl, (uint32_t)n), acc);
-  red[threadIdx.x] = acc;
+// *acc += sum of n partials (hi, lo), in a fixed order (one block of 1024).
+__global__ void __launch_bounds__(1024) add_partials(const double* __restrict__ partial, int n,
+                                                     double* __restrict__ acc) {
+  __shared__ double red[2][1024];
+  hl::ExactSum v;
+  for (int i = threadIdx.x; i < n; i += 1024) v.add(partial[2 * i], partial[2 * i + 1]);
+  red[0][threadIdx.x] = v.hi;
+  red[1][threadIdx.x] = v.lo;
   __syncthreads();
-  for (int k = blockDim.x / 2; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+  for (int k = 512; k > 0; k >>= 1) {
+    if ((int)threadIdx.x < k) {
+      v.add(red[0][threadIdx.x + k], red[1][threadIdx.x + k]);
+      red[0][threadIdx.x] = v.hi;
+      red[1][threadIdx.x] = v.lo;
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) *acc += v.hi + v.lo;
 }
 
-// *acc += sum of n partials, in a fixed order (one block of 256).
-__global__ void add_partials(const double* __restrict__ partial, int n, double* __restrict__ acc) {
-  __shared__ double red[256];
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) v += partial[i];
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int k = blockDim.x / 2; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *acc += red[0];
+__global__ void clear_words(double* __restrict__ x, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) x[i] = 0.0;
 }
 
-// *acc += <a, b> for two p-shaped (field 0) or u-shaped (field 1) buffers.
-hipError_t dot_into(const hl_plan_s* pl, const void* a, const void* b, int field, double* acc, hipStream_t s) {
-  const int planes = (field == 0 ? 1 : pl->d) * pl->nc;
-  const int64_t nodes = field == 0 ? pl->pnodes : pl->unodes;
-  const int ncomp = field == 0 ? 1 : pl->d;
-  if (pl->precision == HL_FP64) {
-    using S = hl::PlainStore<double>;
-    hipLaunchKernelGGL(dot_kernel<S>, dim3(kNormBlocks), dim3(256), 0, s, S::make(a, ncomp, pl->nc, nodes),
-                       S::make(b, ncomp, pl->nc, nodes), planes, pl->gpart);
-  } else if (pl->precision == HL_FP32_COMP) {
-    using S = hl::SplitStore;
-    hipLaunchKernelGGL(dot_kernel<S>, dim3(kNormBlocks), dim3(256), 0, s, S::make(a, ncomp, pl->nc, nodes),
-                       S::make(b, ncomp, pl->nc, nodes), planes, pl->gpart);
-  } else {
-    using S = hl::PlainStore<float>;
-    hipLaunchKernelGGL(dot_kernel<S>, dim3(kNormBlocks), dim3(256), 0, s, S::make(a, ncomp, pl->nc, nodes),
-                       S::make(b, ncomp, pl->nc, nodes), planes, pl->gpart);
+// The gradient's partial sums: an entry (hi, lo) per workgroup of the pressure grid
+// (*pp), then of the velocity grid (*pu), cleared; and their sum added to *acc.
+int partials_of(const hl::Grid& g) { return g.per_xcd * hl::kXcds; }
+hipError_t begin_partials(hl_plan_s* pl, const hl::PlanView& v, double** pp, double** pu, hipStream_t s) {
+  const int np = 2 * partials_of(v.gp), n = np + 2 * partials_of(v.gu);
+  if (pl->gpart_n < n) {  // other tiles than before: the old sums may still be read
+    hipError_t e = hipStreamSynchronize(s);
+    if (pl->gpart) (void)hipFree(pl->gpart);
+    pl->gpart = nullptr;
+    pl->gpart_n = 0;
+    if (e == hipSuccess) e = hipMalloc((void**)&pl->gpart, (size_t)n * sizeof(double));
+    if (e != hipSuccess) return e;
+    pl->gpart_n = n;
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(add_partials, dim3(1), dim3(256), 0, s, (const double*)pl->gpart, kNormBlocks, acc);
+  hipLaunchKernelGGL(clear_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pl->gpart, n);
+  *pp = pl->gpart;
+  *pu = pl->gpart + np;
+  return hipGetLastError();
+}
+hipError_t end_partials(const hl_plan_s* pl, const hl::PlanView& v, double* acc, hipStream_t s) {
+  hipLaunchKernelGGL(add_partials, dim3(1), dim3(1024), 0, s, (const double*)pl->gpart,
+                     partials_of(v.gp) + partials_of(v.gu), acc);
   return hipGetLastError();
 }
 
@@ -1030,11 +1070,8 @@ hl_status ensure_gradient(hl_plan_s* pl) {
   if (e == hipSuccess) e = upload_table(pl, trev, &pl->tab_rev);
   if (e == hipSuccess) e = hipMalloc(&pl->fp, pbytes);
   if (e == hipSuccess) e = hipMalloc(&pl->fu, ubytes);
-  if (e == hipSuccess) e = hipMalloc(&pl->sp, pbytes);
-  if (e == hipSuccess) e = hipMalloc(&pl->su, ubytes);
-  if (e == hipSuccess) e = hipMalloc((void**)&pl->gpart, kNormBlocks * sizeof(double));
   if (e != hipSuccess) {
-    for (void** q : {&pl->tab_dk, &pl->tab_rev, &pl->fp, &pl->fu, &pl->sp, &pl->su, (void**)&pl->gpart}) {
+    for (void** q : {&pl->tab_dk, &pl->tab_rev, &pl->fp, &pl->fu}) {
       if (*q) (void)hipFree(*q);
       *q = nullptr;
     }
@@ -1094,6 +1131,7 @@ bool make_grid(const hl_plan_s* pl, const int32_t* tile, int32_t ygroup, const i
   g->ty = tile[1];
   // whole 128-byte lines per row (the narrowest word of a row: FP32_COMP's BF16 lo words), and a state past the
   // 256 MB last-level cache
+  g->open = 0;
   const int64_t state = (int64_t)pl->nc * (pl->pnodes + pl->d * pl->unodes) * pl->word_bytes * pl->words_per_coef;
   g->stream = ooff == 0 && (int64_t)oext[0] * pl->word_bytes % 128 == 0 && state > (int64_t)256 << 20;
   g->onodes = onodes;
@@ -1313,14 +1351,17 @@ hl_status hl_plan(const hl_problem* prob, hl_plan_t* out) {
     return hip_fail(e, "hl_plan: table upload");
   }
   if (pl->ks.adj_p) {
-    std::vector<double> tp, tu;
-    build_adjoint_tables(pl, tp, tu, WeightMode{pl->dt, false});
-    pl->adj_u_off = tp.size();
-    const size_t n = tp.size() + tu.size();
+    std::vector<double> all;
+    st = pack_adjoint_tables(pl, all, &pl->adj_u_off);
+    if (st != HL_OK) {
+      (void)hipFree(pl->dtab);
+      (void)hipFree(pl->dpartial);
+      delete pl;
+      return st;
+    }
+    const size_t n = all.size();
     e = hipMalloc(&pl->dadj, n * pl->tab_bytes);
     if (e == hipSuccess) {
-      std::vector<double> all(tp);
-      all.insert(all.end(), tu.begin(), tu.end());
       if (pl->tab_bytes == 8) {
         e = hipMemcpy(pl->dadj, all.data(), n * 8, hipMemcpyHostToDevice);
       } else {
@@ -1363,7 +1404,7 @@ hl_status hl_plan_destroy(hl_plan_t plan) {
   if (plan->cap_stream) (void)hipStreamDestroy(plan->cap_stream);
   if (plan->dtab) (void)hipFree(plan->dtab);
   if (plan->dadj) (void)hipFree(plan->dadj);
-  for (void* q : {plan->dkap_p, plan->dkap_u, plan->tab_dk, plan->tab_rev, plan->fp, plan->fu, plan->sp, plan->su,
+  for (void* q : {plan->dkap_p, plan->dkap_u, plan->tab_dk, plan->tab_rev, plan->fp, plan->fu,
                   (void*)plan->gpart, (void*)plan->gkp, (void*)plan->gku, plan->vscr, plan->wscr, plan->vzw,
                   plan->ucw, plan->stage, plan->alt_p, plan->alt_u})
     if (q) (void)hipFree(q);
@@ -1661,6 +1702,7 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
     if (!make_grid(plan, tile, plan->gu.ygroup, plan->uext, plan->uext, 0, plan->pext, -1, plan->unodes,
                    plan->pnodes, &gf))
       return fail(HL_ERR_UNSUPPORTED, "hl_adjoint_step: grid too large for the launch");
+    gf.open = 1;
     if (!plan->wscr) {
       const size_t ub = (size_t)plan->d * plan->nc * plan->unodes * state_bytes(plan);
       hipError_t e = hipMalloc(&plan->wscr, ub);
@@ -1688,21 +1730,20 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
     const size_t pbytes = (size_t)plan->nc * plan->pnodes * state_bytes(plan);
     const size_t ubytes = (size_t)plan->d * plan->nc * plan->unodes * state_bytes(plan);
     double* g = static_cast<double*>(grad_kappa);
+    double *pp = nullptr, *pu = nullptr;
+    if (e == hipSuccess) e = begin_partials(plan, v, &pp, &pu, s);
     if (e == hipSuccess) e = hipMemcpyAsync(plan->fp, p, pbytes, hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(plan->fu, u, ubytes, hipMemcpyDeviceToDevice, s);
     for (int64_t n = 0; n < nsteps && e == hipSuccess; ++n) {
-      e = hipMemsetAsync(plan->su, 0, ubytes, s);
-      if (e == hipSuccess) e = plan->ks.u_half(vdk, plan->su, plan->fp, 1.0, s);       // su = -B_kappa P'
-      if (e == hipSuccess) e = dot_into(plan, u_bar, plan->su, 1, g, s);
+      e = plan->ks.u_dot(vdk, u_bar, plan->fp, pu, s);                                 // <Ub', -B_kappa P'>
       if (e == hipSuccess) e = plan->ks.u_half(v, plan->fu, plan->fp, -1.0, s);       // fu = U_t
       if (e == hipSuccess) e = plan->ks.adj_p(vb, p_bar, u_bar, s);                    // Pb -= B^T Ub
       if (e == hipSuccess) e = plan->ks.ghost(v, plan->fu, s);                         // G U_t
-      if (e == hipSuccess) e = hipMemsetAsync(plan->sp, 0, pbytes, s);
-      if (e == hipSuccess) e = plan->ks.p_half(vdk, plan->sp, plan->fu, s);             // sp = -A_kappa G U_t
-      if (e == hipSuccess) e = dot_into(plan, p_bar, plan->sp, 0, g, s);
+      if (e == hipSuccess) e = plan->ks.p_dot(vdk, p_bar, plan->fu, pp, s);            // <Pb, -A_kappa G U_t>
       if (e == hipSuccess) e = plan->ks.p_half(vrev, plan->fp, plan->fu, s);            // fp = P_t
       if (e == hipSuccess) e = plan->ks.adj_u_walls(va, gf, u_bar, p_bar, plan->wscr, s);  // Ub -= G^T A^T Pb
     }
+    if (e == hipSuccess) e = end_partials(plan, v, g, s);
     return e == hipSuccess ? HL_OK : hip_fail(e, "hl_adjoint_step: gradient launch");
   }
   if (!grad_kappa) {
@@ -1725,21 +1766,20 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
   const size_t pbytes = (size_t)plan->nc * plan->pnodes * state_bytes(plan);
   const size_t ubytes = (size_t)plan->d * plan->nc * plan->unodes * state_bytes(plan);
   double* g = static_cast<double*>(grad_kappa);
-  hipError_t e = hipMemcpyAsync(plan->fp, p, pbytes, hipMemcpyDeviceToDevice, s);
+  double *pp = nullptr, *pu = nullptr;
+  hipError_t e = begin_partials(plan, v, &pp, &pu, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(plan->fp, p, pbytes, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(plan->fu, u, ubytes, hipMemcpyDeviceToDevice, s);
   for (int64_t n = 0; n < nsteps && e == hipSuccess; ++n) {
     // (fp, fu) = (P', U') after the step being undone; (p_bar, u_bar) its adjoint
-    e = hipMemsetAsync(plan->su, 0, ubytes, s);
-    if (e == hipSuccess) e = plan->ks.u_half(vdk, plan->su, plan->fp, 1.0, s);       // su = -B_kappa P'
-    if (e == hipSuccess) e = dot_into(plan, u_bar, plan->su, 1, g, s);
+    e = plan->ks.u_dot(vdk, u_bar, plan->fp, pu, s);                                 // <Ub', -B_kappa P'>
     if (e == hipSuccess) e = plan->ks.u_half(v, plan->fu, plan->fp, -1.0, s);       // fu = U_t
     if (e == hipSuccess) e = plan->ks.adj_p(vb, p_bar, u_bar, s);                    // Pb -= B^T Ub
-    if (e == hipSuccess) e = hipMemsetAsync(plan->sp, 0, pbytes, s);
-    if (e == hipSuccess) e = plan->ks.p_half(vdk, plan->sp, plan->fu, s);             // sp = -A_kappa U_t
-    if (e == hipSuccess) e = dot_into(plan, p_bar, plan->sp, 0, g, s);
+    if (e == hipSuccess) e = plan->ks.p_dot(vdk, p_bar, plan->fu, pp, s);            // <Pb, -A_kappa U_t>
     if (e == hipSuccess) e = plan->ks.p_half(vrev, plan->fp, plan->fu, s);            // fp = P_t
     if (e == hipSuccess) e = plan->ks.adj_u(va, u_bar, p_bar, s);                    // Ub -= A^T Pb
   }
+  if (e == hipSuccess) e = end_partials(plan, v, g, s);
   return e == hipSuccess ? HL_OK : hip_fail(e, "hl_adjoint_step: gradient launch");
 }
 

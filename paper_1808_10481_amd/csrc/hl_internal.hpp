@@ -40,6 +40,7 @@ typedef hipError_t (*AdjFn)(const PlanView&, void* out, const void* in, hipStrea
 // zeroed), and the ghost-shell clear of an adjoint velocity.
 typedef hipError_t (*AdjWallFn)(const PlanView&, const Grid& gfull, void* ub, const void* pb, void* scr,
                                 hipStream_t);
+typedef hipError_t (*DotFn)(const PlanView&, const void* bar, const void* in, double* part, hipStream_t);
 typedef hipError_t (*GhostZeroFn)(const PlanView&, void* u, hipStream_t);
 // Batched shots: descriptor images of the p and u half-steps of every shot
 // (built where the storage type is known) and the two batched launches.
@@ -70,6 +71,7 @@ struct KernelSet {
   int whole;             // 1D: nodes one workgroup holds
   GhostFn ghost;         // ghost-shell refresh of a wall-bounded velocity array
   AdjFn adj_p, adj_u;    // transposed half-steps, NULL where not built
+  DotFn p_dot, u_dot;    // inner products with a half-step's increment
   AdjWallFn adj_u_walls; // walls: ub -= G^T A^T pb, NULL where not built
   AdjWallFn gather_u_var_walls;  // walls, variable kappa: ub -= G^T (A^T pb from rho), NULL where not built
   GhostZeroFn ghost_zero;
@@ -167,10 +169,14 @@ hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
     using SL = PShape<M, S, kLayered>;
     using S1 = PShape<M, S, kOneLayer>;
     const Grid gz = layered(g, SL::TZ), g1 = layered(g, 1);
-    if (SL::TZ > 1 && gz.tiles >= kLayeredTiles && stage_fits(g.tx, g.ty, SL::TZ, SL::NS, SL::NE))
-      hipLaunchKernelGGL((p_half_3d<M, S, kLayered>), grid_shape(gz),
-                         dim3(SL::NS * class_items(g.tx, g.ty, SL::TZ)), 0, s, vp, vu, (const T*)pv.tab, gz);
-    else if (stage_fits(g.tx, g.ty, 1, S1::NS, S1::NE))
+    if constexpr (SL::TZ > 1) {
+      if (gz.tiles >= kLayeredTiles && stage_fits(g.tx, g.ty, SL::TZ, SL::NS, SL::NE)) {
+        hipLaunchKernelGGL((p_half_3d<M, S, kLayered>), grid_shape(gz),
+                           dim3(SL::NS * class_items(g.tx, g.ty, SL::TZ)), 0, s, vp, vu, (const T*)pv.tab, gz);
+        return hipGetLastError();
+      }
+    }
+    if (stage_fits(g.tx, g.ty, 1, S1::NS, S1::NE))
       hipLaunchKernelGGL((p_half_3d<M, S, kOneLayer>), grid_shape(g1), dim3(S1::NS * class_items(g.tx, g.ty, 1)), 0, s,
                          vp, vu, (const T*)pv.tab, g1);
     else
@@ -273,31 +279,77 @@ hipError_t launch_ghost(const PlanView& pv, void* u, hipStream_t s) {
 }
 
 template <int D, int M, class S, bool PTYPE>
-hipError_t launch_adjoint(const PlanView& pv, void* out, const void* in, hipStream_t s) {
+hipError_t launch_adjoint_on(const PlanView& pv, const Grid& g, void* out, const void* in, hipStream_t s) {
   using T = typename S::C;
   constexpr int NC = Dims<D, M>::NC;
-  const Grid& g = PTYPE ? pv.gp : pv.gu;
   const typename S::View vo = S::make(out, PTYPE ? 1 : D, NC, g.onodes);
   const typename S::View vi = S::make(in, PTYPE ? D : 1, NC, g.snodes);
-  hipLaunchKernelGGL((adjoint_half<D, M, S, PTYPE>), grid_shape(g), block_shape(g), 0, s, vo, vi,
-                     (const T*)pv.adj_tab, g);
+  const T* tab = (const T*)pv.adj_tab;
+  if constexpr (D < 3) {
+    hipLaunchKernelGGL((adjoint_half<D, M, S, PTYPE>), grid_shape(g), block_shape(g), 0, s, vo, vi, tab, g);
+    return hipGetLastError();
+  } else if constexpr (PTYPE) {  // the pressure half-step on the transposed table
+    PlanView pt = pv;
+    pt.tab = tab;
+    pt.gp = g;
+    return launch_p<3, M, S>(pt, out, in, s);
+  } else {
+    const Grid g1 = layered(g, 1);
+    hipLaunchKernelGGL((adjoint_u_3d<M, S>), grid_shape(g1), dim3(kUSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vo,
+                       vi, tab, g1);
+    return hipGetLastError();
+  }
+}
+template <int D, int M, class S, bool PTYPE>
+hipError_t launch_adjoint(const PlanView& pv, void* out, const void* in, hipStream_t s) {
+  return launch_adjoint_on<D, M, S, PTYPE>(pv, PTYPE ? pv.gp : pv.gu, out, in, s);
+}
+
+// part[..] += <pb, -A u> or <ub, -B p>, one entry per workgroup of the half-
+// step's grid (per_xcd * kXcds of them).
+template <int D, int M, class S>
+hipError_t launch_p_dot(const PlanView& pv, const void* pb, const void* u, double* part, hipStream_t s) {
+  using T = typename S::C;
+  constexpr int NC = Dims<D, M>::NC;
+  const Grid& g = pv.gp;
+  const typename S::View vp = S::make(pb, 1, NC, g.onodes), vu = S::make(u, D, NC, g.snodes);
+  if constexpr (D == 3) {
+    const Grid g1 = layered(g, 1);
+    hipLaunchKernelGGL((p_dot_3d<M, S>), grid_shape(g1), dim3(kPSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vp, vu,
+                       (const T*)pv.tab, g1, part);
+  } else {
+    hipLaunchKernelGGL((p_dot<D, M, S>), grid_shape(g), block_shape(g), 0, s, vp, vu, (const T*)pv.tab, g, part);
+  }
+  return hipGetLastError();
+}
+template <int D, int M, class S>
+hipError_t launch_u_dot(const PlanView& pv, const void* ub, const void* p, double* part, hipStream_t s) {
+  using T = typename S::C;
+  constexpr int NC = Dims<D, M>::NC;
+  const Grid& g = pv.gu;
+  const typename S::View vu = S::make(ub, D, NC, g.onodes), vp = S::make(p, 1, NC, g.snodes);
+  if constexpr (D == 3) {
+    const Grid g1 = layered(g, 1);
+    hipLaunchKernelGGL((u_dot_3d<M, S>), grid_shape(g1), dim3(kUSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vu, vp,
+                       (const T*)pv.tab, g1, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2], part);
+  } else {
+    hipLaunchKernelGGL((u_dot<D, M, S>), grid_shape(g), block_shape(g), 0, s, vu, vp, (const T*)pv.tab, g,
+                       (T)pv.ih[0], (T)pv.ih[1], part);
+  }
   return hipGetLastError();
 }
 
 template <int D, int M, class S>
 hipError_t launch_adj_u_walls(const PlanView& pv, const Grid& gf, void* ub, const void* pb, void* scr,
                               hipStream_t s) {
-  using T = typename S::C;
   constexpr int NC = Dims<D, M>::NC;
-  const typename S::View vs = S::make(scr, D, NC, gf.onodes);
-  hipLaunchKernelGGL((adjoint_walls_at<D, M, S>), grid_shape(gf), block_shape(gf), 0, s, vs,
-                     S::make(pb, 1, NC, gf.snodes), (const T*)pv.adj_tab, gf);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_adjoint_on<D, M, S, false>(pv, gf, scr, pb, s);
   if (e != hipSuccess) return e;
   int64_t interior = 1;
   for (int k = 0; k < D; ++k) interior *= pv.uext[k] - 2;
-  hipLaunchKernelGGL((ghost_fold<D, M, S>), dim3((unsigned)((interior + 255) / 256)), dim3(256), 0, s,
-                     S::make(ub, D, NC, gf.onodes), vs, pv.uext[0], pv.uext[1], pv.uext[2]);
+  hipLaunchKernelGGL((ghost_fold<D, M, S>), dim3((unsigned)((interior + 255) / 256), ghost_groups<D, M>), dim3(256), 0, s,
+                     S::make(ub, D, NC, gf.onodes), S::make(scr, D, NC, gf.onodes), pv.uext[0], pv.uext[1],
+                     pv.uext[2]);
   return hipGetLastError();
 }
 
@@ -426,7 +478,7 @@ hipError_t launch_gather_u_var_walls(const PlanView& pv, const Grid& gf, void* u
   if (e != hipSuccess) return e;
   int64_t interior = 1;
   for (int k = 0; k < D; ++k) interior *= pv.uext[k] - 2;
-  hipLaunchKernelGGL((ghost_fold<D, M, S>), dim3((unsigned)((interior + 255) / 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL((ghost_fold<D, M, S>), dim3((unsigned)((interior + 255) / 256), ghost_groups<D, M>), dim3(256), 0, s,
                      S::make(ub, D, NC, gf.onodes), vs, pv.uext[0], pv.uext[1], pv.uext[2]);
   return hipGetLastError();
 }
@@ -581,6 +633,8 @@ inline bool make_set(KernelSet* out) {
   out->adj_u = &launch_adjoint<D, M, S, false>;
   out->adj_u_walls = &launch_adj_u_walls<D, M, S>;
   out->ghost_zero = &launch_ghost_zero<D, M, S>;
+  out->p_dot = &launch_p_dot<D, M, S>;
+  out->u_dot = &launch_u_dot<D, M, S>;
   out->p_half_var = nullptr;
   out->u_half_var = nullptr;
   out->batch_desc = &batch_desc<D, M, S>;

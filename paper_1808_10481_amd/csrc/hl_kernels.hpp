@@ -96,6 +96,7 @@ struct Grid {
   // half-step, streamed / cached: 3D m = 2 FP64 256^3 5.04 / 5.33 ms, 64^3
   // 98 / 83 us; FP32 161x150x143 1006 / 684 us.
   int32_t stream;
+  int32_t open;  // corners outside the source array are zero (no wrap; walled adjoint)
   int64_t onodes;     // output array nodes (plane size)
   int64_t snodes;     // source array nodes (plane size)
 };
@@ -352,21 +353,15 @@ __device__ __forceinline__ void slice_pair_merge(const typename S::View& f, int 
   merge<D, M, VEL, FLIPL>(Mt, l, Sg, Df, acc);
 }
 
-// Pressure half-step at every primal node (1D and 2D).
+// Pressure increment at a primal node from its dual corners (1D and 2D).
 // tab: packed merged tables (hl_layout.hpp TableLayout), in S::C.
 template <int D, int M, class S, typename TP>
-__device__ __forceinline__ void p_half_body(typename S::View p, typename S::View u,
-                                            TP tab,
-                                            Grid g, int blk) {
+__device__ __forceinline__ void p_half_acc(const typename S::View& u, TP tab, const uint32_t* cn,
+                                           typename S::C* acc) {
   using T = typename S::C;
   using TL = TableLayout<D, M>;
   constexpr int MP = M + 1, NC = Dims<D, M>::NC;
   constexpr int NNZ = merged_nnz<D, M>(false);
-  int32_t j[3];
-  if (!node_of_block<D>(g, blk, j)) return;
-  uint32_t cn[1 << D];
-  corner_nodes<D>(g, j, cn);  // dual q = j - 1 + e (p) or primal j = q + e (u)
-  T acc[NC];
 #pragma unroll
   for (int s = 0; s < NC; ++s) acc[s] = T(0);
 #pragma unroll
@@ -376,6 +371,19 @@ __device__ __forceinline__ void p_half_body(typename S::View p, typename S::View
     // last component: interpolation pass in x, derivative in the merged table
     slice_pair_merge<D, M, false, 0, 1, S>(u, D - 1, cn, l, tab + TL::P_B_OFF + l * NNZ, acc);
   }
+}
+
+// Pressure half-step at every primal node (1D and 2D).
+template <int D, int M, class S, typename TP>
+__device__ __forceinline__ void p_half_body(typename S::View p, typename S::View u,
+                                            TP tab,
+                                            Grid g, int blk) {
+  int32_t j[3];
+  if (!node_of_block<D>(g, blk, j)) return;
+  uint32_t cn[1 << D];
+  corner_nodes<D>(g, j, cn);  // dual q = j - 1 + e
+  typename S::C acc[Dims<D, M>::NC];
+  p_half_acc<D, M, S>(u, tab, cn, acc);
   finish_pressure<D, M, S>(g, p, out_index<D>(g, j), acc);
 }
 
@@ -386,6 +394,18 @@ __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) p_half_kernel(typename S
   p_half_body<D, M, S, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
 }
 
+// Q on the set G at a dual node from its primal corners (1D and 2D).
+template <int D, int M, class S, typename TP>
+__device__ __forceinline__ void u_half_Q(const typename S::View& p, TP tab, const uint32_t* cn, typename S::C* Q) {
+  using T = typename S::C;
+  using TL = TableLayout<D, M>;
+  constexpr int NNZ = merged_nnz<D, M>(true);
+#pragma unroll
+  for (int o = 0; o < GSet<D, M>::NG; ++o) Q[o] = T(0);
+#pragma unroll
+  for (int l = 0; l <= M; ++l) slice_pair_merge<D, M, true, 0, 0, S>(p, 0, cn, l, tab + TL::U_OFF + l * NNZ, Q);
+}
+
 // Velocity half-step at every dual node (1D and 2D), weights scaled by wscale.
 template <int D, int M, class S, typename TP>
 __device__ __forceinline__ void u_half_body(typename S::View u, typename S::View p,
@@ -394,19 +414,12 @@ __device__ __forceinline__ void u_half_body(typename S::View u, typename S::View
                                             typename S::C ih0, typename S::C ih1,
                                             typename S::C ih2, int blk) {
   using T = typename S::C;
-  using TL = TableLayout<D, M>;
-  constexpr int MP = M + 1;
-  constexpr int NG = GSet<D, M>::NG;
-  constexpr int NNZ = merged_nnz<D, M>(true);
   int32_t j[3];
   if (!node_of_block<D>(g, blk, j)) return;
   uint32_t cn[1 << D];
-  corner_nodes<D>(g, j, cn);  // dual q = j - 1 + e (p) or primal j = q + e (u)
-  T Q[NG];
-#pragma unroll
-  for (int o = 0; o < NG; ++o) Q[o] = T(0);
-#pragma unroll
-  for (int l = 0; l < MP; ++l) slice_pair_merge<D, M, true, 0, 0, S>(p, 0, cn, l, tab + TL::U_OFF + l * NNZ, Q);
+  corner_nodes<D>(g, j, cn);  // primal j = q + e
+  T Q[GSet<D, M>::NG];
+  u_half_Q<D, M, S>(p, tab, cn, Q);
   const T ih[3] = {ih0, ih1, ih2};
   finish_velocity<D, M, S>(g, u, out_index<D>(g, j), Q, wscale, ih);
 }
@@ -681,16 +694,19 @@ struct Stage3 {
       const int e = min(item + k * items, total - 1);
       const int c[3] = {e % sx, (e / sx) % (g.ty + 1), e / sxy};
       int32_t n[3];
+      bool outside = false;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         // the corners of the grid's nodes wrap at most once; words of nodes
         // outside the grid are clamped into the array and never used
         int32_t i = o[q] + g.soff + c[q];
+        outside = outside || i < 0 || i >= g.sext[q];
         if (i < 0) i += g.sext[q];
         if (i >= g.sext[q]) i -= g.sext[q];
         n[q] = min(i, g.sext[q] - 1);
       }
-      src[k] = node_index<3>(n[0], n[1], n[2], g.sext);
+      // past the plane: the buffer descriptor answers with zero
+      src[k] = g.open && outside ? (uint32_t)g.snodes : node_index<3>(n[0], n[1], n[2], g.sext);
     }
     return true;
   }
@@ -757,6 +773,20 @@ template <typename T>
 __device__ __forceinline__ void pin(T& x) {
   asm volatile("" : "+v"(x));
 }
+
+// A sum that carries its rounding errors along; the terms of one work-item are
+// added plainly (exact products there changed no digit of the result).
+struct ExactSum {
+  double hi = 0.0, lo = 0.0;
+  __device__ __forceinline__ void add(double x, double xlo) {
+    const double t = hi + x, b = t - hi;
+    lo += ((hi - (t - b)) + (x - b)) + xlo;
+    hi = t;
+  }
+  __device__ __forceinline__ void add_product(double a, double b) {
+    hi = fma(a, b, hi);
+  }
+};
 
 // The data loop of one wavefront class: per datum q = 0 .. NQ - 1 (plane q of
 // f) its staged corners' combinations X are handed to apply.  F::kx(q) is the
@@ -839,9 +869,10 @@ struct PApply3 {
   }
 };
 
-template <int M, class S, class SH, int CLS, typename TP>
-__device__ __forceinline__ void p_half_3d_class(const typename S::View& p, const typename S::View& u, TP tab,
-                                                const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
+// DOT: p is not updated; returns this work-item's part of -<p, increment>.
+template <int M, class S, class SH, int CLS, bool DOT, typename TP>
+__device__ __forceinline__ ExactSum p_half_3d_class(const typename S::View& p, const typename S::View& u, TP tab,
+                                                    const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
   constexpr int NC = Dims<3, M>::NC;
   using A = PApply3<M, S, CLS, SH::NS, TP>;
@@ -851,19 +882,31 @@ __device__ __forceinline__ void p_half_3d_class(const typename S::View& p, const
   for (int s = 0; s < NC; ++s) f.acc[s] = T(0);
   stage_loop<3 * NC, S, SH>(u, st, lds, f, StageGroups<3 * NC>{});
   const uint32_t n0 = st.out(g);
-  update_outputs<3, S, A::kOut.n>(g, p, n0, [](int k) { return A::kOut.v[k]; },
-                                  [&](int k, T x) { return x - f.acc[A::kOut.v[k]]; });
+  if constexpr (DOT) {
+    ExactSum d;
+    if (st.active) {
+#pragma unroll
+      for (int k = 0; k < A::kOut.n; ++k)
+        d.add_product((double)f.acc[A::kOut.v[k]], (double)load_output<3, S, false>(p, A::kOut.v[k], n0));
+    }
+    return d;
+  } else {
+    update_outputs<3, S, A::kOut.n>(g, p, n0, [](int k) { return A::kOut.v[k]; },
+                                    [&](int k, T x) { return x - f.acc[A::kOut.v[k]]; });
+    return {};
+  }
 }
 
-template <int M, class S, class SH, typename TP>
-__device__ __forceinline__ void p_half_3d_body(typename S::View p, typename S::View u, TP tab, Grid g, int blk) {
+template <int M, class S, class SH, typename TP, bool DOT = false>
+__device__ __forceinline__ ExactSum p_half_3d_body(typename S::View p, typename S::View u, TP tab, Grid g, int blk) {
   __shared__ typename S::C lds[2 * kStageGroup * SH::CAP];
   Stage3<SH> st;
-  if (!st.init(g, blk)) return;  // dual q = j - 1 + e
+  if (!st.init(g, blk)) return {};  // dual q = j - 1 + e
   if (SH::NS == 1 || st.cls == 0)
-    p_half_3d_class<M, S, SH, 0>(p, u, tab, g, st, lds);
+    return p_half_3d_class<M, S, SH, 0, DOT>(p, u, tab, g, st, lds);
   else if constexpr (SH::NS > 1)
-    p_half_3d_class<M, S, SH, 1>(p, u, tab, g, st, lds);
+    return p_half_3d_class<M, S, SH, 1, DOT>(p, u, tab, g, st, lds);
+  return {};
 }
 
 template <int M, class S, int FORM>
@@ -910,8 +953,8 @@ struct UApply3 {
   }
 };
 
-template <int M, class S, class SH, int CLS, typename TP>
-__device__ __forceinline__ void u_half_3d_class(const typename S::View& u, const typename S::View& p, TP tab,
+template <int M, class S, class SH, int CLS, bool DOT, typename TP>
+__device__ __forceinline__ ExactSum u_half_3d_class(const typename S::View& u, const typename S::View& p, TP tab,
                                                 const Grid& g, typename S::C wscale, const typename S::C* ih,
                                                 const Stage3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
@@ -925,26 +968,41 @@ __device__ __forceinline__ void u_half_3d_class(const typename S::View& u, const
   const uint32_t n0 = st.out(g);
   // u_i[s] -= wscale * (s_i + 1) / h_i * Q[s + e_i]
   const T w[3] = {wscale * ih[0], wscale * ih[1], wscale * ih[2]};
-  update_outputs<3, S, A::kOut.n>(g, u, n0, [](int k) { return A::kOut.v[k]; }, [&](int k, T x) {
-    const int i = A::kOut.v[k] / NC, s = A::kOut.v[k] % NC;
-    const T a = -(T)(digit(s, MP, i) + 1) * w[i];
-    return fma(a, f.Q[kGIndex<3, M>.g[i][s]], x);
-  });
+  if constexpr (DOT) {
+    ExactSum d;
+    if (st.active) {
+#pragma unroll
+      for (int k = 0; k < A::kOut.n; ++k) {
+        const int i = A::kOut.v[k] / NC, s = A::kOut.v[k] % NC;
+        const T a = (T)(digit(s, MP, i) + 1) * w[i];
+        d.add_product((double)(a * f.Q[kGIndex<3, M>.g[i][s]]), (double)load_output<3, S, false>(u, A::kOut.v[k], n0));
+      }
+    }
+    return d;
+  } else {
+    update_outputs<3, S, A::kOut.n>(g, u, n0, [](int k) { return A::kOut.v[k]; }, [&](int k, T x) {
+      const int i = A::kOut.v[k] / NC, s = A::kOut.v[k] % NC;
+      const T a = -(T)(digit(s, MP, i) + 1) * w[i];
+      return fma(a, f.Q[kGIndex<3, M>.g[i][s]], x);
+    });
+    return {};
+  }
 }
 
-template <int M, class S, class SH, typename TP>
-__device__ __forceinline__ void u_half_3d_body(typename S::View u, typename S::View p, TP tab, Grid g,
+template <int M, class S, class SH, typename TP, bool DOT = false>
+__device__ __forceinline__ ExactSum u_half_3d_body(typename S::View u, typename S::View p, TP tab, Grid g,
                                                typename S::C wscale, typename S::C ih0, typename S::C ih1,
                                                typename S::C ih2, int blk) {
   using T = typename S::C;
   __shared__ T lds[2 * kStageGroup * SH::CAP];
   Stage3<SH> st;
-  if (!st.init(g, blk)) return;  // primal j = q + e
+  if (!st.init(g, blk)) return {};  // primal j = q + e
   const T ih[3] = {ih0, ih1, ih2};
   if (SH::NS == 1 || st.cls == 0)
-    u_half_3d_class<M, S, SH, 0>(u, p, tab, g, wscale, ih, st, lds);
+    return u_half_3d_class<M, S, SH, 0, DOT>(u, p, tab, g, wscale, ih, st, lds);
   else if constexpr (SH::NS > 1)
-    u_half_3d_class<M, S, SH, 1>(u, p, tab, g, wscale, ih, st, lds);
+    return u_half_3d_class<M, S, SH, 1, DOT>(u, p, tab, g, wscale, ih, st, lds);
+  return {};
 }
 
 template <int M, class S, int FORM>

@@ -9,150 +9,279 @@
 namespace hl {
 
 // ---------------------------------------------------------------------------
-// Discrete adjoint (periodic grids).  A step maps (P, U) to P' = P - A U,
-// U' = U - B P'; its transpose is Pb <- Pb - B^T Ub, then Ub <- Ub - A^T Pb:
-// the transposed half-steps in reverse order.  On the periodic grid each
-// transposed half-step is again a gather with the forward stencil: B^T Ub at
-// primal node j reads the dual nodes q = j - 1 + e' (the pressure half-step's
-// corners) and A^T Pb at dual node q reads the primal nodes j = q + e' (the
-// velocity half-step's), so no atomics are needed.  The operators are dense
-// per corner: T[e'][io][ii][r][c] (nc x nc blocks for output component io and
-// input component ii), built on the host from the same interpolation and
-// weight operators as the forward tables.
+// Discrete adjoint.  A step maps (P, U) to P' = P - A U, U' = U - B P'; its
+// transpose is Pb <- Pb - B^T Ub, then Ub <- Ub - A^T Pb: the transposed
+// half-steps in reverse order.  On the periodic grid each transposed half-step
+// is again a gather with the forward stencil: B^T Ub at primal node j reads
+// the dual nodes q = j - 1 + e' (the pressure half-step's corners) and A^T Pb
+// at dual node q reads the primal nodes j = q + e' (the velocity half-step's),
+// so no atomics are needed.  The operator of corner e' is that of the all-
+// upper corner up to sign: -1 for a lower corner in a dimension k in which
+// r_k + c_k + [k = i] is odd (output coefficient r, input coefficient c,
+// velocity component i on either side), because every interpolant coefficient
+// that links them has the parity of that component's derivative.  So, as in
+// the forward half-steps, an output takes one sigma / delta combination of the
+// 2^D corners of each datum times one table entry: 2^D times fewer multiply-
+// adds than a dense block per corner (2D m = 2 512^2 FP64 16 + 17 us; 34 + 37 us
+// with dense blocks; 3D m = 2 17496 multiply-adds per node and half-step against 2187).
 //   PTYPE = true:  out = Pb (1 component), in = Ub (D components)
 //   PTYPE = false: out = Ub (D components), in = Pb (1 component)
+// Table: entry (t, o), datum t = (input component, c), output o = (output
+// component, r), built on the host from the same interpolation and weight
+// operators as the forward tables; in 3D the outputs of a row are stored even
+// r_x + [i = 0] first (pressure: the forward table's order, so that Pb runs
+// the pressure half-step's own kernel on it).
+// With reflecting walls the step is P' = P - A G U, U' = U - B P', G the ghost
+// refresh; Ub -= G^T A^T Pb goes through a zeroed scratch array shaped like
+// the padded velocity: A^T Pb on every slot (an open grid: primal corners past
+// a wall contribute nothing), then the fold G^T (ghost_fold).  B writes no
+// ghost, so the ghost slots of Ub are held at zero.
 // ---------------------------------------------------------------------------
-// Output rows per pass: all nc at once up to nc = 27 (nc inputs plus nc
-// accumulators in registers); beyond that (2D m >= 5, 3D m = 3) passes of 16
-// rows, each re-reading the corner data (L1/L2 hits) so that the registers
-// and the unrolled code stay bounded.
-constexpr int kAdjointMaxNC = 27;
-template <int NC>
-constexpr int kAdjRows = NC <= kAdjointMaxNC ? NC : 16;
-
-// acc[r] += sum_c Tb[r][c] src[c] for the rows r0 + r < NC of one pass.
-template <int NC, int RB, typename T>
-__device__ __forceinline__ void dense_rows(const T* __restrict__ Tb, int r0, const T* src, T* acc) {
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    if (r0 + r >= NC) break;
-    // keep the scalar table loads of one row together (SGPR pressure)
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[r] = fma(Tb[r * NC + c], src[c], acc[r]);
-  }
-}
-
-template <int D, int M, class S, bool PTYPE>
-__device__ __forceinline__ void adjoint_half_body(typename S::View out, typename S::View in,
-                                                  const typename S::C* __restrict__ tab, Grid g, int blk) {
-  using T = typename S::C;
-  constexpr int NC = Dims<D, M>::NC, NO = PTYPE ? 1 : D, NI = PTYPE ? D : 1;
-  constexpr int RB = kAdjRows<NC>, NRB = (NC + RB - 1) / RB;
-  int32_t j[3];
-  if (!node_of_block<D>(g, blk, j)) return;
-  uint32_t cn[1 << D];
-  corner_nodes<D>(g, j, cn);
-  const uint32_t n0 = out_index<D>(g, j);
-#pragma unroll 1
-  for (int io = 0; io < NO; ++io) {
-#pragma unroll 1
-    for (int rb = 0; rb < NRB; ++rb) {
-      T acc[RB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) acc[r] = T(0);
-#pragma unroll
-      for (int e = 0; e < (1 << D); ++e) {
-#pragma unroll 1
-        for (int ii = 0; ii < NI; ++ii) {
-          T src[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) src[c] = S::load(in, ii * NC + c, cn[e]);
-          dense_rows<NC, RB>(tab + ((int64_t)((e * NO + io) * NI + ii) * NC + rb * RB) * NC, rb * RB, src, acc);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        if (rb * RB + r >= NC) break;
-        S::update(out, io * NC + rb * RB + r, n0, [&](T x) { return x - acc[r]; });
-      }
-    }
-  }
-}
-
 template <int D, int M, class S, bool PTYPE>
 __global__ void __launch_bounds__(256) adjoint_half(typename S::View out, typename S::View in,
                                                     const typename S::C* __restrict__ tab, Grid g) {
-  adjoint_half_body<D, M, S, PTYPE>(out, in, tab, g, blockIdx.x);
+  static_assert(D <= 2, "3D uses the staged kernels");
+  using T = typename S::C;
+  constexpr int MP = M + 1, NC = Dims<D, M>::NC, NI = PTYPE ? D : 1, NO = PTYPE ? NC : D * NC, NE = 1 << D;
+  int32_t j[3];
+  if (!node_of_block<D>(g, blockIdx.x, j)) return;
+  uint32_t cn[NE];
+  corner_nodes<D>(g, j, cn);
+  bool in_grid[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    in_grid[e] = true;
+    if (g.open) {
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        const int c = j[k] + g.soff + ((e >> k) & 1);
+        in_grid[e] = in_grid[e] && c >= 0 && c < g.sext[k];
+      }
+      if (!in_grid[e]) cn[e] = 0;
+    }
+  }
+  auto corner = [&](int t, int e) {
+    const T x = S::load(in, t, cn[e]);
+    return in_grid[e] ? x : T(0);
+  };
+  T acc[NO], vn[NE];  // vn: the next datum's corners, loaded one datum ahead
+#pragma unroll
+  for (int o = 0; o < NO; ++o) acc[o] = T(0);
+#pragma unroll
+  for (int e = 0; e < NE; ++e) vn[e] = corner(0, e);
+#pragma unroll
+  for (int t = 0; t < NI * NC; ++t) {
+    // keep the scalar table loads of one datum together (SGPR pressure)
+    __builtin_amdgcn_sched_barrier(0);
+    T X[NE], v[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) v[e] = vn[e];
+    if (t + 1 < NI * NC) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) vn[e] = corner(t + 1, e);
+    }
+#pragma unroll
+    for (int q = 0; q < NE / 2; ++q) {
+      X[2 * q] = v[2 * q + 1] + v[2 * q];
+      X[2 * q + 1] = v[2 * q + 1] - v[2 * q];
+    }
+    if constexpr (D == 2) {
+#pragma unroll
+      for (int kx = 0; kx < 2; ++kx) {
+        const T lo = X[kx], hi = X[kx + 2];
+        X[kx] = hi + lo;
+        X[kx + 2] = hi - lo;
+      }
+    }
+    const int c = t % NC;
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+      const int r = o % NC, i = PTYPE ? t / NC : o / NC;
+      int k = 0;
+#pragma unroll
+      for (int d = 0; d < D; ++d) k += ((digit(r, MP, d) + digit(c, MP, d) + (d == i)) & 1) << d;
+      acc[o] = fma(tab[t * NO + o], X[k], acc[o]);
+    }
+  }
+  update_outputs<D, S, NO>(g, out, out_index<D>(g, j), [](int o) { return o; }, [&](int o, T x) { return x - acc[o]; });
+}
+
+// Ub -= A^T Pb in 3D: the velocity half-step's staging and wavefront classes
+// with 3 (m+1)^3 outputs, a class taking one parity of r_x + [i = 0].
+template <int M>
+struct ARank {
+  short r[3 * Dims<3, M>::NC];
+  static constexpr int par(int o) { return (o % (M + 1) + (o / Dims<3, M>::NC == 0)) & 1; }
+  constexpr ARank() : r() {
+    int n = 0;
+    for (int p = 0; p < 2; ++p)
+      for (int o = 0; o < 3 * Dims<3, M>::NC; ++o)
+        if (par(o) == p) r[o] = (short)n++;
+  }
+};
+template <int M>
+inline constexpr ARank<M> kARank{};
+
+template <int M, class S, int CLS, int NS, typename TP>
+struct AApply3 {
+  using T = typename S::C;
+  static constexpr int MP = M + 1, NC = Dims<3, M>::NC, NO = 3 * NC;
+  TP tab;
+  T acc[NO];
+  static constexpr int kx(int a) { return (CLS + a % MP) & 1; }
+  static constexpr bool mine(int o) { return NS == 1 || ARank<M>::par(o) == CLS; }
+  static constexpr IndexList<NO> outputs() {
+    IndexList<NO> l{};
+    for (int o = 0; o < NO; ++o)
+      if (mine(o)) l.v[l.n++] = (short)o;
+    return l;
+  }
+  static constexpr IndexList<NO> kOut = outputs();
+  template <int A>
+  __device__ __forceinline__ void operator()(const T* X) {
+    constexpr int ax = A % MP, ay = (A / MP) % MP, az = A / (MP * MP);
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+      if (!mine(o)) continue;
+      const int i = o / NC, r = o % NC;
+      const int k = ((r % MP + ax + (i == 0)) & 1) + 2 * (((r / MP) % MP + ay + (i == 1)) & 1) +
+                    4 * ((r / (MP * MP) + az + (i == 2)) & 1);
+      acc[o] = fma(tab[A * NO + kARank<M>.r[o]], X[k], acc[o]);
+    }
+#pragma unroll
+    for (int o = 0; o < NO; ++o)
+      if (mine(o)) pin(acc[o]);
+  }
+};
+
+template <int M, class S, class SH, int CLS, typename TP>
+__device__ __forceinline__ void adjoint_u_3d_class(const typename S::View& out, const typename S::View& in, TP tab,
+                                                   const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
+  using T = typename S::C;
+  using A = AApply3<M, S, CLS, SH::NS, TP>;
+  A f;
+  f.tab = tab;
+#pragma unroll
+  for (int o = 0; o < A::NO; ++o) f.acc[o] = T(0);
+  stage_loop<A::NC, S, SH>(in, st, lds, f, StageGroups<A::NC>{});
+  update_outputs<3, S, A::kOut.n>(g, out, st.out(g), [](int k) { return A::kOut.v[k]; },
+                                  [&](int k, T x) { return x - f.acc[A::kOut.v[k]]; });
+}
+
+template <int M, class S>
+__global__ void __launch_bounds__((256 * kUSplit<M, S>)) adjoint_u_3d(typename S::View out, typename S::View in,
+                                                                      const typename S::C* __restrict__ tab, Grid g) {
+  using SH = UShape<M, S, kAnyTile>;
+  __shared__ typename S::C lds[2 * kStageGroup * SH::CAP];
+  Stage3<SH> st;
+  if (!st.init(g, blockIdx.x)) return;
+  if (SH::NS == 1 || st.cls == 0)
+    adjoint_u_3d_class<M, S, SH, 0>(out, in, tab, g, st, lds);
+  else if constexpr (SH::NS > 1)
+    adjoint_u_3d_class<M, S, SH, 1>(out, in, tab, g, st, lds);
 }
 
 // ---------------------------------------------------------------------------
-// Discrete adjoint with reflecting walls.  The walled step is P' = P - A G U,
-// U' = U - B P' with G the ghost refresh (each ghost the signed mirror of an
-// interior node); its transpose is Pb <- Pb - B^T Ub (adjoint_half with the
-// pressure grid, the ghost slots of Ub held at zero: B writes no ghost), then
-// Ub <- Ub - G^T A^T Pb: A^T Pb on every slot of the padded velocity array
-// (adjoint_walls_at below; primal corners beyond the walls contribute
-// nothing) into a scratch array, then the fold G^T (ghost_fold) that adds
-// each ghost slot, with its mirror sign, into the node it mirrors.
+// Inner products of a field with a half-step's increment, without forming the
+// increment: part[workgroup] -= <pb, A U> (pressure tables) or <ub, B P>.
+// The kappa gradient takes them with the kappa-derivative tables once per step;
+// a workgroup adds to its own entry, so the sum over steps has a fixed order.
+// The terms of smooth fields may all but cancel over the grid (orthogonal modes:
+// a sum of 1e-13 from terms of 1e4 in all), so the sums over work-items,
+// workgroups and steps carry their rounding errors along (hi, lo).
+// Against storing the increment and a dot product over the whole arrays,
+// 2D m = 2 512^2 FP64: 15 + 13 us instead of 17 + 28 + 17 + 19 us and two clears.
 // ---------------------------------------------------------------------------
-
-// scr[r] -= sum_e' T[e'] Pb[r - 1 + e'] at padded dual slot r (0..K+1 per
-// dimension) over the primal corners inside [0, K]: the grid's K are the
-// padded extents, soff = -1, sext the primal extents.
-template <int D, int M, class S>
-__global__ void __launch_bounds__(256) adjoint_walls_at(typename S::View scr, typename S::View pb,
-                                                        const typename S::C* __restrict__ tab, Grid g) {
-  using T = typename S::C;
-  constexpr int NC = Dims<D, M>::NC, RB = kAdjRows<NC>, NRB = (NC + RB - 1) / RB;
-  int32_t j[3];
-  if (!node_of_block<D>(g, blockIdx.x, j)) return;
-  int32_t lo[3] = {0, 0, 0};
-  bool vlo[3] = {true, true, true}, vhi[3] = {true, true, true};
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    lo[k] = j[k] - 1;
-    vlo[k] = lo[k] >= 0;
-    vhi[k] = lo[k] + 1 < g.sext[k];
+__device__ __forceinline__ void add_block_sum(ExactSum d, double* part) {
+  __shared__ double red[2][16];
+  const int tid = threadIdx.x + blockDim.x * threadIdx.y, n = blockDim.x * blockDim.y;
+  const int lane = tid & 63, lanes = min(64, n - (tid & ~63));
+  for (int k = 32; k > 0; k >>= 1) {
+    const double x = __shfl_down(d.hi, k), xl = __shfl_down(d.lo, k);
+    if (lane + k < lanes) d.add(x, xl);
   }
-  const uint32_t n0 = node_index<D>(j[0], j[1], j[2], g.oext);
-#pragma unroll 1
-  for (int io = 0; io < D; ++io) {
-#pragma unroll 1
-    for (int rb = 0; rb < NRB; ++rb) {
-      T acc[RB];
+  if (lane == 0) {
+    red[0][tid >> 6] = d.hi;
+    red[1][tid >> 6] = d.lo;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    ExactSum s{part[2 * blockIdx.x], part[2 * blockIdx.x + 1]};
+    for (int w = 0; w < (n + 63) / 64; ++w) s.add(-red[0][w], -red[1][w]);
+    part[2 * blockIdx.x] = s.hi;
+    part[2 * blockIdx.x + 1] = s.lo;
+  }
+}
+
+template <int D, int M, class S>
+__global__ void __launch_bounds__(256) p_dot(typename S::View pb, typename S::View u,
+                                             const typename S::C* __restrict__ tab, Grid g, double* part) {
+  static_assert(D <= 2, "3D uses the staged kernels");
+  using T = typename S::C;
+  int32_t j[3];
+  ExactSum d;
+  if (node_of_block<D>(g, blockIdx.x, j)) {
+    uint32_t cn[1 << D];
+    corner_nodes<D>(g, j, cn);
+    T acc[Dims<D, M>::NC];
+    p_half_acc<D, M, S>(u, tab, cn, acc);
+    const uint32_t n0 = out_index<D>(g, j);
 #pragma unroll
-      for (int r = 0; r < RB; ++r) acc[r] = T(0);
+    for (int s = 0; s < Dims<D, M>::NC; ++s) d.add_product((double)acc[s], (double)S::load(pb, s, n0));
+  }
+  add_block_sum(d, part);
+}
+
+template <int D, int M, class S>
+__global__ void __launch_bounds__(256) u_dot(typename S::View ub, typename S::View p,
+                                             const typename S::C* __restrict__ tab, Grid g, typename S::C ih0,
+                                             typename S::C ih1, double* part) {
+  static_assert(D <= 2, "3D uses the staged kernels");
+  using T = typename S::C;
+  constexpr int MP = M + 1, NC = Dims<D, M>::NC;
+  int32_t j[3];
+  ExactSum d;
+  if (node_of_block<D>(g, blockIdx.x, j)) {
+    uint32_t cn[1 << D];
+    corner_nodes<D>(g, j, cn);
+    T Q[GSet<D, M>::NG];
+    u_half_Q<D, M, S>(p, tab, cn, Q);
+    const uint32_t n0 = out_index<D>(g, j);
+    const T ih[2] = {ih0, ih1};
 #pragma unroll
-      for (int e = 0; e < (1 << D); ++e) {
-        bool valid = true;
-        int32_t c3[3] = {0, 0, 0};
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-          const bool up = (e >> k) & 1;
-          valid = valid && (up ? vhi[k] : vlo[k]);
-          c3[k] = lo[k] + (up ? 1 : 0);
-        }
-        if (!valid) continue;
-        const uint32_t cn = node_index<D>(c3[0], c3[1], c3[2], g.sext);
-        T src[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) src[c] = S::load(pb, c, cn);
-        dense_rows<NC, RB>(tab + ((int64_t)(e * D + io) * NC + rb * RB) * NC, rb * RB, src, acc);
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        if (rb * RB + r >= NC) break;
-        S::update(scr, io * NC + rb * RB + r, n0, [&](T x) { return x - acc[r]; });
-      }
+    for (int t = 0; t < D * NC; ++t) {
+      const int i = t / NC, s = t % NC;
+      const T a = (T)(digit(s, MP, i) + 1) * ih[i];
+      d.add_product((double)(a * Q[kGIndex<D, M>.g[i][s]]), (double)S::load(ub, t, n0));
     }
   }
+  add_block_sum(d, part);
+}
+
+template <int M, class S>
+__global__ void __launch_bounds__((256 * kPSplit<M, S>)) p_dot_3d(typename S::View pb, typename S::View u,
+                                                                  const typename S::C* __restrict__ tab, Grid g,
+                                                                  double* part) {
+  add_block_sum(p_half_3d_body<M, S, PShape<M, S, kAnyTile>, const typename S::C* __restrict__, true>(pb, u, tab, g,
+                                                                                                      blockIdx.x),
+                part);
+}
+
+template <int M, class S>
+__global__ void __launch_bounds__((256 * kUSplit<M, S>)) u_dot_3d(typename S::View ub, typename S::View p,
+                                                                  const typename S::C* __restrict__ tab, Grid g,
+                                                                  typename S::C ih0, typename S::C ih1,
+                                                                  typename S::C ih2, double* part) {
+  add_block_sum(u_half_3d_body<M, S, UShape<M, S, kAnyTile>, const typename S::C* __restrict__, true>(
+                    ub, p, tab, g, typename S::C(1), ih0, ih1, ih2, blockIdx.x),
+                part);
 }
 
 // G^T: ub[q] += scr[q] + sum over the ghost slots mirroring q of the signed
 // ghost value, and every scratch slot read is cleared (each ghost mirrors
 // exactly one interior node, so each slot is read once).  One work-item per
-// interior dual node; E the padded extents.
+// interior dual node and kGhostPlanes planes (grid y), their loads before
+// their stores; E the padded extents.
 template <int D, int M, class S>
 __global__ void __launch_bounds__(256) ghost_fold(typename S::View ub, typename S::View scr, int32_t E0, int32_t E1,
                                                   int32_t E2) {
@@ -181,13 +310,24 @@ __global__ void __launch_bounds__(256) ghost_fold(typename S::View ub, typename 
     }
   }
   const uint32_t n_q = node_index<D>(q[0], q[1], q[2], E);
+  const int pl0 = blockIdx.y * kGhostPlanes;
+  bool wall = false;
+  for (int k = 0; k < D; ++k) wall = wall || at[k];
+  T v[kGhostPlanes], x[kGhostPlanes];
 #pragma unroll
-  for (int i = 0; i < D; ++i)
+  for (int p = 0; p < kGhostPlanes; ++p) {
+    const int pl = min(pl0 + p, D * NC - 1);
+    v[p] = S::load(scr, pl, n_q);
+    x[p] = S::load(ub, pl, n_q);
+  }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      T v = S::load(scr, i * NC + c, n_q);
-      S::store(scr, i * NC + c, n_q, T(0));
+  for (int p = 0; p < kGhostPlanes; ++p) {
+    const int pl = pl0 + p;
+    if (pl >= D * NC) break;
+    S::store(scr, pl, n_q, T(0));
+    if (wall) {
       // every nonempty subset R of the wall dimensions: the ghost reflected in R
+      const int i = pl / NC, c = pl % NC;
 #pragma unroll
       for (int R = 1; R < (1 << D); ++R) {
         bool ok = true, neg = false;
@@ -201,12 +341,13 @@ __global__ void __launch_bounds__(256) ghost_fold(typename S::View ub, typename 
           }
         if (!ok) continue;
         const uint32_t n_g = node_index<D>(gq[0], gq[1], gq[2], E);
-        const T w = S::load(scr, i * NC + c, n_g);
-        S::store(scr, i * NC + c, n_g, T(0));
-        v += neg ? -w : w;
+        const T w = S::load(scr, pl, n_g);
+        S::store(scr, pl, n_g, T(0));
+        v[p] += neg ? -w : w;
       }
-      S::update(ub, i * NC + c, n_q, [&](T x) { return x + v; });
     }
+    S::store(ub, pl, n_q, x[p] + v[p]);
+  }
 }
 
 // Zero the ghost shell of a padded velocity array (E the padded extents).
@@ -663,6 +804,7 @@ __device__ __forceinline__ void u_half_var_body(typename S::View u, typename S::
   for (int b = 0; b < NP; ++b) {
     gk[b] *= va.w0;
     q[b] = gk[b];
+    pin(q[b]);  // rounded before the first t_k is added, also where the series is unrolled from k = 1
   }
   auto add = [&](const T* x) {
 #pragma unroll

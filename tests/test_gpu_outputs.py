@@ -18,7 +18,7 @@ import pytest
 
 import oracle
 from paper_1808_10481_amd import inputs
-from tests.tolerances import _close, tol
+from tolerances import _close, tol
 
 pytestmark = pytest.mark.gpu
 
