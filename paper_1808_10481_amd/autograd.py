@@ -116,7 +116,7 @@ class ReceiverTraces(torch.autograd.Function):
         pb = g_p.detach().contiguous().clone() if g_p is not None else torch.zeros_like(p0)
         ub = g_u.detach().contiguous().clone() if g_u is not None else torch.zeros_like(u0)
         g_tr = g_tr.detach().to(pb.dtype) if g_tr is not None else None
-        plan.kappa_grad(reset=True)  # start from zero
+        plan._clear_kappa_grad()
         for c in range(len(ctx.ckpts) - 1, -1, -1):
             t0 = c * seg
             t1 = min(nsteps, t0 + seg)
