@@ -1274,7 +1274,9 @@ __global__ void __launch_bounds__(64) u_half_var_wave(typename S::View u, typena
 //   g_k = r_k Lap t_{k-1} (k >= 1), g_0 = f (pressure side only).
 // The transposed interpolation then spreads dS/dc onto the 2^d corner blocks
 // (a gather over the neighbouring cells, second kernel).  t_{k-1} is
-// recomputed from t_0 for each k: no per-node stack of kmax polynomials.
+// recomputed from t_0 for each k: no per-node stack of kmax polynomials; where
+// they fit in registers (below) the lam_k, which depend on y and kappa alone,
+// are formed first and kept, and t_k is formed once.
 // ---------------------------------------------------------------------------
 
 // Cell-polynomial slots on which the adjoint data y of a node can be nonzero:
@@ -1323,10 +1325,24 @@ struct LaneLds {
 // 2D m = 3), where registers would spill to scratch.
 template <int D, int M, typename T>
 constexpr bool kGradStage = sizeof(T) * VK<D, M>::NP >= 512;
+// The lam_k kept in registers: polynomials of at most 288 bytes (up to FP64 2D
+// m = 2 and FP32 3D m = 1); longer ones would spill, and recompute.  One
+// transposed step, recomputed / kept: 2D m = 2 192 x 160 FP64 116 / 95 us, FP32
+// 101 / 78 us; 512^2 FP64 568 / 500 us, FP32 310 / 265 us; 3D m = 1 48^3 FP32
+// 553 / 459 us; 2D m = 1 256^2 FP64 44 / 41 us.
+template <int D, int M, typename T>
+constexpr bool kKeepLam = sizeof(T) * VK<D, M>::NP <= 288 && VK<D, M>::KMAX <= 4;
+// Wavefronts per SIMD asked for: 2D FP32 fits its kept lam_k in half the
+// registers to within two (left to itself the compiler takes those two and one
+// wavefront runs per SIMD: 326 us at 512^2).
+template <int D, int M, typename T>
+constexpr int kGradWaves = D == 2 && sizeof(T) == 4 && kKeepLam<D, M, T> ? 2 : 1;
 
 // grad_A += sum_b lam_{A+b} g_b (the kappa_A derivative of <lam, T[kappa g]>).
-template <int D, int M, int A, typename T>
+// lam and g on the coefficients of need <= J.
+template <int D, int M, bool VEL, int J, int A, typename T>
 __device__ __forceinline__ void corr_term(const T* lam, const T* g, const LaneLds<T>& L, int gs) {
+  if constexpr (kNeed<D, M, VEL>.n[A] > J) return;
   constexpr int N2 = 2 * M + 2, AX = A % N2, AY = (A / N2) % N2, AZ = A / (N2 * N2);
   constexpr int NY = D > 1 ? N2 : 1, NZ = D > 2 ? N2 : 1, NP = VK<D, M>::NP;
   T acc = L(gs, A, NP);
@@ -1335,24 +1351,27 @@ __device__ __forceinline__ void corr_term(const T* lam, const T* g, const LaneLd
 #pragma unroll
     for (int by = 0; by + AY < NY; ++by)
 #pragma unroll
-      for (int bx = 0; bx + AX < N2; ++bx)
-        acc = fma(lam[(bx + AX) + N2 * ((by + AY) + N2 * (bz + AZ))], g[bx + N2 * (by + N2 * bz)], acc);
+      for (int bx = 0; bx + AX < N2; ++bx) {
+        const int hi = (bx + AX) + N2 * ((by + AY) + N2 * (bz + AZ));
+        if (kNeed<D, M, VEL>.n[hi] <= J) acc = fma(lam[hi], g[bx + N2 * (by + N2 * bz)], acc);
+      }
   L(gs, A, NP) = acc;
 }
 
-template <int D, int M, typename T, int... A>
+template <int D, int M, bool VEL, int J, typename T, int... A>
 __device__ __forceinline__ void corr_terms(const T* lam, const T* g, const LaneLds<T>& L, int gs,
                                            std::integer_sequence<int, A...>) {
-  (corr_term<D, M, A>(lam, g, L, gs), ...);
+  (corr_term<D, M, VEL, J, A>(lam, g, L, gs), ...);
 }
 
-template <int D, int M, typename T>
+template <int D, int M, bool VEL, int J, typename T>
 __device__ __forceinline__ void corr(const T* lam, const T* g, const LaneLds<T>& L, int gs) {
-  corr_terms<D, M>(lam, g, L, gs, std::make_integer_sequence<int, VK<D, M>::NP>{});
+  corr_terms<D, M, VEL, J>(lam, g, L, gs, std::make_integer_sequence<int, VK<D, M>::NP>{});
 }
 
-// out = sc Lap^T f: sc sum_i (b_i - 1) b_i / h_i^2 f_{b - 2 e_i}.
-template <int D, int M, typename T>
+// out = sc Lap^T f: sc sum_i (b_i - 1) b_i / h_i^2 f_{b - 2 e_i}; f zero off
+// need <= J, out formed on need <= J + 1.
+template <int D, int M, bool VEL, int J, typename T>
 __device__ __forceinline__ void lapT_coef(const T* f, T* out, const T* ih, T sc) {
   constexpr int N2 = 2 * M + 2, NP = VK<D, M>::NP;
   const T ix2 = sc * ih[0] * ih[0], iy2 = sc * ih[1] * ih[1], iz2 = sc * ih[2] * ih[2];
@@ -1360,9 +1379,11 @@ __device__ __forceinline__ void lapT_coef(const T* f, T* out, const T* ih, T sc)
   for (int b = 0; b < NP; ++b) {
     const int bx = b % N2, by = (b / N2) % N2, bz = b / (N2 * N2);
     T v = T(0);
-    if (bx >= 2) v = fma(T((bx - 1) * bx) * ix2, f[b - 2], v);
-    if (D > 1 && by >= 2) v = fma(T((by - 1) * by) * iy2, f[b - 2 * N2], v);
-    if (D > 2 && bz >= 2) v = fma(T((bz - 1) * bz) * iz2, f[b - 2 * N2 * N2], v);
+    if (kNeed<D, M, VEL>.n[b] > J + 1) continue;
+    auto in = [](int x) { return kNeed<D, M, VEL>.n[x] <= J; };
+    if (bx >= 2 && in(bx >= 2 ? b - 2 : 0)) v = fma(T((bx - 1) * bx) * ix2, f[b - 2], v);
+    if (D > 1 && by >= 2 && in(by >= 2 ? b - 2 * N2 : 0)) v = fma(T((by - 1) * by) * iy2, f[b - 2 * N2], v);
+    if (D > 2 && bz >= 2 && in(bz >= 2 ? b - 2 * N2 * N2 : 0)) v = fma(T((bz - 1) * bz) * iz2, f[b - 2 * N2 * N2], v);
     out[b] = v;
   }
 }
@@ -1370,6 +1391,45 @@ __device__ __forceinline__ void lapT_coef(const T* f, T* out, const T* ih, T sc)
 // The series part shared by both sides: given t_0 (registers t0r, or LDS
 // slot t0s when staged) and y (compact on its support), returns lam_0 in lam
 // and adds sum_{k >= 1} sum_b lam_k[a + b] g_k[b] to the gradient (LDS slot gs).
+//
+// Kept form: lam_k lives on need <= J = kmax - k, so with g_k on the same set
+// each product is formed on it; lam_kmax .. lam_0 in registers, then one pass
+// over t_k.  Multiply-adds of 2D m = 2 against recomputing t_k with full
+// products: 3933 of 7497 (pressure), 3522 of 6174.  192 x 160 FP64, where a
+// SIMD has one wavefront at most, 36 + 32 us against 47 + 41.
+template <int D, int M, bool PSIDE, int K, class S>
+__device__ __forceinline__ void lam_back(const typename S::View& kv, uint32_t n0, const typename S::C* yc,
+                                         const VarArgs<typename S::C>& va, typename S::C (*lam)[VK<D, M>::NP]) {
+  if constexpr (K >= 1) {  // lam[K - 1] from lam[K]
+    using T = typename S::C;
+    using Y = YSupport<D, M, PSIDE>;
+    constexpr int NP = VK<D, M>::NP, J = VK<D, M>::KMAX - K;
+    T t[NP], l[NP];
+    tprod_grouped<D, M, !PSIDE, J, true, S>(kv, n0, lam[K], t);
+    lapT_coef<D, M, !PSIDE, J>(t, l, va.ih, va.ratio[K]);
+#pragma unroll
+    for (int b = 0; b < NP; ++b) {
+      const int yi = Y::idx(b);
+      lam[K - 1][b] = (yi >= 0 ? yc[yi < 0 ? 0 : yi] : T(0)) + (kNeed<D, M, !PSIDE>.n[b] <= J + 1 ? l[b] : T(0));
+    }
+    lam_back<D, M, PSIDE, K - 1, S>(kv, n0, yc, va, lam);
+  }
+}
+template <int D, int M, bool PSIDE, int K, class S>
+__device__ __forceinline__ void grad_forward(const typename S::View& kv, uint32_t n0, const LaneLds<typename S::C>& L,
+                                             int gs, const VarArgs<typename S::C>& va,
+                                             const typename S::C (*lam)[VK<D, M>::NP], typename S::C* t) {
+  if constexpr (K <= VK<D, M>::KMAX) {
+    using T = typename S::C;
+    constexpr int NP = VK<D, M>::NP, J = VK<D, M>::KMAX - K;
+    T l[NP];
+    lap_coef<D, M, !PSIDE, J>(t, l, va.ih, va.ratio[K]);  // g_k
+    corr<D, M, !PSIDE, J>(lam[K], l, L, gs);
+    if constexpr (K < VK<D, M>::KMAX) tprod_grouped<D, M, !PSIDE, J, false, S>(kv, n0, l, t);
+    grad_forward<D, M, PSIDE, K + 1, S>(kv, n0, L, gs, va, lam, t);
+  }
+}
+
 template <int D, int M, bool PSIDE, class S>
 __device__ __forceinline__ void adjoint_series(const typename S::View& kv, uint32_t n0,
                                                const LaneLds<typename S::C>& L, const typename S::C* t0r, int t0s,
@@ -1377,27 +1437,41 @@ __device__ __forceinline__ void adjoint_series(const typename S::View& kv, uint3
                                                typename S::C* lam) {
   using T = typename S::C;
   using Y = YSupport<D, M, PSIDE>;
-  constexpr int NP = VK<D, M>::NP;
+  constexpr int NP = VK<D, M>::NP, KMAX = VK<D, M>::KMAX;
   constexpr bool STAGE = kGradStage<D, M, T>;
+  if constexpr (kKeepLam<D, M, T>) {
+    T lk[KMAX + 1][NP], t[NP];
+#pragma unroll
+    for (int b = 0; b < NP; ++b) {
+      const int yi = Y::idx(b);
+      lk[KMAX][b] = yi >= 0 ? yc[yi < 0 ? 0 : yi] : T(0);
+      t[b] = t0r[b];
+    }
+    lam_back<D, M, PSIDE, KMAX, S>(kv, n0, yc, va, lk);
+    grad_forward<D, M, PSIDE, 1, S>(kv, n0, L, gs, va, lk, t);
+#pragma unroll
+    for (int b = 0; b < NP; ++b) lam[b] = lk[0][b];
+    return;
+  }
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     const int yi = Y::idx(b);
     lam[b] = yi >= 0 ? yc[yi < 0 ? 0 : yi] : T(0);
   }
 #pragma unroll 1
-  for (int k = VK<D, M>::KMAX; k >= 1; --k) {
+  for (int k = KMAX; k >= 1; --k) {
     T t[NP], l[NP];
 #pragma unroll
     for (int b = 0; b < NP; ++b) t[b] = STAGE ? L(t0s, b, NP) : t0r[b];
 #pragma unroll 1
     for (int q = 1; q < k; ++q) {  // t = t_{k-1}
-      lap_coef<D, M, !PSIDE, VK<D, M>::KMAX>(t, l, va.ih, va.ratio[q]);
-      tprod_grouped<D, M, !PSIDE, VK<D, M>::KMAX, false, S>(kv, n0, l, t);
+      lap_coef<D, M, !PSIDE, KMAX>(t, l, va.ih, va.ratio[q]);
+      tprod_grouped<D, M, !PSIDE, KMAX, false, S>(kv, n0, l, t);
     }
-    lap_coef<D, M, !PSIDE, VK<D, M>::KMAX>(t, l, va.ih, va.ratio[k]);  // g_k
-    corr<D, M>(lam, l, L, gs);
-    tprod_grouped<D, M, !PSIDE, VK<D, M>::KMAX, true, S>(kv, n0, lam, t);
-    lapT_coef<D, M>(t, l, va.ih, va.ratio[k]);
+    lap_coef<D, M, !PSIDE, KMAX>(t, l, va.ih, va.ratio[k]);  // g_k
+    corr<D, M, !PSIDE, KMAX>(lam, l, L, gs);
+    tprod_grouped<D, M, !PSIDE, KMAX, true, S>(kv, n0, lam, t);
+    lapT_coef<D, M, !PSIDE, KMAX>(t, l, va.ih, va.ratio[k]);
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
       const int yi = Y::idx(b);
@@ -1411,7 +1485,7 @@ __device__ __forceinline__ void adjoint_series(const typename S::View& kv, uint3
 // kappa coefficient) and rho_i = d S / d c^(i) (D NP planes of scratch).
 // 64 work-items per workgroup (a 64 x 1 tile).
 template <int D, int M, class S>
-__global__ void __launch_bounds__(64) grad_p_var(typename S::View pb, typename S::View u, typename S::View kp,
+__global__ void __launch_bounds__(64, (kGradWaves<D, M, typename S::C>)) grad_p_var(typename S::View pb, typename S::View u, typename S::View kp,
                                                  double* __restrict__ gk, typename S::View rho, Grid g,
                                                  VarArgs<typename S::C> va) {
   static_assert(D <= 2 || M <= 1, "the adjoint of the variable-kappa half-steps: d <= 2, or d = 3 with m <= 1");
@@ -1460,7 +1534,7 @@ __global__ void __launch_bounds__(64) grad_p_var(typename S::View pb, typename S
 #pragma unroll
     for (int b = 0; b < NP; ++b) f[b] = L(FS, b, NP);
   }
-  corr<D, M>(lam, f, L, GS);  // k = 0: t_0 = T[kappa f]
+  corr<D, M, false, VK<D, M>::KMAX>(lam, f, L, GS);  // k = 0: t_0 = T[kappa f]
 #pragma unroll
   for (int b = 0; b < NP; ++b) gk[(size_t)b * g.onodes + n0] -= (double)L(GS, b, NP);
   T phi[NP];  // dS/df
@@ -1482,7 +1556,7 @@ __global__ void __launch_bounds__(64) grad_p_var(typename S::View pb, typename S
 // pressure after the step's pressure half-step, gk -= dS/dkappa and
 // z = dS/dc (NP planes of scratch).  64 work-items per workgroup.
 template <int D, int M, class S>
-__global__ void __launch_bounds__(64) grad_u_var(typename S::View ub, typename S::View p, typename S::View ku,
+__global__ void __launch_bounds__(64, (kGradWaves<D, M, typename S::C>)) grad_u_var(typename S::View ub, typename S::View p, typename S::View ku,
                                                  double* __restrict__ gk, typename S::View z, Grid g,
                                                  VarArgs<typename S::C> va) {
   static_assert(D <= 2 || M <= 1, "the adjoint of the variable-kappa half-steps: d <= 2, or d = 3 with m <= 1");
