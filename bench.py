@@ -294,7 +294,7 @@ def run_1d(hl, torch, K=200, m=1):
             "value": K * wl.steps / (ms * 1e-3), "unit": "cell-updates/s",
             "nodal_l2_vs_exact": float(np.sqrt(wl.h[0] * np.sum((P[:, 0] - ex[:, 0]) ** 2))),
             "config": {"workload": f"standing_wave_1d m={m} {K} cells nu=0.5 T=1", "d": 1, "m": m,
-                       "cells": [K], "note": "launch-latency bound; hl_step replays 16-step graphs"}}
+                       "cells": [K], "note": "one launch takes all steps: a serial chain of half-steps in LDS"}}
 
 
 def run_walls(hl, torch, steps, K=1024, m=3):

@@ -162,8 +162,11 @@ hl_status hl_export(hl_plan_t plan, const void* p, const void* u,
  * velocity half-step (eq. (vdup)).  nsteps >= 0.  Asynchronous.
  * For nsteps >= 16 the steps are replayed from a HIP graph of 16 steps that
  * the plan captures (on a stream of its own) for the last (p, u) pair it was
- * given; a new pair re-captures.  A plan is not safe to use from several
- * host threads at once. */
+ * given; a new pair re-captures.  1D with constant kappa in HL_FP64 and
+ * HL_FP32 needs no graph: one launch takes many steps (all of them where one
+ * workgroup holds the grid; else several workgroups, from 4 steps on and not
+ * on a stream under capture, through a second pair of buffers of the plan).
+ * A plan is not safe to use from several host threads at once. */
 hl_status hl_step(hl_plan_t plan, void* p, void* u, int64_t nsteps, void* stream);
 /* With HL_WALLS every pressure half-step (in hl_step and hl_p_half) is
  * preceded by the ghost refresh of u. */
@@ -253,9 +256,9 @@ hl_status hl_norms_noalloc(hl_plan_t plan, const void* p, const void* u, double*
  * slots of u_bar are cleared first and stay zero.  The kappa gradient walks
  * the walled step back the same way (the ghost refresh of U_t before the
  * pressure-side operators read it).
- * The transposed half-steps apply dense per-corner blocks of nc x nc
- * (nc = (m+1)^d), all output rows at once up to nc = 27 and in passes of 16
- * rows beyond.  Built in every precision for every d and m (HL_FP32_COMP:
+ * The transposed half-steps take the sums and differences of a datum's
+ * corners times one table entry per output, as the forward half-steps do.
+ * Built in every precision for every d and m (HL_FP32_COMP:
  * FP64 arithmetic on the hi + lo data, each update rounded back to hi + lo as
  * in the forward step).  Asynchronous. */
 hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* p,
