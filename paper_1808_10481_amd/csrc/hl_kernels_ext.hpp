@@ -847,6 +847,13 @@ struct VW {
   static_assert(NPEN <= 64 && 8 * NC == NP && 4 * MP * MP == NPEN, "one pencil and one line per lane");
 };
 
+// Wavefronts per SIMD asked for.  FP64 (8.3 KB of LDS per node at m = 2) takes
+// 120 to 128 registers and 4 of them (5 spill: velocity 56^3 1160 us against
+// 1065); FP32 fits 8 with a few words of scratch (64^3 1280 + 1080 us; 5 of
+// them 1340 + 1113).
+template <class S>
+constexpr int kVarWaves = sizeof(typename S::C) == 8 ? 4 : 8;
+
 // Node of workgroup blk when every workgroup updates one node: consecutive
 // node numbers (x fastest) go to one XCD, so neighbours share its L2.
 __device__ __forceinline__ bool wave_node(const Grid& g, int blk, int32_t per_xcd, int32_t* j) {
@@ -872,16 +879,46 @@ __device__ __forceinline__ uint32_t corner_node_of(const Grid& g, const int32_t*
   return node_index<3>(c[0], c[1], c[2], g.sext);
 }
 
-// Full interpolant of component comp into B[b_x + N2 (b_y + N2 b_z)], through
-// A: the raw corner data A[e + 8 a], the x pass into B (line ey + 2 ez + 4
+// This lane's corner words of one component: corner lane mod 8, coefficients
+// lane div 8 + 8 i.  All of a node's words (and kappa's, and the outputs' old
+// values) are loaded before the first is used: loaded where they are used,
+// each component waited for memory by itself, and each output plane for the
+// store of the one before it.  m = 2 56^3 FP64 1365 + 1137 -> 1250 + 1065 us,
+// 64^3 FP32 1400 + 1220 -> 1280 + 1080 us.
+template <int M>
+constexpr int kCornerWords = (VW<M>::NC + 7) / 8;
+template <int M, class S>
+__device__ __forceinline__ void corner_words(const typename S::View& f, int comp, uint32_t cnl, int lane,
+                                             typename S::C* w) {
+  constexpr int NC = VW<M>::NC;
+#pragma unroll
+  for (int i = 0; i < kCornerWords<M>; ++i) w[i] = S::load(f, comp * NC + min((lane >> 3) + 8 * i, NC - 1), cnl);
+}
+template <int M, class S>
+struct KappaWords {
+  static constexpr int NP = VW<M>::NP, W = (NP + 63) / 64;
+  typename S::C w[W];
+  __device__ __forceinline__ void load(const typename S::View& kv, uint32_t n0, int lane) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = S::load(kv, min(lane + 64 * i, NP - 1), n0);
+  }
+  __device__ __forceinline__ void put(int lane, typename S::C* KA) const {
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+      if (lane + 64 * i < NP) KA[lane + 64 * i] = w[i];
+  }
+};
+
+// Full interpolant of one component (its corner words w) into
+// B[b_x + N2 (b_y + N2 b_z)], through A: the raw corner data A[e + 8 a], the x pass into B (line ey + 2 ez + 4
 // (ay + MP az), entries b_x), the y pass into A (line ez + 2 (az + MP b_x),
 // entries b_y), the z pass into B.  Every line is one lane's.
-template <int M, class S>
-__device__ __forceinline__ void interp_wave(const typename S::View& f, int comp, uint32_t cnl, int lane,
-                                            typename S::C* A, typename S::C* B) {
-  using T = typename S::C;
+template <int M, typename T>
+__device__ __forceinline__ void interp_wave(const T* w, int lane, T* A, T* B) {
   constexpr int MP = VW<M>::MP, N2 = VW<M>::N2, NC = VW<M>::NC, NL = VW<M>::NPEN;
-  for (int a = lane >> 3; a < NC; a += 8) A[(lane & 7) + 8 * a] = S::load(f, comp * NC + a, cnl);
+#pragma unroll
+  for (int i = 0; i < kCornerWords<M>; ++i)
+    if ((lane >> 3) + 8 * i < NC) A[(lane & 7) + 8 * ((lane >> 3) + 8 * i)] = w[i];
   __syncthreads();
   if (lane < NL) {
     const int ey = lane & 1, ez = (lane >> 1) & 1, ay = (lane >> 2) % MP, az = (lane >> 2) / MP;
@@ -1136,15 +1173,25 @@ __device__ __forceinline__ void p_half_var_wave_body(typename S::View p, typenam
   const WaveLane<M, false> w(lane);
   const uint32_t n0 = out_index<3>(g, j);
   const uint32_t cnl = corner_node_of(g, j, lane & 7);  // dual q = j - 1 + e
-  for (int a = lane; a < NP; a += 64) KA[a] = S::load(kp, a, n0);
   const bool pen = w.pen;
   const int by = w.by, bz = w.bz;
+  const bool own = pen && by < MP && bz < MP;  // pencil holds data entries (b_x < MP)
+  KappaWords<M, S> kw;
+  T cw[3][kCornerWords<M>], old[MP];
+  kw.load(kp, n0, lane);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) corner_words<M, S>(u, i, cnl, lane, cw[i]);
+  if (own) {
+#pragma unroll
+    for (int bx = 0; bx < MP; ++bx) old[bx] = S::load(p, bx + MP * (by + MP * bz), n0);
+  }
+  kw.put(lane, KA);
   T dv[N2];  // w_0 div c on the lane's pencil
 #pragma unroll
   for (int b = 0; b < N2; ++b) dv[b] = T(0);
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    interp_wave<M, S>(u, i, cnl, lane, A, B);
+    interp_wave<M>(cw[i], lane, A, B);
     if (pen) {
       const T f = va.w0 * va.ih[i];
       const T* r = B + N2 * (by + N2 * bz);
@@ -1164,7 +1211,6 @@ __device__ __forceinline__ void p_half_var_wave_body(typename S::View p, typenam
     for (int b = 0; b < N2; ++b) F[N2 * (by + N2 * bz) + b] = dv[b];
   }
   __syncthreads();
-  const bool own = pen && by < MP && bz < MP;  // pencil holds data entries (b_x < MP)
   T acc[MP], t[N2];
 #pragma unroll
   for (int b = 0; b < N2; ++b) t[b] = T(0);
@@ -1178,8 +1224,7 @@ __device__ __forceinline__ void p_half_var_wave_body(typename S::View p, typenam
   wave_series<M, false>(KA, F, Tc, RED, w, va, t, add);
   if (own) {
 #pragma unroll
-    for (int bx = 0; bx < MP; ++bx)
-      S::update(p, bx + MP * (by + MP * bz), n0, [&](T x) { return x - acc[bx]; });
+    for (int bx = 0; bx < MP; ++bx) S::store(p, bx + MP * (by + MP * bz), n0, old[bx] - acc[bx]);
   }
 }
 
@@ -1196,10 +1241,25 @@ __device__ __forceinline__ void u_half_var_wave_body(typename S::View u, typenam
   const WaveLane<M, true> w(lane);
   const uint32_t n0 = out_index<3>(g, j);
   const uint32_t cnl = corner_node_of(g, j, lane & 7);  // primal j = q + e
-  for (int a = lane; a < NP; a += 64) KA[a] = S::load(ku, a, n0);
   const bool pen = w.pen;
   const int by = w.by, bz = w.bz;
-  interp_wave<M, S>(p, 0, cnl, lane, A, B);
+  // u_i[s] takes q[s + e_i]: the pencil holding that updates it
+  const bool own[3] = {pen && by < MP && bz < MP, pen && by >= 1 && by <= MP && bz < MP,
+                       pen && by < MP && bz >= 1 && bz <= MP};
+  const int pl[3] = {MP * (by + MP * bz), NC + MP * ((by - 1) + MP * bz), 2 * NC + MP * (by + MP * (bz - 1))};
+  KappaWords<M, S> kw;
+  T cw[kCornerWords<M>], old[3][MP];
+  kw.load(ku, n0, lane);
+  corner_words<M, S>(p, 0, cnl, lane, cw);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (own[i]) {
+#pragma unroll
+      for (int sx = 0; sx < MP; ++sx) old[i][sx] = S::load(u, pl[i] + sx, n0);
+    }
+  }
+  kw.put(lane, KA);
+  interp_wave<M>(cw, lane, A, B);
   T* F = A;  // Laplacian of the current term (input of the product)
   T* Tc = B;  // current term g_k
   T gk[N2], q[N2];
@@ -1217,44 +1277,28 @@ __device__ __forceinline__ void u_half_var_wave_body(typename S::View u, typenam
     for (int b = 0; b <= MP; ++b) q[b] += x[b];
   };
   wave_series<M, true>(KA, F, Tc, RED, w, va, gk, add);
-  // u_i[s] -= wscale (s_i + 1) / h_i q[s + e_i]: the pencil holding q[s + e_i]
-  // updates u_i[s]
-  if (pen) {
-    if (by < MP && bz < MP) {
-      const T f = wscale * va.ih[0];
+  // u_i[s] -= wscale (s_i + 1) / h_i q[s + e_i]
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (own[i]) {
+      const T f = wscale * va.ih[i];
 #pragma unroll
       for (int sx = 0; sx < MP; ++sx) {
-        const T a = -(T)(sx + 1) * f, qv = q[sx + 1];
-        S::update(u, sx + MP * (by + MP * bz), n0, [&](T x) { return fma(a, qv, x); });
-      }
-    }
-    if (by >= 1 && by <= MP && bz < MP) {
-      const T a = -(T)by * (wscale * va.ih[1]);
-#pragma unroll
-      for (int sx = 0; sx < MP; ++sx) {
-        const T qv = q[sx];
-        S::update(u, NC + sx + MP * ((by - 1) + MP * bz), n0, [&](T x) { return fma(a, qv, x); });
-      }
-    }
-    if (by < MP && bz >= 1 && bz <= MP) {
-      const T a = -(T)bz * (wscale * va.ih[2]);
-#pragma unroll
-      for (int sx = 0; sx < MP; ++sx) {
-        const T qv = q[sx];
-        S::update(u, 2 * NC + sx + MP * (by + MP * (bz - 1)), n0, [&](T x) { return fma(a, qv, x); });
+        const T a = -(T)(i == 0 ? sx + 1 : i == 1 ? by : bz) * f;
+        S::store(u, pl[i] + sx, n0, fma(a, q[i == 0 ? sx + 1 : sx], old[i][sx]));
       }
     }
   }
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__(64) p_half_var_wave(typename S::View p, typename S::View u, typename S::View kp,
+__global__ void __launch_bounds__(64, kVarWaves<S>) p_half_var_wave(typename S::View p, typename S::View u, typename S::View kp,
                                                       Grid g, VarArgs<typename S::C> va, int32_t per_xcd) {
   p_half_var_wave_body<M, S>(p, u, kp, g, va, per_xcd, blockIdx.x);
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__(64) u_half_var_wave(typename S::View u, typename S::View p, typename S::View ku,
+__global__ void __launch_bounds__(64, kVarWaves<S>) u_half_var_wave(typename S::View u, typename S::View p, typename S::View ku,
                                                       Grid g, VarArgs<typename S::C> va, typename S::C wscale,
                                                       int32_t per_xcd) {
   u_half_var_wave_body<M, S>(u, p, ku, g, va, wscale, per_xcd, blockIdx.x);
@@ -1880,7 +1924,7 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kUSplit<M, S> : 256), 
 // Variable kappa, 3D m >= 2, batched: one 64-wide workgroup per node of each
 // shot, as in the single-shot launch.
 template <int M, class S>
-__global__ void __launch_bounds__(64) p_half_batch_wave(const ShotHalf<S>* __restrict__ shots, int n) {
+__global__ void __launch_bounds__(64, kVarWaves<S>) p_half_batch_wave(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   using G = typename S::Global;
   p_half_var_wave_body<M, G>(S::global(sh.out), S::global(sh.in), S::global(sh.kap), sh.g, sh.va, sh.wave_per_xcd,
@@ -1888,7 +1932,7 @@ __global__ void __launch_bounds__(64) p_half_batch_wave(const ShotHalf<S>* __res
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__(64) u_half_batch_wave(const ShotHalf<S>* __restrict__ shots, int n) {
+__global__ void __launch_bounds__(64, kVarWaves<S>) u_half_batch_wave(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   using G = typename S::Global;
   u_half_var_wave_body<M, G>(S::global(sh.out), S::global(sh.in), S::global(sh.kap), sh.g, sh.va, sh.wscale,
