@@ -201,13 +201,11 @@ struct hl_plan_s {
   // is launched on the caller's stream.
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
-  // 1D: the other buffers of multi-step launches over several workgroups, the
-  // stream that used them last and its event (a call on another stream waits
-  // for it)
+  // 1D: the other buffers of multi-step launches over several workgroups, and
+  // the event after their last use, which every call waits for
   void* alt_p = nullptr;
   void* alt_u = nullptr;
   hipEvent_t alt_done = nullptr;
-  hipStream_t alt_stream = nullptr;
   bool alt_used = false;
   const void* graph_p = nullptr;  // buffers the graph was captured for
   const void* graph_u = nullptr;
@@ -324,13 +322,18 @@ hl_status steps_1d(hl_plan_s* pl, const hl::PlanView& v, void* p, void* u, int64
       return HL_OK;
     }
     if (cap != hipStreamCaptureStatusNone) return HL_OK;
-    if (pl->alt_used && pl->alt_stream != s) e = hipStreamWaitEvent(s, pl->alt_done, 0);
+    // also where the handle is that of the last call: it may name another
+    // stream by now (a destroyed stream's handle given to a new one, the
+    // per-thread default stream of another thread)
+    if (pl->alt_used) e = hipStreamWaitEvent(s, pl->alt_done, 0);
   }
-  if (e == hipSuccess) e = pl->ks.steps(v, pl->K[0], pl->walls, p, u, pl->alt_p, pl->alt_u, nsteps, s);
-  if (!whole && e == hipSuccess) {
-    e = hipEventRecord(pl->alt_done, s);
-    pl->alt_stream = s;
-    pl->alt_used = true;
+  if (e == hipSuccess) {
+    e = pl->ks.steps(v, pl->K[0], pl->walls, p, u, pl->alt_p, pl->alt_u, nsteps, s);
+    if (!whole) {  // also after a launch that failed: the ones before it are under way
+      const hipError_t er = hipEventRecord(pl->alt_done, s);
+      pl->alt_used = true;
+      if (e == hipSuccess) e = er;
+    }
   }
   if (e != hipSuccess) return hip_fail(e, "hl_step: launch");
   *done = true;
