@@ -244,6 +244,14 @@ struct hl_batch_s {
 
 namespace {
 
+// Clears device memory and returns when it is clear: hipMemset may return
+// before, and streams that do not wait for the null stream would use the
+// memory uncleared.
+hipError_t clear_device(void* ptr, size_t bytes) {
+  hipError_t e = hipMemset(ptr, 0, bytes);
+  return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+}
+
 // Bytes per stored coefficient (FP32_COMP: an FP32 hi word and a BF16 lo word).
 size_t state_bytes(const hl_plan_s* pl) { return (size_t)pl->word_bytes * pl->words_per_coef; }
 
@@ -1097,8 +1105,8 @@ hl_status ensure_var_gradient(hl_plan_s* pl) {
   hipError_t e = hipMalloc((void**)&pl->gkp, gp);
   if (e == hipSuccess) e = hipMalloc((void**)&pl->gku, gu);
   if (e == hipSuccess) e = hipMalloc(&pl->vscr, sc);
-  if (e == hipSuccess) e = hipMemset(pl->gkp, 0, gp);
-  if (e == hipSuccess) e = hipMemset(pl->gku, 0, gu);
+  if (e == hipSuccess) e = clear_device(pl->gkp, gp);
+  if (e == hipSuccess) e = clear_device(pl->gku, gu);
   if (e != hipSuccess) {
     for (void** q : {(void**)&pl->gkp, (void**)&pl->gku, &pl->vscr}) {
       if (*q) (void)hipFree(*q);
@@ -1709,7 +1717,7 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
     if (!plan->wscr) {
       const size_t ub = (size_t)plan->d * plan->nc * plan->unodes * state_bytes(plan);
       hipError_t e = hipMalloc(&plan->wscr, ub);
-      if (e == hipSuccess) e = hipMemset(plan->wscr, 0, ub);  // the fold leaves it zeroed after each use
+      if (e == hipSuccess) e = clear_device(plan->wscr, ub);  // the fold leaves it zeroed after each use
       if (e != hipSuccess) {
         if (plan->wscr) (void)hipFree(plan->wscr);
         plan->wscr = nullptr;
@@ -1909,7 +1917,7 @@ hl_status hl_adjoint_step_var(hl_plan_t plan, void* p_bar, void* u_bar, const vo
     for (auto [q, bytes] : {std::pair<void**, size_t>{&plan->vzw, zb}, {&plan->ucw, ub}, {&plan->wscr, ub}}) {
       if (*q) continue;
       e = hipMalloc(q, bytes);
-      if (e == hipSuccess) e = hipMemset(*q, 0, bytes);
+      if (e == hipSuccess) e = clear_device(*q, bytes);
       if (e != hipSuccess) {
         if (*q) (void)hipFree(*q);
         *q = nullptr;
@@ -1961,7 +1969,7 @@ hl_status hl_kappa_grad(hl_plan_t plan, double* grad_p, double* grad_u, int rese
       }
       if (e != hipSuccess) return hip_fail(e, "hl_kappa_grad: copy to host");
     }
-    if (reset && (e = hipMemset(dev[f], 0, (size_t)(np * nodes[f]) * sizeof(double))) != hipSuccess)
+    if (reset && (e = clear_device(dev[f], (size_t)(np * nodes[f]) * sizeof(double))) != hipSuccess)
       return hip_fail(e, "hl_kappa_grad: reset");
   }
   return HL_OK;
