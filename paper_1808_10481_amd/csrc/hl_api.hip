@@ -987,6 +987,8 @@ hl_status sumsq(const hl_plan_s* pl, const void* x, int field, double* out) {
 }
 
 // *acc += sum of n partials (hi, lo), in a fixed order (one block of 1024).
+// Past the largest finite value the rounding errors carried along are inf - inf:
+// hi alone is the plain sum, infinite with its sign.
 __global__ void __launch_bounds__(1024) add_partials(const double* __restrict__ partial, int n,
                                                      double* __restrict__ acc) {
   __shared__ double red[2][1024];
@@ -1003,7 +1005,7 @@ __global__ void __launch_bounds__(1024) add_partials(const double* __restrict__ 
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) *acc += v.hi + v.lo;
+  if (threadIdx.x == 0) *acc += isfinite(v.lo) ? v.hi + v.lo : v.hi;
 }
 
 __global__ void clear_words(double* __restrict__ x, int n) {
