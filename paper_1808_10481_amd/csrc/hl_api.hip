@@ -666,6 +666,8 @@ bool finite_pos(double x) { return std::isfinite(x) && x > 0.0; }
 
 using hl_host::FieldImage;
 using hl_host::LayoutMap;
+using hl_host::Slabs;
+using hl_host::slabs_of;
 
 // Field 0 = p (primal), 1 = u (dual).
 LayoutMap layout_of(const hl_plan_s* pl, int field) {
@@ -681,7 +683,8 @@ LayoutMap layout_of(const hl_plan_s* pl, int field) {
 // to 64 coefficients through LDS, so that both sides move whole lines: runs of
 // coefficients on the host side, runs of i_1 on the plane side.
 // ---------------------------------------------------------------------------
-constexpr int kConvNodes = 32, kConvCoefs = 64;
+using hl_host::kConvCoefs;
+using hl_host::kConvNodes;
 
 // One slab j_1 in [j0, j0 + jn) of a field component.
 struct ConvMap {
@@ -694,7 +697,7 @@ struct ConvMap {
 };
 
 template <class S, bool TO_PLANES>
-__global__ void __launch_bounds__(256) convert_layout(typename S::View v, double* __restrict__ host, ConvMap m) {
+__global__ void __launch_bounds__(hl_host::kConvItems) convert_layout(typename S::View v, double* __restrict__ host, ConvMap m) {
   __shared__ double tile[kConvNodes * (kConvCoefs + 1)];
   const int t1 = blockIdx.x % m.tiles, r = blockIdx.x / m.tiles;  // tile along j_1, host node j_2 K3 + j_3
   const int j2 = r / m.K3, j3 = r % m.K3;
@@ -713,19 +716,19 @@ __global__ void __launch_bounds__(256) convert_layout(typename S::View v, double
   };
   auto host_at = [&](int i, int c) -> double& { return host[((int64_t)(base + i) * rows + r) * m.nc + c0 + c]; };
   if (TO_PLANES) {
-    for (int x = threadIdx.x; x < cnt * cw; x += 256) tile[x / cw * (kConvCoefs + 1) + x % cw] = host_at(x / cw, x % cw);
+    for (int x = threadIdx.x; x < cnt * cw; x += hl_host::kConvItems) tile[x / cw * (kConvCoefs + 1) + x % cw] = host_at(x / cw, x % cw);
     __syncthreads();
-    for (int x = threadIdx.x; x < kConvNodes * cw; x += 256) {
+    for (int x = threadIdx.x; x < kConvNodes * cw; x += hl_host::kConvItems) {
       const int i = x % kConvNodes, c = x / kConvNodes;
       if (i < cnt) S::store(v, plane(c0 + c), row + i, (typename S::C)tile[i * (kConvCoefs + 1) + c]);
     }
   } else {
-    for (int x = threadIdx.x; x < kConvNodes * cw; x += 256) {
+    for (int x = threadIdx.x; x < kConvNodes * cw; x += hl_host::kConvItems) {
       const int i = x % kConvNodes, c = x / kConvNodes;
       if (i < cnt) tile[i * (kConvCoefs + 1) + c] = (double)S::load(v, plane(c0 + c), row + i);
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < cnt * cw; x += 256) host_at(x / cw, x % cw) = tile[x / cw * (kConvCoefs + 1) + x % cw];
+    for (int x = threadIdx.x; x < cnt * cw; x += hl_host::kConvItems) host_at(x / cw, x % cw) = tile[x / cw * (kConvCoefs + 1) + x % cw];
   }
 }
 
@@ -739,8 +742,8 @@ __global__ void check_finite(const double* __restrict__ x, int64_t n, int* __res
 
 // A staging buffer of at least `bytes`: the plan's own up to kStageKeep (kept
 // until the plan is destroyed), a temporary one beyond.  NULL: no memory.
-constexpr size_t kStageKeep = (size_t)64 << 20;   // kept with the plan
-constexpr size_t kStageMost = (size_t)256 << 20;  // per call; larger components go slab by slab
+constexpr size_t kStageKeep = (size_t)64 << 20;  // kept with the plan
+using hl_host::kStageMost;                       // per call; larger components go slab by slab
 struct Staging {
   void* ptr = nullptr;
   bool own = false;
@@ -776,7 +779,7 @@ hipError_t launch_convert(int precision, void* dev, int ncomp, const LayoutMap& 
   const dim3 grid((unsigned)((int64_t)m.tiles * m.K2 * m.K3), (unsigned)((m.nc + kConvCoefs - 1) / kConvCoefs));
   const auto go = [&](auto tag) {
     using S = decltype(tag);
-    hipLaunchKernelGGL((convert_layout<S, TO_PLANES>), grid, dim3(256), 0, s, S::make(dev, ncomp, L.nc, L.nodes), stage,
+    hipLaunchKernelGGL((convert_layout<S, TO_PLANES>), grid, dim3(hl_host::kConvItems), 0, s, S::make(dev, ncomp, L.nc, L.nodes), stage,
                        m);
   };
   if (precision == HL_FP64)
@@ -788,18 +791,6 @@ hipError_t launch_convert(int precision, void* dev, int ncomp, const LayoutMap& 
   return hipGetLastError();
 }
 
-// The slabs of one component: words per j_1 and j_1 per staged slab (0: even
-// one j_1 is too large for the staging buffer or the launch).
-struct Slabs {
-  int64_t per, jn;
-};
-Slabs slabs_of(const LayoutMap& L) {
-  const int64_t rows = (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
-  Slabs q{rows * L.nc, std::min<int64_t>(L.K[0], (int64_t)(kStageMost / 8) / (rows * L.nc))};
-  if (rows > (int64_t)INT32_MAX / 64) q.jn = 0;
-  while (q.jn > 0 && (q.jn + kConvNodes - 1) / kConvNodes * rows > (int64_t)INT32_MAX) q.jn /= 2;
-  return q;
-}
 ConvMap conv_map(const LayoutMap& L, int comp) {
   ConvMap m{};
   m.d = L.d;

@@ -74,6 +74,33 @@ inline LayoutMap field_layout(int d, int m, const int32_t* K, bool walls, int fi
   return L;
 }
 
+// ---------------------------------------------------------------------------
+// Conversion on the device: a component crosses the bus slab by slab of j_1
+// through a staging buffer, and a workgroup of kConvItems work-items transposes
+// kConvNodes nodes along j_1 (of one j_2, j_3) by kConvCoefs coefficients.
+// ---------------------------------------------------------------------------
+constexpr int kConvNodes = 32, kConvCoefs = 64, kConvItems = 256;
+constexpr int64_t kStageMost = (int64_t)256 << 20;  // staged bytes per slab
+
+// The slabs of one component: words per j_1 and j_1 per staged slab (0: even
+// one j_1 is too large for the staging buffer or the launch, and the host
+// converts the component).
+struct Slabs {
+  int64_t per, jn;
+};
+// Workgroups of a slab of jn j_1, and the most of a launch (fewer than 2^32
+// work-items per dimension).
+inline int64_t conv_blocks(const LayoutMap& L, int64_t jn) {
+  return (jn + kConvNodes - 1) / kConvNodes * (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
+}
+constexpr int64_t kConvMaxBlocks = (int64_t)UINT32_MAX / kConvItems;
+inline Slabs slabs_of(const LayoutMap& L) {
+  const int64_t rows = (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
+  Slabs q{rows * L.nc, std::min<int64_t>(L.K[0], kStageMost / 8 / (rows * L.nc))};
+  while (q.jn > 0 && conv_blocks(L, q.jn) > kConvMaxBlocks) q.jn /= 2;
+  return q;
+}
+
 // BF16 bits of x rounded to nearest even (x finite); the device side of the
 // FP32_COMP format rounds the same way.
 uint16_t bf16_rne(float x) {
