@@ -791,6 +791,8 @@ hipError_t launch_convert(int precision, void* dev, int ncomp, const LayoutMap& 
   return hipGetLastError();
 }
 
+// Bytes per entry of the widest planes of a storage (FP32_COMP: the hi words).
+int word_of(int precision) { return precision == HL_FP64 ? 8 : 4; }
 ConvMap conv_map(const LayoutMap& L, int comp) {
   ConvMap m{};
   m.d = L.d;
@@ -813,7 +815,7 @@ ConvMap conv_map(const LayoutMap& L, int comp) {
 template <bool TO_PLANES>
 hipError_t convert_component(hl_plan_s* pl, int precision, void* dev, int ncomp, int comp, const LayoutMap& L,
                              double* host, hipStream_t s) {
-  const Slabs q = slabs_of(L);
+  const Slabs q = slabs_of(L, word_of(precision));
   if (q.jn < 1) return hipErrorOutOfMemory;
   Staging st(pl, (size_t)(q.per * q.jn) * 8);
   if (!st.ptr) return hipErrorOutOfMemory;
@@ -1588,8 +1590,9 @@ hl_status hl_set_kappa(hl_plan_t plan, const double* kappa_p, const double* kapp
   }
   // Both arrays are checked before either is converted: on the device where
   // the staging buffer holds both, else on the host.
-  const bool both = (words[0] + words[1]) * 8 + 8 <= kStageMost && slabs_of(Ls[0]).jn == Ls[0].K[0] &&
-                    slabs_of(Ls[1]).jn == Ls[1].K[0];
+  const int word = word_of(plan->precision);
+  const bool both = (words[0] + words[1]) * 8 + 8 <= kStageMost && slabs_of(Ls[0], word).jn == Ls[0].K[0] &&
+                    slabs_of(Ls[1], word).jn == Ls[1].K[0];
   Staging buf(plan, both ? (words[0] + words[1]) * 8 + 8 : 0);
   double* staged = static_cast<double*>(buf.ptr);
   if (!both) staged = nullptr;

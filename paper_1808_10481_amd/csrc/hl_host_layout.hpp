@@ -83,8 +83,10 @@ constexpr int kConvNodes = 32, kConvCoefs = 64, kConvItems = 256;
 constexpr int64_t kStageMost = (int64_t)256 << 20;  // staged bytes per slab
 
 // The slabs of one component: words per j_1 and j_1 per staged slab (0: even
-// one j_1 is too large for the staging buffer or the launch, and the host
-// converts the component).
+// one j_1 is too large for the staging buffer or the launch, or the planes, of
+// word_bytes per entry, too large for the kernel's 32-bit byte offsets; the
+// host then converts the component).  A plan's own planes stay below 4 GiB,
+// but the FP64 gradient accumulators of an FP32 plan may be twice as large.
 struct Slabs {
   int64_t per, jn;
 };
@@ -94,9 +96,10 @@ inline int64_t conv_blocks(const LayoutMap& L, int64_t jn) {
   return (jn + kConvNodes - 1) / kConvNodes * (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
 }
 constexpr int64_t kConvMaxBlocks = (int64_t)UINT32_MAX / kConvItems;
-inline Slabs slabs_of(const LayoutMap& L) {
+inline Slabs slabs_of(const LayoutMap& L, int word_bytes) {
   const int64_t rows = (L.d > 1 ? L.K[1] : 1) * (L.d > 2 ? L.K[2] : 1);
   Slabs q{rows * L.nc, std::min<int64_t>(L.K[0], kStageMost / 8 / (rows * L.nc))};
+  if (L.nodes > (int64_t)UINT32_MAX / word_bytes) q.jn = 0;
   while (q.jn > 0 && conv_blocks(L, q.jn) > kConvMaxBlocks) q.jn /= 2;
   return q;
 }
