@@ -190,8 +190,7 @@ struct hl_plan_s {
   void* tab_rev = nullptr;
   void* fp = nullptr;
   void* fu = nullptr;
-  double* gpart = nullptr;
-  int gpart_n = 0;
+  double* gpart = nullptr;     // partial sums, for the workgroups of any tile
   void* stage = nullptr;       // staging of host-layout data (convert_component), at most kStageKeep
   size_t stage_bytes = 0;
   double* dpartial = nullptr;  // norms scratch, kNormBlocks per plane
@@ -1011,15 +1010,6 @@ __global__ void clear_words(double* __restrict__ x, int n) {
 int partials_of(const hl::Grid& g) { return g.per_xcd * hl::kXcds; }
 hipError_t begin_partials(hl_plan_s* pl, const hl::PlanView& v, double** pp, double** pu, hipStream_t s) {
   const int np = 2 * partials_of(v.gp), n = np + 2 * partials_of(v.gu);
-  if (pl->gpart_n < n) {  // other tiles than before: the old sums may still be read
-    hipError_t e = hipStreamSynchronize(s);
-    if (pl->gpart) (void)hipFree(pl->gpart);
-    pl->gpart = nullptr;
-    pl->gpart_n = 0;
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->gpart, (size_t)n * sizeof(double));
-    if (e != hipSuccess) return e;
-    pl->gpart_n = n;
-  }
   hipLaunchKernelGGL(clear_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pl->gpart, n);
   *pp = pl->gpart;
   *pu = pl->gpart + np;
@@ -1063,7 +1053,24 @@ hipError_t upload_table(const hl_plan_s* pl, const std::vector<double>& tab, voi
   return hipMemcpy(*out, f.data(), f.size() * 4, hipMemcpyHostToDevice);
 }
 
-// Gradient resources of a periodic plan (first use only).
+bool build_grids(const hl_plan_s* pl, int32_t tx, int32_t ty, int32_t ygroup, hl::Grid* gp, hl::Grid* gu);
+bool valid_tile(int d, int32_t tx, int32_t ty);
+
+// Words of the partial sums whatever tile hl_set_tile gives the plan: the
+// buffer is never reallocated, so that a gradient call after the first allocates
+// nothing and can be captured, also with another tile.
+size_t partial_words(const hl_plan_s* pl) {
+  int64_t most = 0;
+  for (int32_t tx = 32; tx <= 256; tx += 32)
+    for (int32_t ty = 1; ty <= 8; ++ty) {
+      hl::Grid gp, gu;
+      if (!valid_tile(pl->d, tx, ty) || !build_grids(pl, tx, ty, 1, &gp, &gu)) continue;
+      most = std::max<int64_t>(most, (int64_t)partials_of(gp) + partials_of(gu));
+    }
+  return (size_t)(2 * most);
+}
+
+// Gradient resources of a plan (first use only).
 hl_status ensure_gradient(hl_plan_s* pl) {
   if (pl->tab_dk) return HL_OK;
   std::vector<double> tdk, trev;
@@ -1076,8 +1083,9 @@ hl_status ensure_gradient(hl_plan_s* pl) {
   if (e == hipSuccess) e = upload_table(pl, trev, &pl->tab_rev);
   if (e == hipSuccess) e = hipMalloc(&pl->fp, pbytes);
   if (e == hipSuccess) e = hipMalloc(&pl->fu, ubytes);
+  if (e == hipSuccess) e = hipMalloc((void**)&pl->gpart, partial_words(pl) * sizeof(double));
   if (e != hipSuccess) {
-    for (void** q : {&pl->tab_dk, &pl->tab_rev, &pl->fp, &pl->fu}) {
+    for (void** q : {&pl->tab_dk, &pl->tab_rev, &pl->fp, &pl->fu, (void**)&pl->gpart}) {
       if (*q) (void)hipFree(*q);
       *q = nullptr;
     }
