@@ -165,7 +165,7 @@ struct hl_plan_s {
   int32_t pext[3], uext[3], uoff;
   int64_t pnodes, unodes;
   hl::Grid gp, gu;       // pressure / velocity half-step launch grids
-  int32_t ygroup_req = 0; // 3D tile rows per group asked for (the grids clamp it to their extent)
+  int32_t ygroup_req = 0; // 3D tile rows per group asked for, 0: the kernels' defaults (make_grid)
   hl::KernelSet ks;
   void* dtab = nullptr;
   void* dadj = nullptr;        // transposed half-steps' tables (B^T then A^T), or NULL
@@ -225,7 +225,7 @@ struct hl_batch_s {
   std::vector<void*> bp, bu;          // buffers the descriptors describe
   std::vector<uint64_t> gens;         // the member plans' generations they were built at
   std::vector<hl::PlanView> views;    // per shot (walled shots: the ghost refresh)
-  int32_t tile[3] = {0, 0, 0};        // workgroup shape and 3D y-group of the batched launches
+  int32_t tile[3] = {0, 0, 0};        // workgroup shape and 3D y-group asked for of the batched launches
   bool walls = false;                 // some shot has reflecting walls
   int pblocks = 0, ublocks = 0;
   hipStream_t cap_stream = nullptr;   // graph of kGraphChunk batched steps
@@ -256,10 +256,11 @@ size_t state_bytes(const hl_plan_s* pl) { return (size_t)pl->word_bytes * pl->wo
 
 constexpr int kNormBlocks = 256;
 constexpr int64_t kGraphChunk = 16;   // steps per captured graph (32 kernel nodes)
-#ifndef HL_3D_YGROUP
-#define HL_3D_YGROUP 2
-#endif
-constexpr int32_t kYGroup3 = HL_3D_YGROUP;
+// Default tile rows per y-group in 3D: of the kernels that load their corners
+// directly (variable kappa), and of the staged half-steps, which keep fewer
+// nodes in flight (256^3 FP32 with 2 and 4 rows: pressure 2.32 and 2.26 ms,
+// velocity 2.62 and 2.53 ms).
+constexpr int32_t kYGroup3 = 2, kYGroupStaged = 4;
 
 // Advances a batch's step counter (one work-item; runs after the step's source).
 __global__ void batch_tick(int64_t* counter) {
@@ -1122,7 +1123,7 @@ hl_status ensure_var_gradient(hl_plan_s* pl) {
 
 // Launch grid of one half-step: updates K[] nodes stored at index j + ooff
 // of an array with extents oext, corners from an array with extents sext
-// (lower corner at j + soff).
+// (lower corner at j + soff).  ygroup 0: the kernels' default y-groups.
 bool make_grid(const hl_plan_s* pl, const int32_t* tile, int32_t ygroup, const int32_t* K, const int32_t* oext,
                int32_t ooff, const int32_t* sext, int32_t soff, int64_t onodes, int64_t snodes, hl::Grid* g) {
   int64_t tiles = 1;
@@ -1138,7 +1139,12 @@ bool make_grid(const hl_plan_s* pl, const int32_t* tile, int32_t ygroup, const i
   g->per_xcd = (int32_t)((tiles + hl::kXcds - 1) / hl::kXcds);
   // 3D: tile numbering x, then y in groups of `ygroup` tile rows, then z
   // (z-neighbour planes reused from L2); 1D/2D: plain row-major
-  g->ygroup = pl->d == 3 ? std::max<int32_t>(1, std::min<int32_t>(ygroup, g->nt[1])) : g->nt[1];
+  const auto rows = [&](int32_t by_default) {
+    const int32_t y = ygroup > 0 ? ygroup : by_default;
+    return pl->d == 3 ? std::max<int32_t>(1, std::min<int32_t>(y, g->nt[1])) : g->nt[1];
+  };
+  g->ygroup = rows(kYGroup3);
+  g->ystaged = rows(kYGroupStaged);
   g->ooff = ooff;
   g->soff = soff;
   g->tx = tile[0];
@@ -1328,8 +1334,7 @@ hl_status hl_plan(const hl_problem* prob, hl_plan_t* out) {
     delete pl;
     return fail(HL_ERR_UNSUPPORTED, "hl_plan: (d, m, precision) not built");
   }
-  pl->ygroup_req = kYGroup3;
-  if (!build_grids(pl, pl->ks.tile[0], pl->ks.tile[1], kYGroup3, &pl->gp, &pl->gu)) {
+  if (!build_grids(pl, pl->ks.tile[0], pl->ks.tile[1], 0, &pl->gp, &pl->gu)) {
     delete pl;
     return fail(HL_ERR_UNSUPPORTED, "hl_plan: grid too large for the launch");
   }
@@ -1439,7 +1444,7 @@ hl_status hl_plan_info(hl_plan_t plan, hl_info* out) {
   out->p_words = (int64_t)plan->words_per_coef * plan->nc * plan->pnodes;
   out->tile[0] = plan->gp.tx;
   out->tile[1] = plan->gp.ty;
-  out->ygroup = plan->d == 3 ? plan->gp.ygroup : 0;
+  out->ygroup = plan->d == 3 ? (plan->var_kappa ? plan->gp.ygroup : plan->gp.ystaged) : 0;
   out->reserved = 0;
   out->u_words = (int64_t)plan->words_per_coef * plan->d * plan->nc * plan->unodes;
   return HL_OK;
@@ -1714,7 +1719,7 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
     // primal corners j = r - 1 + e from the K + 1 primal nodes
     hl::Grid gf;
     const int32_t tile[3] = {plan->gu.tx, plan->gu.ty, 1};
-    if (!make_grid(plan, tile, plan->gu.ygroup, plan->uext, plan->uext, 0, plan->pext, -1, plan->unodes,
+    if (!make_grid(plan, tile, plan->ygroup_req, plan->uext, plan->uext, 0, plan->pext, -1, plan->unodes,
                    plan->pnodes, &gf))
       return fail(HL_ERR_UNSUPPORTED, "hl_adjoint_step: grid too large for the launch");
     gf.open = 1;
@@ -1810,7 +1815,7 @@ hl_status hl_set_tile(hl_plan_t plan, int32_t tx, int32_t ty, int32_t ygroup) {
     return fail(HL_ERR_ARG, "hl_set_tile: tx a multiple of 32 in [32, 256], ty >= 1 (1 in 1D), 64 <= tx ty <= 256");
   if (ygroup < 0) return fail(HL_ERR_ARG, "hl_set_tile: ygroup must be >= 0");
   hl::Grid gp, gu;
-  if (!build_grids(plan, tx, ty, ygroup == 0 ? kYGroup3 : ygroup, &gp, &gu))
+  if (!build_grids(plan, tx, ty, ygroup, &gp, &gu))
     return fail(HL_ERR_UNSUPPORTED, "hl_set_tile: grid too large for the launch");
   hipError_t e = hipDeviceSynchronize();  // launches in flight keep their own grid copies; graphs are rebuilt
   if (e != hipSuccess) return hip_fail(e, "hl_set_tile: pending work failed");
@@ -1818,7 +1823,7 @@ hl_status hl_set_tile(hl_plan_t plan, int32_t tx, int32_t ty, int32_t ygroup) {
   ++plan->gen;
   plan->gp = gp;
   plan->gu = gu;
-  plan->ygroup_req = ygroup == 0 ? kYGroup3 : ygroup;
+  plan->ygroup_req = ygroup;
   return HL_OK;
 }
 
@@ -1850,7 +1855,7 @@ hl_status hl_tune(hl_plan_t plan, const void* p, const void* u, int32_t reps, vo
         cand.push_back({sh[0], sh[1], yg});
   }
   float best = -1.0f;
-  std::array<int32_t, 3> pick = {plan->ks.tile[0], plan->ks.tile[1], kYGroup3};
+  std::array<int32_t, 3> pick = {plan->ks.tile[0], plan->ks.tile[1], 0};
   for (size_t c = 0; c < cand.size() && e == hipSuccess; ++c) {
     hl_plan_s trial = *plan;  // grids only; no ownership is taken or released
     if (!build_grids(plan, cand[c][0], cand[c][1], cand[c][2], &trial.gp, &trial.gu)) continue;
@@ -1902,7 +1907,7 @@ hl_status hl_adjoint_step_var(hl_plan_t plan, void* p_bar, void* u_bar, const vo
   hl::PlanView v = view(plan);
   // the gradient kernels run 64 work-items per workgroup (per-lane LDS arrays)
   hl::PlanView v64 = v;
-  if (!build_grids(plan, 64, 1, plan->gp.ygroup, &v64.gp, &v64.gu))
+  if (!build_grids(plan, 64, 1, plan->ygroup_req, &v64.gp, &v64.gu))
     return fail(HL_ERR_ARG, "hl_adjoint_step_var: grid too large");
   hipStream_t s = (hipStream_t)stream;
   if (plan->walls) {
@@ -1912,7 +1917,7 @@ hl_status hl_adjoint_step_var(hl_plan_t plan, void* p_bar, void* u_bar, const vo
     // every slot of the padded array and the ghost fold; A_kappa reads G U_t.
     hl::Grid gf;
     const int32_t tile[3] = {plan->gu.tx, plan->gu.ty, 1};
-    if (!make_grid(plan, tile, plan->gu.ygroup, plan->uext, plan->uext, 0, plan->pext, -1, plan->unodes,
+    if (!make_grid(plan, tile, plan->ygroup_req, plan->uext, plan->uext, 0, plan->pext, -1, plan->unodes,
                    plan->pnodes, &gf))
       return fail(HL_ERR_UNSUPPORTED, "hl_adjoint_step_var: grid too large for the launch");
     const size_t zb = (size_t)kappa_planes(plan) * plan->unodes * plan->tab_bytes;
@@ -2159,7 +2164,7 @@ hl_status hl_batch_step(hl_batch_t batch, void* const* p, void* const* u, int64_
     }
     batch->tile[0] = common ? p0->gp.tx : batch->ks.tile[0];
     batch->tile[1] = common ? p0->gp.ty : batch->ks.tile[1];
-    batch->tile[2] = common ? p0->ygroup_req : kYGroup3;
+    batch->tile[2] = common ? p0->ygroup_req : 0;
     for (int i = 0; i < n; ++i) {
       const hl_plan_s* pl = batch->plans[i];
       views[i] = view(pl);

@@ -146,12 +146,10 @@ inline dim3 block_shape(const Grid& g) { return dim3((unsigned)g.tx, (unsigned)g
 
 inline dim3 grid_shape(const Grid& g) { return dim3((unsigned)(g.per_xcd * kXcds), 1, 1); }
 
-// The grid with tiles of tz node layers in z, and the plan's tile rows per
-// y-group doubled: the staged half-steps keep fewer nodes in flight than their
-// direct-load form, for which the plan's default of 2 was chosen (256^3 FP32:
-// pressure 2.32 -> 2.26 ms, velocity 2.62 -> 2.53 ms).
+// The grid of a staged half-step: tiles of tz node layers in z, and its own
+// y-group.
 inline Grid layered(Grid g, int tz) {
-  g.ygroup = g.nt[1] < 2 * g.ygroup ? g.nt[1] : 2 * g.ygroup;
+  g.ygroup = g.ystaged;
   g.nt[2] = (g.K[2] + tz - 1) / tz;
   g.tiles = g.nt[0] * g.nt[1] * g.nt[2];
   g.per_xcd = (g.tiles + kXcds - 1) / kXcds;

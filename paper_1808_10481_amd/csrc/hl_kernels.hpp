@@ -82,6 +82,7 @@ struct Grid {
   int32_t tiles;      // nt[0] * nt[1] * nt[2]
   int32_t per_xcd;    // ceil(tiles / kXcds)
   int32_t ygroup;     // tile rows per group in the tile numbering, 1..nt[1]
+  int32_t ystaged;    // the same for the staged 3D half-steps (layered())
   int32_t ooff;       // output node j is stored at index j + ooff (0, or 1 in a ghost-padded array)
   int32_t oext[3];    // output array extents
   int32_t soff;       // lower corner of node j at index j + soff (-1 or 0)
