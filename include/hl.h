@@ -270,8 +270,9 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
  * hl_set_tile: tiles of tx x ty nodes (tx a multiple of 32 in [32, 256],
  * ty >= 1, 1 in 1D, 64 <= tx ty <= 256; tx = ty = 0: the default 64 x 4, or
  * 256 in 1D) and, in 3D, tile rows per group in the XCD-banded tile order
- * (ygroup, 0: the default, 4, or 2 with variable kappa; hl_plan_info reports
- * the half-steps' value, clamped to the tile rows there are).  hl_tune: times `reps` steps (after one warm-up
+ * (ygroup, 0: the default, 4, or 2 with variable kappa and at m = 0;
+ * hl_plan_info reports the half-steps' value, clamped to the tile rows there
+ * are).  hl_tune: times `reps` steps (after one warm-up
  * step) for each candidate shape (1D: 256, 128, 64; 2D/3D: 64x4, 64x2, 64x1,
  * 128x2, 128x1, 256x1, 32x8, in 3D each with y-groups 1, 2, 4) on copies of
  * (p, u) in device buffers it allocates for the call and frees, keeps the

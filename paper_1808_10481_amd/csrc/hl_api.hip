@@ -257,7 +257,7 @@ size_t state_bytes(const hl_plan_s* pl) { return (size_t)pl->word_bytes * pl->wo
 constexpr int kNormBlocks = 256;
 constexpr int64_t kGraphChunk = 16;   // steps per captured graph (32 kernel nodes)
 // Default tile rows per y-group in 3D: of the kernels that load their corners
-// directly (variable kappa), and of the staged half-steps, which keep fewer
+// directly (variable kappa, m = 0), and of the staged half-steps, which keep fewer
 // nodes in flight (256^3 FP32 with 2 and 4 rows: pressure 2.32 and 2.26 ms,
 // velocity 2.62 and 2.53 ms).
 constexpr int32_t kYGroup3 = 2, kYGroupStaged = 4;
@@ -1444,7 +1444,7 @@ hl_status hl_plan_info(hl_plan_t plan, hl_info* out) {
   out->p_words = (int64_t)plan->words_per_coef * plan->nc * plan->pnodes;
   out->tile[0] = plan->gp.tx;
   out->tile[1] = plan->gp.ty;
-  out->ygroup = plan->d == 3 ? (plan->var_kappa ? plan->gp.ygroup : plan->gp.ystaged) : 0;
+  out->ygroup = plan->d < 3 ? 0 : plan->ks.staged && !plan->var_kappa ? plan->gp.ystaged : plan->gp.ygroup;
   out->reserved = 0;
   out->u_words = (int64_t)plan->words_per_coef * plan->d * plan->nc * plan->unodes;
   return HL_OK;

@@ -69,6 +69,7 @@ struct KernelSet {
   UHalfFn u_half;
   StepsFn steps;         // 1D FP64 and FP32, NULL otherwise
   int whole;             // 1D: nodes one workgroup holds
+  bool staged;           // 3D, constant kappa: half-steps stage their corners (layered())
   GhostFn ghost;         // ghost-shell refresh of a wall-bounded velocity array
   AdjFn adj_p, adj_u;    // transposed half-steps, NULL where not built
   DotFn p_dot, u_dot;    // inner products with a half-step's increment
@@ -155,6 +156,15 @@ inline Grid layered(Grid g, int tz) {
   g.per_xcd = (g.tiles + kXcds - 1) / kXcds;
   return g;
 }
+// Grid and workgroup of a 3D half-step's shape.
+template <class SH>
+Grid grid_of(const Grid& g) {
+  return SH::DIRECT ? g : layered(g, SH::TZ);
+}
+template <class SH>
+dim3 block_of(int tx, int ty) {
+  return SH::DIRECT ? dim3((unsigned)tx, (unsigned)ty, 1) : dim3((unsigned)(SH::NS * class_items(tx, ty, SH::TZ)));
+}
 
 template <int D, int M, class S>
 hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
@@ -165,21 +175,21 @@ hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
   const typename S::View vu = S::make(u, D, NC, g.snodes);
   if constexpr (D == 3) {
     using SL = PShape<M, S, kLayered>;
-    using S1 = PShape<M, S, kOneLayer>;
-    const Grid gz = layered(g, SL::TZ), g1 = layered(g, 1);
     if constexpr (SL::TZ > 1) {
-      if (gz.tiles >= kLayeredTiles && stage_fits(g.tx, g.ty, SL::TZ, SL::NS, SL::NE)) {
-        hipLaunchKernelGGL((p_half_3d<M, S, kLayered>), grid_shape(gz),
-                           dim3(SL::NS * class_items(g.tx, g.ty, SL::TZ)), 0, s, vp, vu, (const T*)pv.tab, gz);
+      const Grid gz = grid_of<SL>(g);
+      if (gz.tiles >= kLayeredTiles && takes_tile<SL>(g.tx, g.ty)) {
+        hipLaunchKernelGGL((p_half_3d<M, S, kLayered>), grid_shape(gz), block_of<SL>(g.tx, g.ty), 0, s, vp, vu,
+                           (const T*)pv.tab, gz);
         return hipGetLastError();
       }
     }
-    if (stage_fits(g.tx, g.ty, 1, S1::NS, S1::NE))
-      hipLaunchKernelGGL((p_half_3d<M, S, kOneLayer>), grid_shape(g1), dim3(S1::NS * class_items(g.tx, g.ty, 1)), 0, s,
-                         vp, vu, (const T*)pv.tab, g1);
+    using S1 = PShape<M, S, kOneLayer>;
+    const Grid g1 = grid_of<S1>(g);
+    const dim3 block = block_of<S1>(g.tx, g.ty);
+    if (takes_tile<S1>(g.tx, g.ty))
+      hipLaunchKernelGGL((p_half_3d<M, S, kOneLayer>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
     else
-      hipLaunchKernelGGL((p_half_3d<M, S, kAnyTile>), grid_shape(g1), dim3(S1::NS * class_items(g.tx, g.ty, 1)), 0, s,
-                         vp, vu, (const T*)pv.tab, g1);
+      hipLaunchKernelGGL((p_half_3d<M, S, kAnyTile>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
   } else
     hipLaunchKernelGGL((p_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vp, vu, (const T*)pv.tab,
                        g);
@@ -194,10 +204,10 @@ hipError_t launch_u(const PlanView& pv, void* u, const void* p, double wscale, h
   const typename S::View vu = S::make(u, D, NC, g.onodes);
   const typename S::View vp = S::make(p, 1, NC, g.snodes);
   if constexpr (D == 3) {
-    using SH = UShape<M, S, kOneLayer>;
-    const Grid g1 = layered(g, 1);
-    const dim3 block(SH::NS * class_items(g.tx, g.ty, 1));
-    if (stage_fits(g.tx, g.ty, 1, SH::NS, SH::NE))
+    using S1 = UShape<M, S, kOneLayer>;
+    const Grid g1 = grid_of<S1>(g);
+    const dim3 block = block_of<S1>(g.tx, g.ty);
+    if (takes_tile<S1>(g.tx, g.ty))
       hipLaunchKernelGGL((u_half_3d<M, S, kOneLayer>), grid_shape(g1), block, 0, s, vu, vp, (const T*)pv.tab, g1,
                          (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
     else
@@ -292,9 +302,9 @@ hipError_t launch_adjoint_on(const PlanView& pv, const Grid& g, void* out, const
     pt.gp = g;
     return launch_p<3, M, S>(pt, out, in, s);
   } else {
-    const Grid g1 = layered(g, 1);
-    hipLaunchKernelGGL((adjoint_u_3d<M, S>), grid_shape(g1), dim3(kUSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vo,
-                       vi, tab, g1);
+    using SH = UShape<M, S, kAnyTile>;
+    const Grid gf = grid_of<SH>(g);
+    hipLaunchKernelGGL((adjoint_u_3d<M, S>), grid_shape(gf), block_of<SH>(g.tx, g.ty), 0, s, vo, vi, tab, gf);
     return hipGetLastError();
   }
 }
@@ -312,9 +322,10 @@ hipError_t launch_p_dot(const PlanView& pv, const void* pb, const void* u, doubl
   const Grid& g = pv.gp;
   const typename S::View vp = S::make(pb, 1, NC, g.onodes), vu = S::make(u, D, NC, g.snodes);
   if constexpr (D == 3) {
-    const Grid g1 = layered(g, 1);
-    hipLaunchKernelGGL((p_dot_3d<M, S>), grid_shape(g1), dim3(kPSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vp, vu,
-                       (const T*)pv.tab, g1, part);
+    using SH = PShape<M, S, kAnyTile>;
+    const Grid gf = grid_of<SH>(g);
+    hipLaunchKernelGGL((p_dot_3d<M, S>), grid_shape(gf), block_of<SH>(g.tx, g.ty), 0, s, vp, vu, (const T*)pv.tab, gf,
+                       part);
   } else {
     hipLaunchKernelGGL((p_dot<D, M, S>), grid_shape(g), block_shape(g), 0, s, vp, vu, (const T*)pv.tab, g, part);
   }
@@ -327,9 +338,10 @@ hipError_t launch_u_dot(const PlanView& pv, const void* ub, const void* p, doubl
   const Grid& g = pv.gu;
   const typename S::View vu = S::make(ub, D, NC, g.onodes), vp = S::make(p, 1, NC, g.snodes);
   if constexpr (D == 3) {
-    const Grid g1 = layered(g, 1);
-    hipLaunchKernelGGL((u_dot_3d<M, S>), grid_shape(g1), dim3(kUSplit<M, S> * class_items(g.tx, g.ty, 1)), 0, s, vu, vp,
-                       (const T*)pv.tab, g1, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2], part);
+    using SH = UShape<M, S, kAnyTile>;
+    const Grid gf = grid_of<SH>(g);
+    hipLaunchKernelGGL((u_dot_3d<M, S>), grid_shape(gf), block_of<SH>(g.tx, g.ty), 0, s, vu, vp, (const T*)pv.tab, gf,
+                       (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2], part);
   } else {
     hipLaunchKernelGGL((u_dot<D, M, S>), grid_shape(g), block_shape(g), 0, s, vu, vp, (const T*)pv.tab, g,
                        (T)pv.ih[0], (T)pv.ih[1], part);
@@ -510,7 +522,7 @@ void batch_desc(const BatchShot* shots, int n, bool var, std::vector<unsigned ch
     a.tab = (const T*)v.tab;
     a.g = v.gp;
     if constexpr (D == 3)
-      if (!var) a.g = layered(v.gp, 1);
+      if (!var) a.g = grid_of<PShape<M, S, kAnyTile>>(v.gp);
     a.va = var_args<S>(v);
     a.wscale = T(1);
     for (int k = 0; k < 3; ++k) a.ih[k] = (T)v.ih[k];
@@ -529,7 +541,7 @@ void batch_desc(const BatchShot* shots, int n, bool var, std::vector<unsigned ch
     b.tab = (const T*)v.tab;
     b.g = v.gu;
     if constexpr (D == 3)
-      if (!var) b.g = layered(v.gu, 1);
+      if (!var) b.g = grid_of<UShape<M, S, kAnyTile>>(v.gu);
     b.va = a.va;
     b.wscale = T(1);
     for (int k = 0; k < 3; ++k) b.ih[k] = (T)v.ih[k];
@@ -568,13 +580,9 @@ hipError_t launch_batch(const void* desc, int n, int blocks, bool var, dim3 bloc
       return hipErrorInvalidValue;
     }
   } else {
-    // 3D: a workgroup of the half-step's wavefront classes over the tile
-    if constexpr (D == 3) {
-      using SP = PShape<M, S, kAnyTile>;
-      using SU = UShape<M, S, kAnyTile>;
-      block = P ? dim3(SP::NS * class_items((int)block.x, (int)block.y, SP::TZ))
-                : dim3(SU::NS * class_items((int)block.x, (int)block.y, SU::TZ));
-    }
+    if constexpr (D == 3)
+      block = P ? block_of<PShape<M, S, kAnyTile>>((int)block.x, (int)block.y)
+                : block_of<UShape<M, S, kAnyTile>>((int)block.x, (int)block.y);
     if (P)
       hipLaunchKernelGGL((p_half_batch<D, M, S, false>), dim3((unsigned)blocks), block, 0, s, d, n);
     else
@@ -617,6 +625,8 @@ inline bool make_set(KernelSet* out) {
   out->u_half = &launch_u<D, M, S>;
   out->steps = nullptr;
   out->whole = 0;
+  out->staged = false;
+  if constexpr (D == 3) out->staged = !PShape<M, S, kOneLayer>::DIRECT;
   if constexpr (D == 1 && kPlain<S>) {
     out->steps = &launch_steps_1d<M, S>;
     out->whole = kWhole1<M, S>;

@@ -238,7 +238,7 @@ __device__ __forceinline__ void update_outputs_as(const typename S::View& v, uin
 #pragma unroll
   for (int c = 0; c * B < N; ++c) {
     int zero = 0;  // 3D: opaque, so that plane bases are formed here and not all held from the start
-    if constexpr (D == 3) asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+    if constexpr (D == 3 && N > B) asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
 #pragma unroll
     for (int i = 0; i < B; ++i)
       if ((c + 1) * B + i < N) x[(c + 1) & 1][i] = load_output<D, S, NT>(v, plane((c + 1) * B + i) + zero, n0);
@@ -639,19 +639,46 @@ constexpr int stage_any(int ns, int tz) {
 // ANY: tiles that need fewer than NE words skip the rest.
 template <int NS_, int TZ_, int NE_, bool ANY_>
 struct StageShape {
-  static constexpr bool ANY = ANY_;
-  static constexpr int NS = NS_, TZ = TZ_, NE = NE_, CAP = NE_ * NS_ * 256 * TZ_;
+  static constexpr bool ANY = ANY_, DIRECT = false;
+  static constexpr int NS = NS_, TZ = TZ_, NE = NE_, CAP = NE_ * NS_ * 256 * TZ_, LDS = 2 * kStageGroup * CAP;
+};
+// Every work-item loads its own corners (the tile's work-items as they are):
+// m = 0, whose three data (pressure; one for the velocity) are not worth the
+// staging's barriers and address arithmetic.  m = 0, staged / direct: step of
+// 192^3 FP32 130 / 70 us, FP32_COMP 178 / 102 us, FP64 162 / 137 us; transposed
+// step of 161x150x143 FP32_COMP 372 / 125 us.
+struct DirectShape {
+  static constexpr bool DIRECT = true;
+  static constexpr int NS = 1, TZ = 1, LDS = 1;
 };
 // The default tile with its layers, with one layer, and any tile.
-enum StageForm { kLayered, kOneLayer, kAnyTile };
+enum StageForm { kLayered, kOneLayer, kAnyTile, kDirect };
 template <int NS, int TZ, int FORM>
-using ShapeOf = StageShape<NS, FORM == kLayered ? TZ : 1,
-                           FORM == kAnyTile ? stage_any(NS, 1) : stage_few(NS, FORM == kLayered ? TZ : 1),
-                           FORM == kAnyTile>;
+struct ShapeOf {
+  using type = StageShape<NS, FORM == kLayered ? TZ : 1,
+                          FORM == kAnyTile ? stage_any(NS, 1) : stage_few(NS, FORM == kLayered ? TZ : 1),
+                          FORM == kAnyTile>;
+};
+template <int NS, int TZ>
+struct ShapeOf<NS, TZ, kDirect> {
+  using type = DirectShape;
+};
+template <int M>
+constexpr int form3(int form) {
+  return M == 0 ? (int)kDirect : form;
+}
 template <int M, class S, int FORM>
-using PShape = ShapeOf<kPSplit<M, S>, kPLayers<M, S>, FORM>;
+using PShape = typename ShapeOf<kPSplit<M, S>, kPLayers<M, S>, form3<M>(FORM)>::type;
 template <int M, class S, int FORM>
-using UShape = ShapeOf<kUSplit<M, S>, 1, FORM>;
+using UShape = typename ShapeOf<kUSplit<M, S>, 1, form3<M>(FORM)>::type;
+// Whether a shape takes tiles of tx x ty nodes.
+template <class SH>
+__host__ constexpr bool takes_tile(int tx, int ty) {
+  if constexpr (SH::DIRECT)
+    return true;
+  else
+    return stage_fits(tx, ty, SH::TZ, SH::NS, SH::NE);
+}
 
 // One workgroup's tile: this work-item's node and the source nodes of the
 // words it stages.
@@ -718,6 +745,41 @@ struct Stage3 {
   }
 };
 
+// One work-item's node when it loads its own corners.
+struct Direct3 {
+  int32_t j[3];
+  uint32_t cn[8];
+  static constexpr bool active = true;
+  static constexpr int cls = 0;
+  // false: no node (per work-item)
+  __device__ __forceinline__ bool init(const Grid& g, int blk) {
+    if (!node_of_block<3>(g, blk, j)) return false;
+    corner_nodes<3>(g, j, cn);
+    return true;
+  }
+  // For an open grid: corners outside the source array are zero.
+  __device__ __forceinline__ void open_corners(const Grid& g) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int32_t c = j[k] + g.soff + ((e >> k) & 1);
+        if (c < 0 || c >= g.sext[k]) cn[e] = (uint32_t)g.snodes;  // past the plane: the descriptor answers with zero
+      }
+  }
+  __device__ __forceinline__ uint32_t out(const Grid& g) const { return out_index<3>(g, j); }
+};
+template <class SH>
+struct SourceOf {
+  using type = Stage3<SH>;
+};
+template <>
+struct SourceOf<DirectShape> {
+  using type = Direct3;
+};
+template <class SH>
+using Source3 = typename SourceOf<SH>::type;
+
 // Issue the loads of plane pl's staged words.
 template <class S, class SH>
 __device__ __forceinline__ void stage_load(const typename S::View& f, int pl, const Stage3<SH>& st,
@@ -773,6 +835,11 @@ __device__ __forceinline__ void butterfly3(const T* c, int sx, int sxy, T* X) {
 template <typename T>
 __device__ __forceinline__ void pin(T& x) {
   asm volatile("" : "+v"(x));
+}
+// .. of a 3D half-step's accumulators (at m = 0 there is nothing to keep apart)
+template <int M, typename T>
+__device__ __forceinline__ void pin_acc(T& x) {
+  if constexpr (M > 0) pin(x);
 }
 
 // A sum that carries its rounding errors along; the terms of one work-item are
@@ -830,6 +897,46 @@ __device__ __forceinline__ void stage_loop(const typename S::View& f, const Stag
 template <int NQ>
 using StageGroups = std::make_integer_sequence<int, (NQ + kStageGroup - 1) / kStageGroup>;
 
+// The data loop of a work-item that loads its own corners, W - 1 data ahead.
+template <class S>
+__device__ __forceinline__ void direct_load(const typename S::View& f, int pl, const uint32_t* cn, typename S::C* v) {
+  int zero;  // opaque: the plane base is formed here, not hoisted to the kernel start
+  asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+  const typename S::Planes pr = S::planes(f, pl + zero);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = S::bload(pr, cn[e]);
+}
+template <int NQ, class S, int W, int Q, class F>
+__device__ __forceinline__ void direct_datum(const typename S::View& f, const uint32_t* cn, typename S::C (*v)[8],
+                                             F& apply) {
+  // keep the scalar table loads of one datum together (SGPR pressure)
+  if constexpr (NQ > 3) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (Q + W - 1 < NQ) direct_load<S>(f, Q + W - 1, cn, v[(Q + W - 1) % W]);
+  typename S::C X[8];
+  butterfly3<-1>(v[Q % W], 2, 4, X);
+  apply.template operator()<Q>(X);
+}
+template <int NQ, class S, class F, int... Q>
+__device__ __forceinline__ void direct_loop(const typename S::View& f, const uint32_t* cn, F& apply,
+                                            std::integer_sequence<int, Q...>) {
+  // all of m = 0's data at once; one ahead of FP64 words, which wait on memory
+  constexpr int W = NQ <= 3 ? NQ : S::kBytes == 8 ? 2 : 1;
+  typename S::C v[W][8];
+#pragma unroll
+  for (int q = 0; q + 1 < W; ++q) direct_load<S>(f, q, cn, v[q]);
+  (direct_datum<NQ, S, W, Q>(f, cn, v, apply), ...);
+}
+
+// The combinations of data 0 .. NQ - 1 of a node, handed to apply.
+template <int NQ, class S, class SH, class F>
+__device__ __forceinline__ void data_loop(const typename S::View& f, const Source3<SH>& st, typename S::C* lds,
+                                          F& apply) {
+  if constexpr (SH::DIRECT)
+    direct_loop<NQ, S>(f, st.cn, apply, std::make_integer_sequence<int, NQ>{});
+  else
+    stage_loop<NQ, S, SH>(f, st, lds, apply, StageGroups<NQ>{});
+}
+
 template <int N>
 struct IndexList {
   int n;
@@ -866,14 +973,14 @@ struct PApply3 {
     }
 #pragma unroll
     for (int o = 0; o < NC; ++o)
-      if (mine(o)) pin(acc[o]);
+      if (mine(o)) pin_acc<M>(acc[o]);
   }
 };
 
 // DOT: p is not updated; returns this work-item's part of -<p, increment>.
 template <int M, class S, class SH, int CLS, bool DOT, typename TP>
 __device__ __forceinline__ ExactSum p_half_3d_class(const typename S::View& p, const typename S::View& u, TP tab,
-                                                    const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
+                                                    const Grid& g, const Source3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
   constexpr int NC = Dims<3, M>::NC;
   using A = PApply3<M, S, CLS, SH::NS, TP>;
@@ -881,7 +988,7 @@ __device__ __forceinline__ ExactSum p_half_3d_class(const typename S::View& p, c
   f.tab = tab;
 #pragma unroll
   for (int s = 0; s < NC; ++s) f.acc[s] = T(0);
-  stage_loop<3 * NC, S, SH>(u, st, lds, f, StageGroups<3 * NC>{});
+  data_loop<3 * NC, S, SH>(u, st, lds, f);
   const uint32_t n0 = st.out(g);
   if constexpr (DOT) {
     ExactSum d;
@@ -900,8 +1007,8 @@ __device__ __forceinline__ ExactSum p_half_3d_class(const typename S::View& p, c
 
 template <int M, class S, class SH, typename TP, bool DOT = false>
 __device__ __forceinline__ ExactSum p_half_3d_body(typename S::View p, typename S::View u, TP tab, Grid g, int blk) {
-  __shared__ typename S::C lds[2 * kStageGroup * SH::CAP];
-  Stage3<SH> st;
+  __shared__ typename S::C lds[SH::LDS];
+  Source3<SH> st;
   if (!st.init(g, blk)) return {};  // dual q = j - 1 + e
   if (SH::NS == 1 || st.cls == 0)
     return p_half_3d_class<M, S, SH, 0, DOT>(p, u, tab, g, st, lds);
@@ -911,7 +1018,7 @@ __device__ __forceinline__ ExactSum p_half_3d_body(typename S::View p, typename 
 }
 
 template <int M, class S, int FORM>
-__global__ void __launch_bounds__((256 * kPSplit<M, S> * PShape<M, S, FORM>::TZ), HL_WAVES_PER_EU)
+__global__ void __launch_bounds__((256 * PShape<M, S, FORM>::NS * PShape<M, S, FORM>::TZ), HL_WAVES_PER_EU)
     p_half_3d(typename S::View p, typename S::View u, const typename S::C* __restrict__ tab, Grid g) {
   p_half_3d_body<M, S, PShape<M, S, FORM>, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
 }
@@ -950,14 +1057,14 @@ struct UApply3 {
     }
 #pragma unroll
     for (int o = 0; o < NG; ++o)
-      if (mine(o)) pin(Q[o]);
+      if (mine(o)) pin_acc<M>(Q[o]);
   }
 };
 
 template <int M, class S, class SH, int CLS, bool DOT, typename TP>
 __device__ __forceinline__ ExactSum u_half_3d_class(const typename S::View& u, const typename S::View& p, TP tab,
                                                 const Grid& g, typename S::C wscale, const typename S::C* ih,
-                                                const Stage3<SH>& st, typename S::C* lds) {
+                                                const Source3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
   constexpr int NC = Dims<3, M>::NC, MP = M + 1, NG = GSet<3, M>::NG;
   using A = UApply3<M, S, CLS, SH::NS, TP>;
@@ -965,7 +1072,7 @@ __device__ __forceinline__ ExactSum u_half_3d_class(const typename S::View& u, c
   f.tab = tab;
 #pragma unroll
   for (int o = 0; o < NG; ++o) f.Q[o] = T(0);
-  stage_loop<NC, S, SH>(p, st, lds, f, StageGroups<NC>{});
+  data_loop<NC, S, SH>(p, st, lds, f);
   const uint32_t n0 = st.out(g);
   // u_i[s] -= wscale * (s_i + 1) / h_i * Q[s + e_i]
   const T w[3] = {wscale * ih[0], wscale * ih[1], wscale * ih[2]};
@@ -995,8 +1102,8 @@ __device__ __forceinline__ ExactSum u_half_3d_body(typename S::View u, typename 
                                                typename S::C wscale, typename S::C ih0, typename S::C ih1,
                                                typename S::C ih2, int blk) {
   using T = typename S::C;
-  __shared__ T lds[2 * kStageGroup * SH::CAP];
-  Stage3<SH> st;
+  __shared__ T lds[SH::LDS];
+  Source3<SH> st;
   if (!st.init(g, blk)) return {};  // primal j = q + e
   const T ih[3] = {ih0, ih1, ih2};
   if (SH::NS == 1 || st.cls == 0)
@@ -1007,7 +1114,7 @@ __device__ __forceinline__ ExactSum u_half_3d_body(typename S::View u, typename 
 }
 
 template <int M, class S, int FORM>
-__global__ void __launch_bounds__((256 * kUSplit<M, S>), HL_WAVES_PER_EU)
+__global__ void __launch_bounds__((256 * UShape<M, S, FORM>::NS), HL_WAVES_PER_EU)
     u_half_3d(typename S::View u, typename S::View p, const typename S::C* __restrict__ tab, Grid g,
               typename S::C wscale, typename S::C ih0, typename S::C ih1, typename S::C ih2) {
   u_half_3d_body<M, S, UShape<M, S, FORM>, const typename S::C* __restrict__>(u, p, tab, g, wscale, ih0, ih1, ih2,

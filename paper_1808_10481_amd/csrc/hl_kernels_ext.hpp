@@ -150,31 +150,33 @@ struct AApply3 {
     }
 #pragma unroll
     for (int o = 0; o < NO; ++o)
-      if (mine(o)) pin(acc[o]);
+      if (mine(o)) pin_acc<M>(acc[o]);
   }
 };
 
 template <int M, class S, class SH, int CLS, typename TP>
 __device__ __forceinline__ void adjoint_u_3d_class(const typename S::View& out, const typename S::View& in, TP tab,
-                                                   const Grid& g, const Stage3<SH>& st, typename S::C* lds) {
+                                                   const Grid& g, const Source3<SH>& st, typename S::C* lds) {
   using T = typename S::C;
   using A = AApply3<M, S, CLS, SH::NS, TP>;
   A f;
   f.tab = tab;
 #pragma unroll
   for (int o = 0; o < A::NO; ++o) f.acc[o] = T(0);
-  stage_loop<A::NC, S, SH>(in, st, lds, f, StageGroups<A::NC>{});
+  data_loop<A::NC, S, SH>(in, st, lds, f);
   update_outputs<3, S, A::kOut.n>(g, out, st.out(g), [](int k) { return A::kOut.v[k]; },
                                   [&](int k, T x) { return x - f.acc[A::kOut.v[k]]; });
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__((256 * kUSplit<M, S>)) adjoint_u_3d(typename S::View out, typename S::View in,
-                                                                      const typename S::C* __restrict__ tab, Grid g) {
+__global__ void __launch_bounds__((256 * UShape<M, S, kAnyTile>::NS)) adjoint_u_3d(
+    typename S::View out, typename S::View in, const typename S::C* __restrict__ tab, Grid g) {
   using SH = UShape<M, S, kAnyTile>;
-  __shared__ typename S::C lds[2 * kStageGroup * SH::CAP];
-  Stage3<SH> st;
+  __shared__ typename S::C lds[SH::LDS];
+  Source3<SH> st;
   if (!st.init(g, blockIdx.x)) return;
+  if constexpr (SH::DIRECT)
+    if (g.open) st.open_corners(g);
   if (SH::NS == 1 || st.cls == 0)
     adjoint_u_3d_class<M, S, SH, 0>(out, in, tab, g, st, lds);
   else if constexpr (SH::NS > 1)
@@ -259,19 +261,19 @@ __global__ void __launch_bounds__(256) u_dot(typename S::View ub, typename S::Vi
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__((256 * kPSplit<M, S>)) p_dot_3d(typename S::View pb, typename S::View u,
-                                                                  const typename S::C* __restrict__ tab, Grid g,
-                                                                  double* part) {
+__global__ void __launch_bounds__((256 * PShape<M, S, kAnyTile>::NS)) p_dot_3d(typename S::View pb,
+                                                                               typename S::View u,
+                                                                               const typename S::C* __restrict__ tab,
+                                                                               Grid g, double* part) {
   add_block_sum(p_half_3d_body<M, S, PShape<M, S, kAnyTile>, const typename S::C* __restrict__, true>(pb, u, tab, g,
                                                                                                       blockIdx.x),
                 part);
 }
 
 template <int M, class S>
-__global__ void __launch_bounds__((256 * kUSplit<M, S>)) u_dot_3d(typename S::View ub, typename S::View p,
-                                                                  const typename S::C* __restrict__ tab, Grid g,
-                                                                  typename S::C ih0, typename S::C ih1,
-                                                                  typename S::C ih2, double* part) {
+__global__ void __launch_bounds__((256 * UShape<M, S, kAnyTile>::NS)) u_dot_3d(
+    typename S::View ub, typename S::View p, const typename S::C* __restrict__ tab, Grid g, typename S::C ih0,
+    typename S::C ih1, typename S::C ih2, double* part) {
   add_block_sum(u_half_3d_body<M, S, UShape<M, S, kAnyTile>, const typename S::C* __restrict__, true>(
                     ub, p, tab, g, typename S::C(1), ih0, ih1, ih2, blockIdx.x),
                 part);
@@ -1890,7 +1892,7 @@ __device__ __forceinline__ ShotHalf<S> shot_desc(const ShotHalf<S>* __restrict__
 }
 
 template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kPSplit<M, S> : 256), HL_WAVES_PER_EU)
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * PShape<M, S, kAnyTile>::NS : 256), HL_WAVES_PER_EU)
     p_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;
@@ -1906,7 +1908,7 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kPSplit<M, S> : 256), 
 }
 
 template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * kUSplit<M, S> : 256), HL_WAVES_PER_EU)
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * UShape<M, S, kAnyTile>::NS : 256), HL_WAVES_PER_EU)
     u_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;

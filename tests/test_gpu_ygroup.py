@@ -1,6 +1,6 @@
 """The y-group of 3D plans: hl_plan_info reports what the half-steps run, an
 explicit value (hl_set_tile) is used as given, and 0 is the default: 4, or 2
-with variable kappa."""
+with variable kappa and at m = 0."""
 
 import sys
 
@@ -34,3 +34,11 @@ def test_reported_y_group(m):
     plan.set_kappa(None, None)
     plan.set_tile()
     assert plan.info.ygroup == 4
+
+
+def test_default_at_m0():
+    print("[ygroup] m=0", file=sys.stderr, flush=True)
+    plan = hl.Plan(3, 0, (5, 37, 3))
+    for given, used in ((0, 2), (1, 1), (4, 4)):
+        plan.set_tile(64, 4, given)
+        assert plan.info.ygroup == used
