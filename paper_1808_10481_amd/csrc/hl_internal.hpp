@@ -166,6 +166,12 @@ dim3 block_of(int tx, int ty) {
   return SH::DIRECT ? dim3((unsigned)tx, (unsigned)ty, 1) : dim3((unsigned)(SH::NS * class_items(tx, ty, SH::TZ)));
 }
 
+// The form for tiles that form F's shape SH does not take (direct: none).
+template <class SH>
+constexpr int any_form(int f) {
+  return SH::DIRECT ? f : (int)kAnyTile;
+}
+
 template <int D, int M, class S>
 hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
   using T = typename S::C;
@@ -189,7 +195,7 @@ hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
     if (takes_tile<S1>(g.tx, g.ty))
       hipLaunchKernelGGL((p_half_3d<M, S, kOneLayer>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
     else
-      hipLaunchKernelGGL((p_half_3d<M, S, kAnyTile>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
+      hipLaunchKernelGGL((p_half_3d<M, S, any_form<S1>(kOneLayer)>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
   } else
     hipLaunchKernelGGL((p_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vp, vu, (const T*)pv.tab,
                        g);
@@ -211,7 +217,7 @@ hipError_t launch_u(const PlanView& pv, void* u, const void* p, double wscale, h
       hipLaunchKernelGGL((u_half_3d<M, S, kOneLayer>), grid_shape(g1), block, 0, s, vu, vp, (const T*)pv.tab, g1,
                          (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
     else
-      hipLaunchKernelGGL((u_half_3d<M, S, kAnyTile>), grid_shape(g1), block, 0, s, vu, vp, (const T*)pv.tab, g1,
+      hipLaunchKernelGGL((u_half_3d<M, S, any_form<S1>(kOneLayer)>), grid_shape(g1), block, 0, s, vu, vp, (const T*)pv.tab, g1,
                          (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
   } else
     hipLaunchKernelGGL((u_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vu, vp, (const T*)pv.tab,
@@ -522,7 +528,7 @@ void batch_desc(const BatchShot* shots, int n, bool var, std::vector<unsigned ch
     a.tab = (const T*)v.tab;
     a.g = v.gp;
     if constexpr (D == 3)
-      if (!var) a.g = grid_of<PShape<M, S, kAnyTile>>(v.gp);
+      if (!var) a.g = grid_of<PShape<M, S, kBatchForm<M, S>>>(v.gp);
     a.va = var_args<S>(v);
     a.wscale = T(1);
     for (int k = 0; k < 3; ++k) a.ih[k] = (T)v.ih[k];
@@ -541,7 +547,7 @@ void batch_desc(const BatchShot* shots, int n, bool var, std::vector<unsigned ch
     b.tab = (const T*)v.tab;
     b.g = v.gu;
     if constexpr (D == 3)
-      if (!var) b.g = grid_of<UShape<M, S, kAnyTile>>(v.gu);
+      if (!var) b.g = grid_of<UShape<M, S, kBatchForm<M, S>>>(v.gu);
     b.va = a.va;
     b.wscale = T(1);
     for (int k = 0; k < 3; ++k) b.ih[k] = (T)v.ih[k];
@@ -579,10 +585,25 @@ hipError_t launch_batch(const void* desc, int n, int blocks, bool var, dim3 bloc
     } else {
       return hipErrorInvalidValue;
     }
+  } else if constexpr (D == 3) {
+    constexpr int F = kBatchForm<M, S>;
+    const int tx = (int)block.x, ty = (int)block.y;  // the shots' common tile
+    if constexpr (P) {
+      using SH = PShape<M, S, F>;
+      if (takes_tile<SH>(tx, ty))
+        hipLaunchKernelGGL((p_half_batch<D, M, S, false, F>), dim3((unsigned)blocks), block_of<SH>(tx, ty), 0, s, d, n);
+      else
+        hipLaunchKernelGGL((p_half_batch<D, M, S, false, any_form<SH>(F)>), dim3((unsigned)blocks),
+                           block_of<SH>(tx, ty), 0, s, d, n);
+    } else {
+      using SH = UShape<M, S, F>;
+      if (takes_tile<SH>(tx, ty))
+        hipLaunchKernelGGL((u_half_batch<D, M, S, false, F>), dim3((unsigned)blocks), block_of<SH>(tx, ty), 0, s, d, n);
+      else
+        hipLaunchKernelGGL((u_half_batch<D, M, S, false, any_form<SH>(F)>), dim3((unsigned)blocks),
+                           block_of<SH>(tx, ty), 0, s, d, n);
+    }
   } else {
-    if constexpr (D == 3)
-      block = P ? block_of<PShape<M, S, kAnyTile>>((int)block.x, (int)block.y)
-                : block_of<UShape<M, S, kAnyTile>>((int)block.x, (int)block.y);
     if (P)
       hipLaunchKernelGGL((p_half_batch<D, M, S, false>), dim3((unsigned)blocks), block, 0, s, d, n);
     else

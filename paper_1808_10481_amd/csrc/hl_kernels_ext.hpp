@@ -1891,8 +1891,21 @@ __device__ __forceinline__ ShotHalf<S> shot_desc(const ShotHalf<S>* __restrict__
   return d;
 }
 
-template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * PShape<M, S, kAnyTile>::NS : 256), HL_WAVES_PER_EU)
+// Form of a 3D batch's half-steps for the default tile.  Shots are small grids
+// and fill the 64-wide tiles badly.  FP32, m <= 2, loads corners directly: they
+// hit in the caches, and a tile's staging is not shared by enough nodes to pay
+// for its barriers.  Otherwise the corners are staged, with the default tile's
+// LDS (37 KB for the FP64 pressure side at m <= 2, against 61 KB of the any-tile
+// form, which fits two workgroups per CU instead of four).  16 steps of 24
+// shots, any-tile / default-tile staged / direct: m = 2 FP32 16^3 2822 / 1946 /
+// 1496 us, 40x36x30 10196 / 8279 / 7281 us; m = 1 FP64 16^3 1390 / 875 / 1010 us,
+// 40x36x30 5720 / 3081 / 3915 us.
+template <int M, class S>
+constexpr int kBatchForm = sizeof(typename S::C) == 4 && M <= 2 ? (int)kDirect : (int)kOneLayer;
+
+// FORM: of the 3D half-steps with constant kappa.
+template <int D, int M, class S, bool VAR, int FORM = kOneLayer>
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * PShape<M, S, FORM>::NS : 256), HL_WAVES_PER_EU)
     p_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;
@@ -1902,13 +1915,13 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * PShape<M, S, kAnyTile>
   if constexpr (VAR)
     p_half_var_body<D, M, G>(out, in, kap, sh.g, sh.va, blk);
   else if constexpr (D == 3)
-    p_half_3d_body<M, G, PShape<M, S, kAnyTile>>(out, in, tab, sh.g, blk);
+    p_half_3d_body<M, G, PShape<M, S, FORM>>(out, in, tab, sh.g, blk);
   else
     p_half_body<D, M, G>(out, in, tab, sh.g, blk);
 }
 
-template <int D, int M, class S, bool VAR>
-__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * UShape<M, S, kAnyTile>::NS : 256), HL_WAVES_PER_EU)
+template <int D, int M, class S, bool VAR, int FORM = kOneLayer>
+__global__ void __launch_bounds__((!VAR && D == 3 ? 256 * UShape<M, S, FORM>::NS : 256), HL_WAVES_PER_EU)
     u_half_batch(const ShotHalf<S>* __restrict__ shots, int n) {
   const ShotHalf<S> sh = shot_desc(shots, shot_of(shots, n, blockIdx.x));
   const int blk = (int)blockIdx.x - sh.first_block;
@@ -1918,7 +1931,7 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * UShape<M, S, kAnyTile>
   if constexpr (VAR)
     u_half_var_body<D, M, G>(out, in, kap, sh.g, sh.va, sh.wscale, blk);
   else if constexpr (D == 3)
-    u_half_3d_body<M, G, UShape<M, S, kAnyTile>>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
+    u_half_3d_body<M, G, UShape<M, S, FORM>>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
   else
     u_half_body<D, M, G>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
 }
