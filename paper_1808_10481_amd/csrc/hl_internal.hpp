@@ -300,7 +300,13 @@ hipError_t launch_adjoint_on(const PlanView& pv, const Grid& g, void* out, const
   const typename S::View vi = S::make(in, PTYPE ? D : 1, NC, g.snodes);
   const T* tab = (const T*)pv.adj_tab;
   if constexpr (D < 3) {
-    hipLaunchKernelGGL((adjoint_half<D, M, S, PTYPE>), grid_shape(g), block_shape(g), 0, s, vo, vi, tab, g);
+    if constexpr (!PTYPE) {
+      if (g.open) {
+        hipLaunchKernelGGL((adjoint_half<D, M, S, PTYPE, true>), grid_shape(g), block_shape(g), 0, s, vo, vi, tab, g);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((adjoint_half<D, M, S, PTYPE, false>), grid_shape(g), block_shape(g), 0, s, vo, vi, tab, g);
     return hipGetLastError();
   } else if constexpr (PTYPE) {  // the pressure half-step on the transposed table
     PlanView pt = pv;

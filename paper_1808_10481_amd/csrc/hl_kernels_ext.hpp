@@ -21,9 +21,10 @@ namespace hl {
 // velocity component i on either side), because every interpolant coefficient
 // that links them has the parity of that component's derivative.  So, as in
 // the forward half-steps, an output takes one sigma / delta combination of the
-// 2^D corners of each datum times one table entry: 2^D times fewer multiply-
-// adds than a dense block per corner (2D m = 2 512^2 FP64 16 + 17 us; 34 + 37 us
-// with dense blocks; 3D m = 2 17496 multiply-adds per node and half-step against 2187).
+// 2^D corners of each datum times one table entry (1D: both corners, each times
+// the entry with its sign): 2^D times fewer multiply-adds than a dense block per
+// corner (2D m = 2 512^2 FP64 16 + 17 us; 34 + 37 us with dense blocks; 3D m = 2
+// 17496 multiply-adds per node and half-step against 2187).
 //   PTYPE = true:  out = Pb (1 component), in = Ub (D components)
 //   PTYPE = false: out = Ub (D components), in = Pb (1 component)
 // Table: entry (t, o), datum t = (input component, c), output o = (output
@@ -37,7 +38,8 @@ namespace hl {
 // a wall contribute nothing), then the fold G^T (ghost_fold).  B writes no
 // ghost, so the ghost slots of Ub are held at zero.
 // ---------------------------------------------------------------------------
-template <int D, int M, class S, bool PTYPE>
+// OPEN: an open grid (a kernel of its own, so that the others hold no code for it).
+template <int D, int M, class S, bool PTYPE, bool OPEN>
 __global__ void __launch_bounds__(256) adjoint_half(typename S::View out, typename S::View in,
                                                     const typename S::C* __restrict__ tab, Grid g) {
   static_assert(D <= 2, "3D uses the staged kernels");
@@ -48,10 +50,10 @@ __global__ void __launch_bounds__(256) adjoint_half(typename S::View out, typena
   uint32_t cn[NE];
   corner_nodes<D>(g, j, cn);
   bool in_grid[NE];
+  if constexpr (OPEN) {
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    in_grid[e] = true;
-    if (g.open) {
+    for (int e = 0; e < NE; ++e) {
+      in_grid[e] = true;
 #pragma unroll
       for (int k = 0; k < D; ++k) {
         const int c = j[k] + g.soff + ((e >> k) & 1);
@@ -62,11 +64,39 @@ __global__ void __launch_bounds__(256) adjoint_half(typename S::View out, typena
   }
   auto corner = [&](int t, int e) {
     const T x = S::load(in, t, cn[e]);
-    return in_grid[e] ? x : T(0);
+    if constexpr (OPEN) return in_grid[e] ? x : T(0);
+    return x;
   };
-  T acc[NO], vn[NE];  // vn: the next datum's corners, loaded one datum ahead
+  const auto update = [&](const T* acc) {
+    update_outputs<D, S, NO>(g, out, out_index<D>(g, j), [](int o) { return o; }, [&](int o, T x) { return x - acc[o]; });
+  };
+  T acc[NO];
 #pragma unroll
   for (int o = 0; o < NO; ++o) acc[o] = T(0);
+  if constexpr (D == 1) {
+    // Two corners: sums and differences save little and round more than each
+    // corner's own products (one half-step FP32 m = 1: 1.2 times as far off
+    // FP64), and all data are few enough to be loaded at once.
+    T v[NE][NC];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int t = 0; t < NC; ++t) v[e][t] = corner(t, e);
+#pragma unroll
+    for (int e = 0; e < NE; ++e)  // corner by corner: their sums cancel for large m
+#pragma unroll
+      for (int t = 0; t < NC; ++t) {
+        // keep the scalar table loads of one datum together (SGPR pressure)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+          const T w = tab[t * NO + o];
+          acc[o] = fma(e == 0 && ((o + t + 1) & 1) ? -w : w, v[e][t], acc[o]);
+        }
+      }
+    return update(acc);
+  }
+  T vn[NE];  // the next datum's corners, loaded one datum ahead
 #pragma unroll
   for (int e = 0; e < NE; ++e) vn[e] = corner(0, e);
 #pragma unroll
@@ -103,7 +133,7 @@ __global__ void __launch_bounds__(256) adjoint_half(typename S::View out, typena
       acc[o] = fma(tab[t * NO + o], X[k], acc[o]);
     }
   }
-  update_outputs<D, S, NO>(g, out, out_index<D>(g, j), [](int o) { return o; }, [&](int o, T x) { return x - acc[o]; });
+  update(acc);
 }
 
 // Ub -= A^T Pb in 3D: the velocity half-step's staging and wavefront classes
