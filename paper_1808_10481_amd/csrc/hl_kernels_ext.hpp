@@ -759,15 +759,19 @@ __device__ __forceinline__ void var_series_tail(const typename S::View& kv, uint
     var_series_tail<D, M, VEL, J - 1, S>(kv, n0, t, va, add);
   }
 }
+// Steps taken unrolled (m >= 4: none, full products throughout: one copy of an
+// already long product; the last steps' own copies spill) and in the loop.
+template <int D, int M, bool VEL>
+constexpr int kSeriesTop = M >= 4 ? 0 : kNeedTop<D, M, VEL>;
+template <int D, int M, bool VEL>
+constexpr int kSeriesLoops = VK<D, M>::KMAX > kSeriesTop<D, M, VEL> ? VK<D, M>::KMAX - kSeriesTop<D, M, VEL> : 0;
 template <int D, int M, bool VEL, class S, class F>
 __device__ __forceinline__ void var_series(const typename S::View& kv, uint32_t n0, typename S::C* t,
                                            const VarArgs<typename S::C>& va, F& add) {
   using T = typename S::C;
-  // m >= 4: full products throughout (one copy of an already long product; the
-  // last steps' own copies spill)
-  constexpr int KMAX = VK<D, M>::KMAX, TOP = M >= 4 ? 0 : kNeedTop<D, M, VEL>;
+  constexpr int KMAX = VK<D, M>::KMAX, TOP = kSeriesTop<D, M, VEL>;
 #pragma unroll 1
-  for (int k = 1; k <= KMAX - TOP; ++k) {
+  for (int k = 1; k <= kSeriesLoops<D, M, VEL>; ++k) {
     T l[VK<D, M>::NP];
     lap_coef<D, M, VEL, KMAX>(t, l, va.ih, va.ratio[k]);
     tprod_fwd<D, M, VEL, KMAX, S>(kv, n0, l, t);
@@ -836,7 +840,10 @@ __device__ __forceinline__ void u_half_var_body(typename S::View u, typename S::
   for (int b = 0; b < NP; ++b) {
     gk[b] *= va.w0;
     q[b] = gk[b];
-    pin(q[b]);  // rounded before the first t_k is added, also where the series is unrolled from k = 1
+    // rounded before the first t_k is added also where that addition is not in
+    // a loop (which keeps them apart by itself); with a single term the product
+    // and the sum are one multiply-add, which rounds less
+    if constexpr (VK<D, M>::KMAX > 1 && kSeriesLoops<D, M, true> < 2) pin(q[b]);
   }
   auto add = [&](const T* x) {
 #pragma unroll
