@@ -1410,11 +1410,14 @@ template <int D, int M, typename T>
 constexpr bool kGradStage = sizeof(T) * VK<D, M>::NP >= 512;
 // The lam_k kept in registers: polynomials of at most 288 bytes (up to FP64 2D
 // m = 2 and FP32 3D m = 1); longer ones would spill, and recompute.  One
-// transposed step, recomputed / kept: 2D m = 2 192 x 160 FP64 116 / 95 us, FP32
-// 101 / 78 us; 512^2 FP64 568 / 500 us, FP32 310 / 265 us; 3D m = 1 48^3 FP32
-// 553 / 459 us; 2D m = 1 256^2 FP64 44 / 41 us.
+// transposed step, recomputed / kept: 2D m = 2 192 x 160 FP64 111 / 100 us, FP32
+// 98 / 78 us; 512^2 FP64 564 / 531 us, FP32 302 / 266 us; 3D m = 1 40^3 FP32
+// 343 / 288 us.
 template <int D, int M, typename T>
 constexpr bool kKeepLam = sizeof(T) * VK<D, M>::NP <= 288 && VK<D, M>::KMAX <= 4;
+// Whether g_1 of the kept form waits in LDS (grad_forward).
+template <int D, int M, typename T>
+constexpr bool kKeepG1 = kKeepLam<D, M, T> && (VK<D, M>::KMAX > 1);
 // Wavefronts per SIMD asked for: 2D FP32 fits its kept lam_k in half the
 // registers to within two (left to itself the compiler takes those two and one
 // wavefront runs per SIMD: 326 us at 512^2).
@@ -1422,13 +1425,15 @@ template <int D, int M, typename T>
 constexpr int kGradWaves = D == 2 && sizeof(T) == 4 && kKeepLam<D, M, T> ? 2 : 1;
 
 // grad_A += sum_b lam_{A+b} g_b (the kappa_A derivative of <lam, T[kappa g]>).
-// lam and g on the coefficients of need <= J.
-template <int D, int M, bool VEL, int J, int A, typename T>
+// lam and g on the coefficients of need <= J.  OWN: the sum over b is formed by
+// itself and then added.
+template <int D, int M, bool VEL, int J, bool OWN, int A, typename T>
 __device__ __forceinline__ void corr_term(const T* lam, const T* g, const LaneLds<T>& L, int gs) {
   if constexpr (kNeed<D, M, VEL>.n[A] > J) return;
   constexpr int N2 = 2 * M + 2, AX = A % N2, AY = (A / N2) % N2, AZ = A / (N2 * N2);
   constexpr int NY = D > 1 ? N2 : 1, NZ = D > 2 ? N2 : 1, NP = VK<D, M>::NP;
-  T acc = L(gs, A, NP);
+  const T before = L(gs, A, NP);
+  T acc = OWN ? T(0) : before;
 #pragma unroll
   for (int bz = 0; bz + AZ < NZ; ++bz)
 #pragma unroll
@@ -1438,18 +1443,18 @@ __device__ __forceinline__ void corr_term(const T* lam, const T* g, const LaneLd
         const int hi = (bx + AX) + N2 * ((by + AY) + N2 * (bz + AZ));
         if (kNeed<D, M, VEL>.n[hi] <= J) acc = fma(lam[hi], g[bx + N2 * (by + N2 * bz)], acc);
       }
-  L(gs, A, NP) = acc;
+  L(gs, A, NP) = OWN ? before + acc : acc;
 }
 
-template <int D, int M, bool VEL, int J, typename T, int... A>
+template <int D, int M, bool VEL, int J, bool OWN, typename T, int... A>
 __device__ __forceinline__ void corr_terms(const T* lam, const T* g, const LaneLds<T>& L, int gs,
                                            std::integer_sequence<int, A...>) {
-  (corr_term<D, M, VEL, J, A>(lam, g, L, gs), ...);
+  (corr_term<D, M, VEL, J, OWN, A>(lam, g, L, gs), ...);
 }
 
-template <int D, int M, bool VEL, int J, typename T>
+template <int D, int M, bool VEL, int J, bool OWN = false, typename T>
 __device__ __forceinline__ void corr(const T* lam, const T* g, const LaneLds<T>& L, int gs) {
-  corr_terms<D, M, VEL, J>(lam, g, L, gs, std::make_integer_sequence<int, VK<D, M>::NP>{});
+  corr_terms<D, M, VEL, J, OWN>(lam, g, L, gs, std::make_integer_sequence<int, VK<D, M>::NP>{});
 }
 
 // out = sc Lap^T f: sc sum_i (b_i - 1) b_i / h_i^2 f_{b - 2 e_i}; f zero off
@@ -1478,8 +1483,7 @@ __device__ __forceinline__ void lapT_coef(const T* f, T* out, const T* ih, T sc)
 // Kept form: lam_k lives on need <= J = kmax - k, so with g_k on the same set
 // each product is formed on it; lam_kmax .. lam_0 in registers, then one pass
 // over t_k.  Multiply-adds of 2D m = 2 against recomputing t_k with full
-// products: 3933 of 7497 (pressure), 3522 of 6174.  192 x 160 FP64, where a
-// SIMD has one wavefront at most, 36 + 32 us against 47 + 41.
+// products: 3933 of 7497 (pressure), 3522 of 6174.
 template <int D, int M, bool PSIDE, int K, class S>
 __device__ __forceinline__ void lam_back(const typename S::View& kv, uint32_t n0, const typename S::C* yc,
                                          const VarArgs<typename S::C>& va, typename S::C (*lam)[VK<D, M>::NP]) {
@@ -1507,9 +1511,25 @@ __device__ __forceinline__ void grad_forward(const typename S::View& kv, uint32_
     constexpr int NP = VK<D, M>::NP, J = VK<D, M>::KMAX - K;
     T l[NP];
     lap_coef<D, M, !PSIDE, J>(t, l, va.ih, va.ratio[K]);  // g_k
-    corr<D, M, !PSIDE, J>(lam[K], l, L, gs);
+    // The terms fall with k, and adding a later k's products to the sum of an
+    // earlier one would round at the size of that sum: k = 1 comes last, its
+    // g_1 waiting in the LDS slot after gs (FP32 3D m = 1, gradient of the
+    // velocity side off FP64: 1.6e-7 so, 2.4e-7 with k ascending).
+    if constexpr (K == 1 && kKeepG1<D, M, T>) {
+#pragma unroll
+      for (int b = 0; b < NP; ++b)
+        if (kNeed<D, M, !PSIDE>.n[b] <= J) L(gs + 1, b, NP) = l[b];
+    } else {
+      corr<D, M, !PSIDE, J, (K > 2)>(lam[K], l, L, gs);
+    }
     if constexpr (K < VK<D, M>::KMAX) tprod_grouped<D, M, !PSIDE, J, false, S>(kv, n0, l, t);
     grad_forward<D, M, PSIDE, K + 1, S>(kv, n0, L, gs, va, lam, t);
+    if constexpr (K == 1 && kKeepG1<D, M, T>) {
+#pragma unroll
+      for (int b = 0; b < NP; ++b)
+        if (kNeed<D, M, !PSIDE>.n[b] <= J) l[b] = L(gs + 1, b, NP);
+      corr<D, M, !PSIDE, J>(lam[1], l, L, gs);
+    }
   }
 }
 
@@ -1577,7 +1597,7 @@ __global__ void __launch_bounds__(64, (kGradWaves<D, M, typename S::C>)) grad_p_
   constexpr int N2 = 2 * M + 2, MP = M + 1, NP = VK<D, M>::NP, NC = Dims<D, M>::NC;
   constexpr bool STAGE = kGradStage<D, M, T>;
   constexpr int FS = 0, T0S = 1, GS = STAGE ? 2 : 0;  // LDS slots
-  __shared__ T lds[(STAGE ? 3 : 1) * NP * 64];
+  __shared__ T lds[(STAGE ? 3 : kKeepG1<D, M, T> ? 2 : 1) * NP * 64];
   const LaneLds<T> L{lds, (int)threadIdx.x};
   int32_t j[3];
   if (!node_of_block<D>(g, blockIdx.x, j)) return;
@@ -1648,7 +1668,7 @@ __global__ void __launch_bounds__(64, (kGradWaves<D, M, typename S::C>)) grad_u_
   constexpr int N2 = 2 * M + 2, MP = M + 1, NP = VK<D, M>::NP, NC = Dims<D, M>::NC;
   constexpr bool STAGE = kGradStage<D, M, T>;
   constexpr int T0S = 0, GS = STAGE ? 1 : 0;  // LDS slots
-  __shared__ T lds[(STAGE ? 2 : 1) * NP * 64];
+  __shared__ T lds[(STAGE ? 2 : kKeepG1<D, M, T> ? 2 : 1) * NP * 64];
   const LaneLds<T> L{lds, (int)threadIdx.x};
   int32_t j[3];
   if (!node_of_block<D>(g, blockIdx.x, j)) return;
