@@ -1151,11 +1151,15 @@ bool make_grid(const hl_plan_s* pl, const int32_t* tile, int32_t ygroup, const i
   g->soff = soff;
   g->tx = tile[0];
   g->ty = tile[1];
-  // whole 128-byte lines per row (the narrowest word of a row: FP32_COMP's BF16 lo words), and a state past the
-  // 256 MB last-level cache
   g->open = 0;
+  // whole 128-byte lines per row (the narrowest word of a row: FP32_COMP's BF16
+  // lo words), and a state past the 256 MB last-level cache; at m = 0 in 1D and
+  // 2D, FP64 and FP32_COMP, past half the L2s' 32 MB, whose dirty lines a kernel
+  // of so few operations would otherwise end by writing back (step of 2e6 nodes
+  // FP64, streamed / cached: 11.6 / 13.0 us)
+  const int64_t past = (pl->m == 0 && pl->d < 3 && pl->precision != HL_FP32 ? 16 : 256) * (int64_t)(1 << 20);
   const int64_t state = (int64_t)pl->nc * (pl->pnodes + pl->d * pl->unodes) * pl->word_bytes * pl->words_per_coef;
-  g->stream = ooff == 0 && (int64_t)oext[0] * pl->word_bytes % 128 == 0 && state > (int64_t)256 << 20;
+  g->stream = ooff == 0 && (int64_t)oext[0] * pl->word_bytes % 128 == 0 && state > past;
   g->onodes = onodes;
   g->snodes = snodes;
   return true;

@@ -196,9 +196,12 @@ hipError_t launch_p(const PlanView& pv, void* p, const void* u, hipStream_t s) {
       hipLaunchKernelGGL((p_half_3d<M, S, kOneLayer>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
     else
       hipLaunchKernelGGL((p_half_3d<M, S, any_form<S1>(kOneLayer)>), grid_shape(g1), block, 0, s, vp, vu, (const T*)pv.tab, g1);
-  } else
-    hipLaunchKernelGGL((p_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vp, vu, (const T*)pv.tab,
-                       g);
+  } else if (g.stream)
+    hipLaunchKernelGGL((p_half_kernel<D, M, S, kStreamed>), grid_shape(g), block_shape(g), 0, s, vp, vu,
+                       (const T*)pv.tab, g);
+  else
+    hipLaunchKernelGGL((p_half_kernel<D, M, S, kCached>), grid_shape(g), block_shape(g), 0, s, vp, vu,
+                       (const T*)pv.tab, g);
   return hipGetLastError();
 }
 
@@ -219,9 +222,12 @@ hipError_t launch_u(const PlanView& pv, void* u, const void* p, double wscale, h
     else
       hipLaunchKernelGGL((u_half_3d<M, S, any_form<S1>(kOneLayer)>), grid_shape(g1), block, 0, s, vu, vp, (const T*)pv.tab, g1,
                          (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
-  } else
-    hipLaunchKernelGGL((u_half_kernel<D, M, S>), grid_shape(g), block_shape(g), 0, s, vu, vp, (const T*)pv.tab,
-                       g, (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
+  } else if (g.stream)
+    hipLaunchKernelGGL((u_half_kernel<D, M, S, kStreamed>), grid_shape(g), block_shape(g), 0, s, vu, vp,
+                       (const T*)pv.tab, g, (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
+  else
+    hipLaunchKernelGGL((u_half_kernel<D, M, S, kCached>), grid_shape(g), block_shape(g), 0, s, vu, vp,
+                       (const T*)pv.tab, g, (T)wscale, (T)pv.ih[0], (T)pv.ih[1], (T)pv.ih[2]);
   return hipGetLastError();
 }
 

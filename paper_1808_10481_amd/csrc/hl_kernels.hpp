@@ -248,33 +248,47 @@ __device__ __forceinline__ void update_outputs_as(const typename S::View& v, uin
   }
 }
 
-template <int D, class S, int N, class P, class F>
+// Whether a 1D or 2D half-step's streamed outputs are updated one by one: the
+// work-item's own wait for each store then spaces the streams.  One by one /
+// batched: 2D pressure m = 3 1024^2 FP64 114 / 131 us (cached outputs, 512^2,
+// 31.6 / 25.9); velocity m = 1 4096x2048 FP64 200 / 264 us, FP32_COMP 160 / 207
+// us, m = 2 2048x1500 FP64 191 / 224 us, but m = 3 1024^2 FP32_COMP 129 / 95 us;
+// 1D m = 1 2^24 nodes FP64 114 / 139 us, m = 5 406 / 447 us.
+template <int D, int M, bool VEL>
+constexpr bool kOneByOne = D == 1 || (D == 2 && (!VEL || M <= 2));
+
+// Which accesses a kernel's output update holds: both and the choice (kEither),
+// or one of them (1D and 2D half-steps, chosen by the launch).  The choice stands
+// between the outputs' loads and all before it, which half-steps of few data
+// feel (velocity 2D m = 1 4096x2048 FP64 222 us with it, 200 without).
+enum OutputMode { kEither, kCached, kStreamed };
+
+template <int D, class S, int N, bool ONE = false, int MODE = kEither, class P, class F>
 __device__ __forceinline__ void update_outputs(const Grid& g, const typename S::View& v, uint32_t n0, P plane, F f) {
-  if (g.stream)
-    update_outputs_as<D, S, N, true>(v, n0, plane, f);
-  else
-    update_outputs_as<D, S, N, false>(v, n0, plane, f);
+  if constexpr (MODE == kEither) {
+    if (g.stream)
+      update_outputs<D, S, N, ONE, kStreamed>(g, v, n0, plane, f);
+    else
+      update_outputs<D, S, N, ONE, kCached>(g, v, n0, plane, f);
+  } else if constexpr (MODE == kStreamed && ONE) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) S::store_nt(v, plane(i), n0, f(i, S::load_nt(v, plane(i), n0)));
+  } else {
+    update_outputs_as<D, S, N, MODE == kStreamed>(v, n0, plane, f);
+  }
 }
 
 // p -= acc at node n0.
-template <int D, int M, class S>
+template <int D, int M, class S, int MODE = kEither>
 __device__ __forceinline__ void finish_pressure(const Grid& g, const typename S::View& p, uint32_t n0,
                                                 const typename S::C* acc) {
   using T = typename S::C;
-  if constexpr (D == 2) {
-    // streamed 2D pressures one by one: FP64 m = 3 1024^2 114 us against 131
-    // batched (at 512^2, not streamed, 31.6 against 25.9)
-    if (g.stream) {
-#pragma unroll
-      for (int s = 0; s < Dims<D, M>::NC; ++s) S::store_nt(p, s, n0, S::load_nt(p, s, n0) - acc[s]);
-      return;
-    }
-  }
-  update_outputs<D, S, Dims<D, M>::NC>(g, p, n0, [](int s) { return s; }, [&](int s, T x) { return x - acc[s]; });
+  update_outputs<D, S, Dims<D, M>::NC, kOneByOne<D, M, false>, MODE>(g, p, n0, [](int s) { return s; },
+                                                                     [&](int s, T x) { return x - acc[s]; });
 }
 
 // u_i[s] -= wscale * (s_i + 1) / h_i * Q[s + e_i]   (Q on the set G)
-template <int D, int M, class S>
+template <int D, int M, class S, int MODE = kEither>
 __device__ __forceinline__ void finish_velocity(const Grid& g, const typename S::View& u, uint32_t n0,
                                                 const typename S::C* Q, typename S::C wscale, const typename S::C* ih) {
   using T = typename S::C;
@@ -282,7 +296,7 @@ __device__ __forceinline__ void finish_velocity(const Grid& g, const typename S:
   T f[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) f[i] = wscale * ih[i];
-  update_outputs<D, S, D * NC>(g, u, n0, [](int t) { return t; }, [&](int t, T x) {
+  update_outputs<D, S, D * NC, kOneByOne<D, M, true>, MODE>(g, u, n0, [](int t) { return t; }, [&](int t, T x) {
     const int i = t / NC, s = t % NC;
     const T a = -(T)(digit(s, MP, i) + 1) * f[i];
     return fma(a, Q[kGIndex<D, M>.g[i][s]], x);
@@ -375,7 +389,7 @@ __device__ __forceinline__ void p_half_acc(const typename S::View& u, TP tab, co
 }
 
 // Pressure half-step at every primal node (1D and 2D).
-template <int D, int M, class S, typename TP>
+template <int D, int M, class S, int MODE, typename TP>
 __device__ __forceinline__ void p_half_body(typename S::View p, typename S::View u,
                                             TP tab,
                                             Grid g, int blk) {
@@ -385,14 +399,14 @@ __device__ __forceinline__ void p_half_body(typename S::View p, typename S::View
   corner_nodes<D>(g, j, cn);  // dual q = j - 1 + e
   typename S::C acc[Dims<D, M>::NC];
   p_half_acc<D, M, S>(u, tab, cn, acc);
-  finish_pressure<D, M, S>(g, p, out_index<D>(g, j), acc);
+  finish_pressure<D, M, S, MODE>(g, p, out_index<D>(g, j), acc);
 }
 
-template <int D, int M, class S>
+template <int D, int M, class S, int MODE>
 __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) p_half_kernel(typename S::View p, typename S::View u,
                                                                        const typename S::C* __restrict__ tab,
                                                                        Grid g) {
-  p_half_body<D, M, S, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
+  p_half_body<D, M, S, MODE, const typename S::C* __restrict__>(p, u, tab, g, blockIdx.x);
 }
 
 // Q on the set G at a dual node from its primal corners (1D and 2D).
@@ -408,7 +422,7 @@ __device__ __forceinline__ void u_half_Q(const typename S::View& p, TP tab, cons
 }
 
 // Velocity half-step at every dual node (1D and 2D), weights scaled by wscale.
-template <int D, int M, class S, typename TP>
+template <int D, int M, class S, int MODE, typename TP>
 __device__ __forceinline__ void u_half_body(typename S::View u, typename S::View p,
                                             TP tab,
                                             Grid g, typename S::C wscale,
@@ -422,16 +436,16 @@ __device__ __forceinline__ void u_half_body(typename S::View u, typename S::View
   T Q[GSet<D, M>::NG];
   u_half_Q<D, M, S>(p, tab, cn, Q);
   const T ih[3] = {ih0, ih1, ih2};
-  finish_velocity<D, M, S>(g, u, out_index<D>(g, j), Q, wscale, ih);
+  finish_velocity<D, M, S, MODE>(g, u, out_index<D>(g, j), Q, wscale, ih);
 }
 
-template <int D, int M, class S>
+template <int D, int M, class S, int MODE>
 __global__ void __launch_bounds__(256, HL_WAVES_PER_EU) u_half_kernel(typename S::View u, typename S::View p,
                                                                        const typename S::C* __restrict__ tab,
                                                                        Grid g, typename S::C wscale,
                                                                        typename S::C ih0, typename S::C ih1,
                                                                        typename S::C ih2) {
-  u_half_body<D, M, S, const typename S::C* __restrict__>(u, p, tab, g, wscale, ih0, ih1, ih2, blockIdx.x);
+  u_half_body<D, M, S, MODE, const typename S::C* __restrict__>(u, p, tab, g, wscale, ih0, ih1, ih2, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------

@@ -1974,7 +1974,7 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * PShape<M, S, FORM>::NS
   else if constexpr (D == 3)
     p_half_3d_body<M, G, PShape<M, S, FORM>>(out, in, tab, sh.g, blk);
   else
-    p_half_body<D, M, G>(out, in, tab, sh.g, blk);
+    p_half_body<D, M, G, kEither>(out, in, tab, sh.g, blk);
 }
 
 template <int D, int M, class S, bool VAR, int FORM = kOneLayer>
@@ -1990,7 +1990,7 @@ __global__ void __launch_bounds__((!VAR && D == 3 ? 256 * UShape<M, S, FORM>::NS
   else if constexpr (D == 3)
     u_half_3d_body<M, G, UShape<M, S, FORM>>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
   else
-    u_half_body<D, M, G>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
+    u_half_body<D, M, G, kEither>(out, in, tab, sh.g, sh.wscale, sh.ih[0], sh.ih[1], sh.ih[2], blk);
 }
 
 // Variable kappa, 3D m >= 2, batched: one 64-wide workgroup per node of each
