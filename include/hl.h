@@ -147,7 +147,11 @@ hl_status hl_plan_info(hl_plan_t plan, hl_info* out);
  *                           device from the odd Taylor terms over dt/2
  *                           (velocity half-step with halved weights; the
  *                           even terms of u0 are dropped, exact for u0 = 0).
- * Synchronous: returns after the data are on the device. */
+ * Synchronous: returns after the data are on the device.  Host arrays cross in
+ * host layout through a device staging buffer of up to 64 MB, one per GPU,
+ * shared by its plans (hl_init, hl_export, hl_set_kappa, hl_kappa_grad) and
+ * freed with the last of them; calls that overlap or need more allocate up to
+ * 256 MB for their duration, and without device memory the host converts. */
 #define HL_INIT_STARTUP 1u
 hl_status hl_init(hl_plan_t plan, const double* p0, const double* u0, uint32_t flags,
                   void* p, void* u, void* stream);
@@ -165,7 +169,8 @@ hl_status hl_export(hl_plan_t plan, const void* p, const void* u,
  * given; a new pair re-captures.  1D with constant kappa in HL_FP64 and
  * HL_FP32 needs no graph: one launch takes many steps (all of them where one
  * workgroup holds the grid; else several workgroups, from 4 steps on and not
- * on a stream under capture, through a second pair of buffers of the plan).
+ * on a stream under capture, through a second pair of buffers of the plan,
+ * allocated by hl_plan for states up to 64 MB).
  * A plan is not safe to use from several host threads at once. */
 hl_status hl_step(hl_plan_t plan, void* p, void* u, int64_t nsteps, void* stream);
 /* With HL_WALLS every pressure half-step (in hl_step and hl_p_half) is
@@ -276,7 +281,7 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
  * step) for each candidate shape (1D: 256, 128, 64; 2D/3D: 64x4, 64x2, 64x1,
  * 128x2, 128x1, 256x1, 32x8, in 3D each with y-groups 1, 2, 4) on copies of
  * (p, u) in device buffers it allocates for the call and frees, keeps the
- * fastest and reports it through hl_plan_info; p and u are not modified.  A
+ * fastest and reports it through hl_plan_info; p and u are not modified.   A
  * batch launches its shots with their common shape when they all have the
  * same one (read when hl_batch_step builds its descriptors), else with the
  * default.  Synchronous. */

@@ -191,8 +191,6 @@ struct hl_plan_s {
   void* fp = nullptr;
   void* fu = nullptr;
   double* gpart = nullptr;     // partial sums, for the workgroups of any tile
-  void* stage = nullptr;       // staging of host-layout data (convert_component), at most kStageKeep
-  size_t stage_bytes = 0;
   double* dpartial = nullptr;  // norms scratch, kNormBlocks per plane
   int device = 0;
   // hl_step replays a captured graph of kGraphChunk steps for the last
@@ -740,36 +738,68 @@ __global__ void check_finite(const double* __restrict__ x, int64_t n, int* __res
   if (b) *bad = 1;
 }
 
-// A staging buffer of at least `bytes`: the plan's own up to kStageKeep (kept
-// until the plan is destroyed), a temporary one beyond.  NULL: no memory.
-constexpr size_t kStageKeep = (size_t)64 << 20;  // kept with the plan
-using hl_host::kStageMost;                       // per call; larger components go slab by slab
+// Staging of host-layout data: one buffer per device of at most kStageKeep,
+// shared by the device's plans and freed with the last of them.  One call holds
+// it at a time; a call that finds it taken, or needs more, allocates a temporary
+// one.  NULL: no memory, or zero bytes asked for.
+constexpr size_t kStageKeep = (size_t)64 << 20;
+using hl_host::kStageMost;  // per call; larger components go slab by slab
+constexpr int kMaxDevices = 64;
+struct StagePool {
+  std::mutex in_use;
+  void* ptr = nullptr;
+  size_t bytes = 0;
+  std::mutex count_mu;
+  int plans = 0;
+  void count(int by) {
+    std::lock_guard<std::mutex> lk(count_mu);
+    plans += by;
+    if (plans > 0) return;
+    std::lock_guard<std::mutex> use(in_use);
+    if (ptr) (void)hipFree(ptr);
+    ptr = nullptr;
+    bytes = 0;
+  }
+};
+StagePool g_stage[kMaxDevices];
+StagePool* stage_pool(int device) { return device >= 0 && device < kMaxDevices ? &g_stage[device] : nullptr; }
+
 struct Staging {
   void* ptr = nullptr;
-  bool own = false;
-  Staging(hl_plan_s* pl, size_t bytes) {
-    if (bytes > kStageKeep) {
-      own = hipMalloc(&ptr, bytes) == hipSuccess;
-      if (!own) ptr = nullptr;
-    } else {
-      if (pl->stage_bytes < bytes) {
-        if (pl->stage) (void)hipFree(pl->stage);
-        pl->stage = nullptr;
-        pl->stage_bytes = 0;
-        if (hipMalloc(&pl->stage, bytes) == hipSuccess)
-          pl->stage_bytes = bytes;
+  bool busy = false;  // work may still use it
+  Staging(const hl_plan_s* pl, size_t bytes) {
+    if (bytes == 0) return;
+    pool = bytes <= kStageKeep ? stage_pool(pl->device) : nullptr;
+    if (pool && !pool->in_use.try_lock()) pool = nullptr;
+    if (pool) {
+      if (pool->bytes < bytes) {
+        if (pool->ptr) (void)hipFree(pool->ptr);
+        pool->ptr = nullptr;
+        pool->bytes = 0;
+        if (hipMalloc(&pool->ptr, bytes) == hipSuccess)
+          pool->bytes = bytes;
         else
-          pl->stage = nullptr;
+          pool->ptr = nullptr;
       }
-      ptr = pl->stage;
+      ptr = pool->ptr;
+    } else if (hipMalloc(&own, bytes) == hipSuccess) {
+      ptr = own;
+    } else {
+      own = nullptr;
     }
     if (!ptr) (void)hipGetLastError();
   }
   ~Staging() {
-    if (own) (void)hipFree(ptr);
+    if (busy) (void)hipDeviceSynchronize();
+    if (own) (void)hipFree(own);
+    if (pool) pool->in_use.unlock();
   }
   Staging(const Staging&) = delete;
   Staging& operator=(const Staging&) = delete;
+
+ private:
+  StagePool* pool = nullptr;  // locked
+  void* own = nullptr;
 };
 
 template <bool TO_PLANES>
@@ -1207,7 +1237,6 @@ constexpr int kNoAllocMaxPlanes = 3 * 64;  // d nc for 3D m = 3, the largest bui
 constexpr size_t kNoAllocWords = (size_t)kNormBlocks * kNoAllocMaxPlanes + 2;
 static __device__ __align__(256) double norm_scratch[kNoAllocWords];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 double* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1418,6 +1447,7 @@ hl_status hl_plan(const hl_problem* prob, hl_plan_t* out) {
       (void)hipGetLastError();
     }
   }
+  if (StagePool* pool = stage_pool(pl->device)) pool->count(1);
   *out = pl;
   return HL_OK;
 }
@@ -1431,10 +1461,11 @@ hl_status hl_plan_destroy(hl_plan_t plan) {
   if (plan->dadj) (void)hipFree(plan->dadj);
   for (void* q : {plan->dkap_p, plan->dkap_u, plan->tab_dk, plan->tab_rev, plan->fp, plan->fu,
                   (void*)plan->gpart, (void*)plan->gkp, (void*)plan->gku, plan->vscr, plan->wscr, plan->vzw,
-                  plan->ucw, plan->stage, plan->alt_p, plan->alt_u})
+                  plan->ucw, plan->alt_p, plan->alt_u})
     if (q) (void)hipFree(q);
   if (plan->alt_done) (void)hipEventDestroy(plan->alt_done);
   if (plan->dpartial) (void)hipFree(plan->dpartial);
+  if (StagePool* pool = stage_pool(plan->device)) pool->count(-1);
   delete plan;
   return HL_OK;
 }
@@ -1616,6 +1647,7 @@ hl_status hl_set_kappa(hl_plan_t plan, const double* kappa_p, const double* kapp
   double* staged = static_cast<double*>(buf.ptr);
   if (!both) staged = nullptr;
   if (staged) {
+    buf.busy = true;
     int* flag = reinterpret_cast<int*>(staged + words[0] + words[1]);
     int bad = 0;
     e = hipMemcpy(staged, kappa_p, words[0] * 8, hipMemcpyHostToDevice);
@@ -1663,6 +1695,7 @@ hl_status hl_set_kappa(hl_plan_t plan, const double* kappa_p, const double* kapp
     if (e != hipSuccess) return hip_fail(e, "hl_set_kappa: copy to device");
   }
   e = hipDeviceSynchronize();  // the staging buffer is read until here
+  buf.busy = false;
   if (e != hipSuccess) return hip_fail(e, "hl_set_kappa: copy to device");
   plan->var_kappa = true;
   return HL_OK;
