@@ -658,14 +658,14 @@ struct StageShape {
 };
 // Every work-item loads its own corners (the tile's work-items as they are):
 // m = 0, whose three data (pressure; one for the velocity) are not worth the
-// staging's barriers and address arithmetic.  m = 0, staged / direct: step of
+// staging's barriers and address arithmetic, and FP32 batches (kBatchForm).  m = 0, staged / direct: step of
 // 192^3 FP32 130 / 70 us, FP32_COMP 178 / 102 us, FP64 162 / 137 us; transposed
 // step of 161x150x143 FP32_COMP 372 / 125 us.
 struct DirectShape {
   static constexpr bool DIRECT = true;
   static constexpr int NS = 1, TZ = 1, LDS = 1;
 };
-// The default tile with its layers, with one layer, and any tile.
+// The default tile with its layers, with one layer, any tile, and no staging.
 enum StageForm { kLayered, kOneLayer, kAnyTile, kDirect };
 template <int NS, int TZ, int FORM>
 struct ShapeOf {
@@ -933,8 +933,7 @@ __device__ __forceinline__ void direct_datum(const typename S::View& f, const ui
 template <int NQ, class S, class F, int... Q>
 __device__ __forceinline__ void direct_loop(const typename S::View& f, const uint32_t* cn, F& apply,
                                             std::integer_sequence<int, Q...>) {
-  // all of m = 0's data at once; one ahead of FP64 words, which wait on memory
-  constexpr int W = NQ <= 3 ? NQ : S::kBytes == 8 ? 2 : 1;
+  constexpr int W = NQ <= 3 ? NQ : 1;  // all of m = 0's data at once
   typename S::C v[W][8];
 #pragma unroll
   for (int q = 0; q + 1 < W; ++q) direct_load<S>(f, q, cn, v[q]);
