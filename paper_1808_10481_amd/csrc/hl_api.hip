@@ -1219,6 +1219,30 @@ bool valid_tile(int d, int32_t tx, int32_t ty) {
   return n >= 64 && n <= 256;
 }
 
+// The tile a plan starts with: the kernels' default, or where its launch would
+// not stay below 2^32 work-items (3D grids of 2^23 layers and more of a few nodes:
+// from m = 2 on a tile has two wavefront classes, 512 work-items) one of fewer
+// work-items per layer.
+void default_tile(const hl_plan_s* pl, int32_t* tx, int32_t* ty) {
+  *tx = pl->ks.tile[0];
+  *ty = pl->ks.tile[1];
+  if (pl->d < 3) return;
+  const int classes = pl->m >= 2 ? 2 : 1;
+  const int32_t shapes[][2] = {{pl->ks.tile[0], pl->ks.tile[1]}, {32, 4}, {64, 1}};
+  for (const auto& sh : shapes) {
+    int64_t n = hl::class_items(sh[0], sh[1], 1) * classes;
+    for (int k = 0; k < 3; ++k) {
+      const int64_t nodes = std::max(pl->pext[k], pl->uext[k]);
+      n *= k < 2 ? (nodes + sh[k] - 1) / sh[k] : nodes;
+    }
+    if (n + 512 * hl::kXcds <= (int64_t)UINT32_MAX) {  // with the last workgroups' rounding up to the XCDs
+      *tx = sh[0];
+      *ty = sh[1];
+      return;
+    }
+  }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1369,7 +1393,9 @@ hl_status hl_plan(const hl_problem* prob, hl_plan_t* out) {
     delete pl;
     return fail(HL_ERR_UNSUPPORTED, "hl_plan: (d, m, precision) not built");
   }
-  if (!build_grids(pl, pl->ks.tile[0], pl->ks.tile[1], 0, &pl->gp, &pl->gu)) {
+  int32_t tx, ty;
+  default_tile(pl, &tx, &ty);
+  if (!build_grids(pl, tx, ty, 0, &pl->gp, &pl->gu)) {
     delete pl;
     return fail(HL_ERR_UNSUPPORTED, "hl_plan: grid too large for the launch");
   }
@@ -1846,10 +1872,7 @@ hl_status hl_set_tile(hl_plan_t plan, int32_t tx, int32_t ty, int32_t ygroup) {
   g_last_error.clear();
   hl_status st = check_plan(plan, "hl_set_tile");
   if (st != HL_OK) return st;
-  if (tx == 0 && ty == 0) {
-    tx = plan->ks.tile[0];
-    ty = plan->ks.tile[1];
-  }
+  if (tx == 0 && ty == 0) default_tile(plan, &tx, &ty);
   if (!valid_tile(plan->d, tx, ty))
     return fail(HL_ERR_ARG, "hl_set_tile: tx a multiple of 32 in [32, 256], ty >= 1 (1 in 1D), 64 <= tx ty <= 256");
   if (ygroup < 0) return fail(HL_ERR_ARG, "hl_set_tile: ygroup must be >= 0");
