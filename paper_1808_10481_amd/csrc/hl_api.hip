@@ -2040,9 +2040,11 @@ hl_status hl_kappa_grad(hl_plan_t plan, double* grad_p, double* grad_u, int rese
       }
       if (e != hipSuccess) return hip_fail(e, "hl_kappa_grad: copy to host");
     }
-    if (reset && (e = clear_device(dev[f], (size_t)(np * nodes[f]) * sizeof(double))) != hipSuccess)
+    if (reset && (e = hipMemset(dev[f], 0, (size_t)(np * nodes[f]) * sizeof(double))) != hipSuccess)
       return hip_fail(e, "hl_kappa_grad: reset");
   }
+  // both are clear on return, also for streams that do not wait for the null stream
+  if (reset && (e = hipStreamSynchronize(nullptr)) != hipSuccess) return hip_fail(e, "hl_kappa_grad: reset");
   return HL_OK;
 }
 
