@@ -274,7 +274,8 @@ hl_status hl_adjoint_step(hl_plan_t plan, void* p_bar, void* u_bar, const void* 
  * same arithmetic whatever the tile, so results do not depend on it.
  * hl_set_tile: tiles of tx x ty nodes (tx a multiple of 32 in [32, 256],
  * ty >= 1, 1 in 1D, 64 <= tx ty <= 256; tx = ty = 0: the default 64 x 4, or
- * 256 in 1D; less in 3D where 2^23 layers would make the launch too large) and, in 3D, tile rows per group in the XCD-banded tile order
+ * 256 in 1D; less in 3D where 2^23 layers would make the launch too large) and,
+ * in 3D, tile rows per group in the XCD-banded tile order
  * (ygroup, 0: the default, 4, or 2 with variable kappa and at m = 0;
  * hl_plan_info reports the half-steps' value, clamped to the tile rows there
  * are).  hl_tune: times `reps` steps (after one warm-up
